@@ -25,43 +25,77 @@ namespace mp {
 constexpr size_t kLdsLimit = 160 * 1024 - 1024;
 constexpr int kWaves = 4;  // waves per workgroup in the row-MLP lock-step kernels
 
-// LDS staging of a ROWS-row block of a W-wide operand, transposed: element
-// (row r, feature f) sits at tile[f * RS + r], so the MFMA operands of the
-// weight-gradient products (rows along K) are contiguous 16-byte reads.
-// Each feature row is padded (4 floats, or 8 bf16 values) to spread banks.
+// LDS staging of a ROWS-row block of a W-wide operand for the weight-gradient
+// products, whose reduction runs over the rows.
+//
+// FP32: transposed, element (row r, feature f) at tile[f * RS + r], so a lane
+// reads four rows of one feature at once.  Each feature row is padded by 4
+// floats to spread banks.
+//
+// BF16: row major, as the rows are held, and transposed on the way out by
+// ds_read_b64_tr_b16 (each 16-lane group reads four rows of 16 features and
+// lane i receives the four rows of feature i).  A lane's four consecutive
+// features go out as one 8-byte store instead of four 2-byte stores into a
+// transposed tile: 4 stores per 64-wide row and lane for 16.  The 8-byte
+// chunk c of row r sits at chunk c ^ stg_swz(r): with 32 chunks per LDS bank
+// cycle the 32 lanes of a half wave then hit all banks once, in the stores
+// (16 rows, two chunks each) and in the reads (8 rows, four chunks each),
+// with no padding.  Against the transposed tile: k_row_dw at H = 128 (bound by
+// its staging) 1.82 -> 1.55 ms per layer of 6.1M edges, the fused edge adjoint
+// (bound by its row traffic) 3.08 -> 3.00 ms at 11.1M edges, 1.88 -> 1.78 ms
+// with BF16 edge states at 6.6M, and 16 registers fewer.
 template <bool BF, int ROWS>
 struct Stg {
   using T = typename std::conditional<BF, __bf16, float>::type;
-  static constexpr int RS = ROWS + (BF ? 8 : 4);
+  static constexpr int RS = ROWS + 4;  // FP32 feature-row stride
 };
 template <int W, bool BF, int ROWS = 64>
-constexpr size_t tile_bytes() { return size_t(W) * Stg<BF, ROWS>::RS * (BF ? 2 : 4); }
+constexpr size_t tile_bytes() { return BF ? size_t(W) * ROWS * 2 : size_t(W) * Stg<BF, ROWS>::RS * 4; }
 
-template <int W, bool BF, int ROWS = 64, bool PK = true>
+template <int W>
+__device__ __forceinline__ int stg_swz(int row) {
+  constexpr int U = W / 4;                 // 8-byte chunks per row
+  constexpr int RP = U >= 32 ? 1 : 32 / U;  // rows per 256 bytes of LDS
+  constexpr int KR = 8 / RP;               // such groups in 8 rows
+  const int k = (row & 15) / RP;
+  return ((k & (KR - 1)) << 2) | (((k / KR) & 1) << 1);
+}
+
+template <int W, bool BF, int ROWS = 64>
 __device__ __forceinline__ void stage_row(void* __restrict__ tile, int row, int g, const float (&v)[W / 4]) {
-  constexpr int RS = Stg<BF, ROWS>::RS;
-  if constexpr (BF && !PK) {
-    // one conversion per value (fewer live registers than the packed form)
-    __bf16* t = reinterpret_cast<__bf16*>(tile);
+  if constexpr (BF) {
+    const int sz = stg_swz<W>(row);
+    char* t = reinterpret_cast<char*>(tile) + row * (W * 2);
 #pragma unroll
-    for (int i = 0; i < W / 4; ++i) t[(16 * (i / 4) + 4 * g + (i % 4)) * RS + row] = (__bf16)v[i];
-  } else if constexpr (BF) {
-    // features f, f+1 (consecutive in the lane) are rounded as one pair and
-    // written as the low and high halves of the packed value
-    uint16_t* t = reinterpret_cast<uint16_t*>(tile);
-#pragma unroll
-    for (int i = 0; i < W / 4; i += 2) {
-      const int f = 16 * (i / 4) + 4 * g + (i % 4);
-      uint32_t pk = __builtin_bit_cast(uint32_t, v2bf{(__bf16)v[i], (__bf16)v[i + 1]});
-      asm volatile("" : "+v"(pk));  // keep the pair packed (one conversion, two half stores)
-      t[f * RS + row] = (uint16_t)pk;
-      t[(f + 1) * RS + row] = (uint16_t)(pk >> 16);
+    for (int b = 0; b < W / 16; ++b) {
+      const v4bf q = {(__bf16)v[4 * b], (__bf16)v[4 * b + 1], (__bf16)v[4 * b + 2], (__bf16)v[4 * b + 3]};
+      *reinterpret_cast<u32x2*>(t + ((4 * b + g) ^ sz) * 8) = __builtin_bit_cast(u32x2, q);
     }
   } else {
+    constexpr int RS = Stg<BF, ROWS>::RS;
     float* t = reinterpret_cast<float*>(tile);
 #pragma unroll
     for (int i = 0; i < W / 4; ++i) t[(16 * (i / 4) + 4 * g + (i % 4)) * RS + row] = v[i];
   }
+}
+
+// MFMA operand of a staged BF16 tile, rows along K: lane (i, kk) receives
+// feature 16 fb + i of rows r0 + 4 kk + 0..3 and r0 + 16 + 4 kk + 0..3 (r0 a
+// multiple of 16; the same row order for both operands of a product).
+// tr_base: the lane's address for feature block fb.
+typedef __attribute__((address_space(3))) v4bf lds_v4bf;
+template <int W>
+__device__ __forceinline__ const char* tr_base(const void* __restrict__ tile, int fb, int lane) {
+  const int row = 4 * (lane >> 4) + ((lane & 15) >> 2);
+  return reinterpret_cast<const char*>(tile) + row * (W * 2) + (((4 * fb + (lane & 3)) ^ stg_swz<W>(row)) * 8);
+}
+__device__ __forceinline__ v4bf tr_read4(const char* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_v4bf*)(p));
+}
+template <int W>
+__device__ __forceinline__ v8bf tr_read8(const char* base, int r0) {
+  const v4bf lo = tr_read4(base + r0 * (W * 2)), hi = tr_read4(base + (r0 + 16) * (W * 2));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
 template <int GW, int AW, int NW = kWaves>
@@ -70,7 +104,8 @@ constexpr int dw_tiles_per_wave() { return ((GW / 16) * (AW / 16) + NW - 1) / NW
 // acc[n] += sum over the 16*NW staged rows of G[f][row] * A[k][row] for the
 // tiles t = wave + NW*n (t = fb * (AW/16) + kb) this wave owns.
 // FP32: v_mfma_f32_16x16x4f32, lane (i, kk) covering rows kk*4NW + s;
-// BF16: v_mfma_f32_16x16x32_bf16, lane (i, kk) covering rows 32t + 8kk + q.
+// BF16: v_mfma_f32_16x16x32_bf16, lane (i, kk) covering rows 32t + 4kk + q
+// and 32t + 16 + 4kk + q (tr_read8).
 template <int GW, int AW, bool BF, int NW = kWaves>
 __device__ __forceinline__ void dw_tiles(const void* __restrict__ G, const void* __restrict__ A,
                                          v4f (&acc)[dw_tiles_per_wave<GW, AW, NW>()], int wave, int lane) {
@@ -83,14 +118,12 @@ __device__ __forceinline__ void dw_tiles(const void* __restrict__ G, const void*
     if (t < NTILE) {
       const int fb = t / KBN, kb = t % KBN;
       if constexpr (BF) {
-        const __bf16* g = reinterpret_cast<const __bf16*>(G) + (16 * fb + li) * RS + 8 * kk;
-        const __bf16* a = reinterpret_cast<const __bf16*>(A) + (16 * kb + li) * RS + 8 * kk;
+        const char* g = tr_base<GW>(G, fb, lane);
+        const char* a = tr_base<AW>(A, kb, lane);
 #pragma unroll
-        for (int tt = 0; tt < ROWS / 32; ++tt) {
-          const v8bf gv = *reinterpret_cast<const v8bf*>(g + 32 * tt);
-          const v8bf av = *reinterpret_cast<const v8bf*>(a + 32 * tt);
-          acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gv, av, acc[n], 0, 0, 0);
-        }
+        for (int tt = 0; tt < ROWS / 32; ++tt)
+          acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr_read8<GW>(g, 32 * tt), tr_read8<AW>(a, 32 * tt), acc[n],
+                                                           0, 0, 0);
       } else {
         const float* g = reinterpret_cast<const float*>(G) + (16 * fb + li) * RS + (ROWS / 4) * kk;
         const float* a = reinterpret_cast<const float*>(A) + (16 * kb + li) * RS + (ROWS / 4) * kk;
@@ -127,19 +160,15 @@ struct ColSum {
     for (int q = 0; q < NA; ++q) acc[q] = v4f{0.f, 0.f, 0.f, 0.f};
   }
   __device__ __forceinline__ void add(const void* __restrict__ tile, int wave, int lane) {
-    constexpr int RS = Stg<true, 16 * NW>::RS;
     const v8bf ones = __builtin_bit_cast(v8bf, uint4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u});
-    const int li = lane & 15, kk = lane >> 4;
 #pragma unroll
     for (int q = 0; q < NA; ++q) {
       const int fb = FBN > NW ? wave + q * NW : wave % FBN;
       const int c0 = FBN >= NW ? 0 : wave / FBN;
-      const __bf16* t = reinterpret_cast<const __bf16*>(tile) + (16 * fb + li) * RS + 8 * kk;
+      const char* t = tr_base<W>(tile, fb, lane);
 #pragma unroll
-      for (int k = 0; k < CPW; ++k) {
-        const v8bf a = *reinterpret_cast<const v8bf*>(t + 32 * (c0 + k * WPF));
-        acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, acc[q], 0, 0, 0);
-      }
+      for (int k = 0; k < CPW; ++k)
+        acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr_read8<W>(t, 32 * (c0 + k * WPF)), ones, acc[q], 0, 0, 0);
     }
   }
   // Sum the waves' partials in a fixed order and write the W sums to dst.
@@ -167,31 +196,35 @@ struct ColSum {
 };
 
 // The same column sums on the vector ALU (one float per thread instead of
-// MFMA accumulators, for kernels short of registers): thread t adds the
-// rows of segment t / W of feature t % W; store() adds the segments in order.
+// MFMA accumulators, for kernels short of registers): lane (i, kk) of a wave
+// adds rows 16 q + 4 kk + 0..3 of feature 16 fb + i over the wave's 16-row
+// blocks q; store() adds the partials in order.
 template <int W, int NW>
 struct ColSumValu {
-  static constexpr int ROWS = 16 * NW, RS = Stg<true, ROWS>::RS, NSEG = 64 * NW / W, LEN = ROWS / NSEG;
-  static_assert(NSEG >= 1 && LEN % 8 == 0, "segment layout");
+  static constexpr int FBN = W / 16;        // feature blocks
+  static_assert(FBN <= NW && NW % FBN == 0, "column-sum layout");
+  static constexpr int WPF = NW / FBN;      // waves per feature block
+  static constexpr int QPW = NW / WPF;      // 16-row blocks per wave
   float acc;
   __device__ __forceinline__ void zero() { acc = 0.f; }
-  __device__ __forceinline__ void add(const void* __restrict__ tile, int, int) {
-    const int f = threadIdx.x % W, sg = threadIdx.x / W;
-    const __bf16* p = reinterpret_cast<const __bf16*>(tile) + f * RS + sg * LEN;
+  __device__ __forceinline__ void add(const void* __restrict__ tile, int wave, int lane) {
+    const char* t = tr_base<W>(tile, wave % FBN, lane) + (wave / FBN) * QPW * 16 * (W * 2);
 #pragma unroll
-    for (int r = 0; r < LEN; r += 8) {
-      const v8bf q = *reinterpret_cast<const v8bf*>(p + r);
+    for (int q = 0; q < QPW; ++q) {
+      const v4bf v = tr_read4(t + q * 16 * (W * 2));
 #pragma unroll
-      for (int c = 0; c < 8; ++c) acc += (float)q[c];
+      for (int c = 0; c < 4; ++c) acc += (float)v[c];
     }
   }
-  __device__ __forceinline__ void store(float* __restrict__ scratch, float* __restrict__ dst, int, int) const {
+  __device__ __forceinline__ void store(float* __restrict__ scratch, float* __restrict__ dst, int wave,
+                                        int lane) const {
     __syncthreads();
-    scratch[threadIdx.x] = acc;
+    // [wave / FBN][kk][feature]
+    scratch[((wave / FBN) * 4 + (lane >> 4)) * W + 16 * (wave % FBN) + (lane & 15)] = acc;
     __syncthreads();
     if ((int)threadIdx.x < W) {
       float sum = 0.f;
-      for (int sg = 0; sg < NSEG; ++sg) sum += scratch[sg * W + threadIdx.x];
+      for (int sg = 0; sg < 4 * WPF; ++sg) sum += scratch[sg * W + threadIdx.x];
       dst[threadIdx.x] = sum;
     }
     __syncthreads();
@@ -682,7 +715,7 @@ hipError_t launch_edge_bwd(const EdgeBwdArgs& a, int grid, hipStream_t s) {
   if (a.es && !a.bf) return hipErrorInvalidValue;
 #define MP_CASE(HH) \
   if (a.H == HH) return a.bf ? launch_edge_bwd_t<HH, true>(a, grid, s) : launch_edge_bwd_t<HH, false>(a, grid, s);
-  MP_CASE(32) MP_CASE(64) MP_CASE(128)
+  MP_CASE(32) MP_CASE(64)  // wider layers: launch_edge_bwd_split
 #undef MP_CASE
   return hipErrorInvalidValue;
 }
@@ -1439,7 +1472,6 @@ template <int H, int KIN, bool TIN, bool TOUT, bool BF, bool GB>
 __global__ __launch_bounds__((64 * MlpBwdCfg<H, KIN, TIN, TOUT, BF>::NW)) void k_mlp_bwd(MlpBwdArgs a) {
   using C = MlpBwdCfg<H, KIN, TIN, TOUT, BF>;
   using In = MlpBwdIn<H, KIN, TIN, TOUT, GB>;
-  constexpr bool PK = KIN != 2 * H;  // packed BF16 staging, except where registers are short
   constexpr int NF = H / 4, MB = H / 16, KB = TIN ? 1 : KIN / 16, AW0 = C::AW0, NW = C::NW, ROWS = C::ROWS;
   constexpr int NT1 = TOUT ? dw_tiles_per_wave<16, H, NW>() : dw_tiles_per_wave<H, H, NW>();
   constexpr int NT0 = dw_tiles_per_wave<H, AW0, NW>();
@@ -1570,9 +1602,9 @@ __global__ __launch_bounds__((64 * MlpBwdCfg<H, KIN, TIN, TOUT, BF>::NW)) void k
         float in16[4];  // lane group g holds input features 4g..4g+3
 #pragma unroll
         for (int k = 0; k < 4; ++k) in16[k] = g == 0 ? cur.in[k] : 0.f;
-        stage_row<16, BF, ROWS, PK>(tA0, srow, g, in16);
+        stage_row<16, BF, ROWS>(tA0, srow, g, in16);
       } else {
-        stage_row<KIN, BF, ROWS, PK>(tA0, srow, g, cur.in);
+        stage_row<KIN, BF, ROWS>(tA0, srow, g, cur.in);
       }
     };
     if constexpr (C::SEP_A0) stage_in();
@@ -1600,8 +1632,8 @@ __global__ __launch_bounds__((64 * MlpBwdCfg<H, KIN, TIN, TOUT, BF>::NW)) void k
       float go16[4];
 #pragma unroll
       for (int o = 0; o < 4; ++o) go16[o] = g == 0 ? cur.go[o] : 0.f;
-      stage_row<16, BF, ROWS, PK>(tG, srow, g, go16);
-      stage_row<H, BF, ROWS, PK>(tA, srow, g, u);
+      stage_row<16, BF, ROWS>(tG, srow, g, go16);
+      stage_row<H, BF, ROWS>(tA, srow, g, u);
       if constexpr (!C::ONE) {
         __syncthreads();
         phase1_products();
@@ -1632,8 +1664,8 @@ __global__ __launch_bounds__((64 * MlpBwdCfg<H, KIN, TIN, TOUT, BF>::NW)) void k
           float t[NF];
 #pragma unroll
           for (int i = 0; i < NF; ++i) t[i] = go[i] * y[i];
-          stage_row<H, BF, ROWS, PK>(tGE, srow, g, cur.go);
-          stage_row<H, BF, ROWS, PK>(tGM, srow, g, t);
+          stage_row<H, BF, ROWS>(tGE, srow, g, cur.go);
+          stage_row<H, BF, ROWS>(tGM, srow, g, t);
         }
         if constexpr (C::TP) {  // rows past n carry go = 0
           float t[NF], rs[1];
@@ -1661,8 +1693,8 @@ __global__ __launch_bounds__((64 * MlpBwdCfg<H, KIN, TIN, TOUT, BF>::NW)) void k
 #pragma unroll
         for (int i = 0; i < NF; ++i) db1[i] += y[i];
       }
-      stage_row<H, BF, ROWS, PK>(tG, srow, g, y);
-      stage_row<H, BF, ROWS, PK>(tA, srow, g, u);
+      stage_row<H, BF, ROWS>(tG, srow, g, y);
+      stage_row<H, BF, ROWS>(tA, srow, g, u);
       if constexpr (!C::ONE) {
         __syncthreads();
         phase1_products();
@@ -1686,7 +1718,7 @@ __global__ __launch_bounds__((64 * MlpBwdCfg<H, KIN, TIN, TOUT, BF>::NW)) void k
 #pragma unroll
       for (int i = 0; i < NF; ++i) db0[i] += gu[i];
     }
-    stage_row<H, BF, ROWS, PK>(tG0, srow, g, gu);
+    stage_row<H, BF, ROWS>(tG0, srow, g, gu);
     if constexpr (!C::SEP_A0) stage_in();
     __syncthreads();
     if constexpr (C::ONE) phase1_products();
@@ -1799,7 +1831,9 @@ static hipError_t launch_mlp_bwd_h(const MlpBwdArgs& a, int grid, hipStream_t s)
   if (tin && !tout) return launch_mlp_bwd_t<H, 4, true, false, BF>(a, grid, s);
   if (!tin && kin == H && tout) return launch_mlp_bwd_t<H, H, false, true, BF>(a, grid, s);
   if (!tin && kin == H && !tout) return launch_mlp_bwd_t<H, H, false, false, BF>(a, grid, s);
-  if (!tin && kin == 2 * H && !tout) return launch_mlp_bwd_t<H, 2 * H, false, false, BF>(a, grid, s);
+  if constexpr (!node_bwd_split(H, BF)) {
+    if (!tin && kin == 2 * H && !tout) return launch_mlp_bwd_t<H, 2 * H, false, false, BF>(a, grid, s);
+  }
   return hipErrorInvalidValue;
 }
 
