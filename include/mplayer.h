@@ -212,8 +212,8 @@ typedef struct {
    * weight-gradient sums): waves per workgroup of the edge adjoint (4, or
    * 8 for BF16 GEMMs at H <= 64, which stage 16 x waves edges per
    * weight-gradient round, and at H > 64, whose split adjoint then runs
-   * two waves per SIMD instead of one), and the tile order of the edge
-   * forward (0: a
+   * two waves per SIMD instead of one; FP32 at H <= 64 has one form), and
+   * the tile order of the edge forward (0: a
    * fixed round robin over each XCD's range of tiles; 1: waves take the
    * next tile of their XCD's range from an atomic counter and move on to
    * the other ranges when theirs is empty; tiles are row aligned, so the

@@ -1,0 +1,183 @@
+// Pieces shared by the adjoint kernels: weight gradients of FP32 products, the
+// segmented receiver sum of an edge block, sums over a workgroup's rows.
+#pragma once
+#include <algorithm>
+
+#include "mp_device.hpp"
+#include "mp_kernels.hpp"
+
+namespace mp {
+
+constexpr size_t kLdsLimit = 160 * 1024 - 1024;
+constexpr int kWaves = 4;  // waves per workgroup in the row-MLP lock-step kernels
+
+// Sum a per-lane row-block vector over all 16*NW rows of the workgroup (16
+// lanes x NW waves) in a fixed order and write the W sums to dst.  Uses
+// `scratch` (at least 16*NW*W floats of LDS); contains barriers.
+template <int W, int NW = kWaves>
+__device__ __forceinline__ void block_sum_vec(const float (&v)[W / 4], float* __restrict__ scratch,
+                                              float* __restrict__ dst, int wave, int lane) {
+  const int j = lane & 15, g = lane >> 4;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < W / 4; ++i) scratch[(wave * 16 + j) * W + 16 * (i / 4) + 4 * g + (i % 4)] = v[i];
+  __syncthreads();
+  for (int t = threadIdx.x; t < W; t += blockDim.x) {
+    float s = 0.f;
+    for (int r = 0; r < 16 * NW; ++r) s += scratch[r * W + t];
+    dst[t] = s;
+  }
+  __syncthreads();
+}
+
+// The BF16 matrix instruction loses low bits of its partial sums downwards: a
+// bias of some 2^-27 of a term, nothing in one product, but a weight gradient
+// adds millions of terms of either sign and the bias then outgrows their sum
+// (3.5M edges: 4.5e-6 of the gradient, 1.5e-6 with FP32 instructions).  Every
+// other workgroup of an XCD therefore sums -G^T A (the staged parts of G with
+// their signs flipped) and negates its result, so the bias cancels: 0.9e-6.
+__device__ __forceinline__ uint32_t dw_sign_mask() { return (blockIdx.x >> 3) & 1 ? 0x80008000u : 0u; }
+__device__ __forceinline__ float dw_sign() { return (blockIdx.x >> 3) & 1 ? -1.f : 1.f; }
+template <int W>
+__device__ __forceinline__ void flip_op(Op<false, W>& o, uint32_t mask) {
+#pragma unroll
+  for (int t = 0; t < W / 32; ++t) {
+    v4u h = __builtin_bit_cast(v4u, o.h[t]), m = __builtin_bit_cast(v4u, o.m[t]), l = __builtin_bit_cast(v4u, o.l[t]);
+    h ^= mask;
+    m ^= mask;
+    l ^= mask;
+    o.h[t] = __builtin_bit_cast(v8bf, h);
+    o.m[t] = __builtin_bit_cast(v8bf, m);
+    o.l[t] = __builtin_bit_cast(v8bf, l);
+  }
+}
+
+// FP32 weight gradients dW += G^T A over the 16 rows one wave holds, from the
+// three BF16 parts of both factors staged in that wave's own LDS tiles
+// (stage_op, 16 rows): no other wave takes part, so nothing waits.  Sixteen
+// rows fill half of the matrix instruction's 32-long reduction; the other half
+// takes the same rows of another part: [Gh|Gm] [Ah|Am] = hh + mm, [Gh|Gm]
+// [Am|Ah] = hm + mh, [Gh|Gl] [Al|Ah] = hl + lh, so three instructions do the
+// six products, added straight onto the running sum (one third of the
+// roundings of the FP32 instruction's).
+template <int GW, int AW>
+struct DwWave {
+  static constexpr int FB = GW / 16, KB = AW / 16;
+  static constexpr int GP = 16 * GW * 2, AP = 16 * AW * 2;  // bytes of one part
+  static constexpr int TILE_G = 3 * GP, TILE_A = 3 * AP;
+  v4f acc[FB * KB];
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int n = 0; n < FB * KB; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
+  }
+  static __device__ __forceinline__ v8bf two(const char* p0, const char* p1) {
+    return __builtin_shufflevector(tr_read4(p0), tr_read4(p1), 0, 1, 2, 3, 4, 5, 6, 7);
+  }
+  __device__ __forceinline__ void add(const char* __restrict__ tG, const char* __restrict__ tA, int lane) {
+    v8bf hm[KB], mh[KB], lh[KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      const char* p = tr_base<AW>(tA, kb, lane);
+      hm[kb] = two(p, p + AP);
+      mh[kb] = two(p + AP, p);
+      lh[kb] = two(p + 2 * AP, p);
+    }
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb) {
+      const char* p = tr_base<GW>(tG, fb, lane);
+      const v8bf ghm = two(p, p + GP), ghl = two(p, p + 2 * GP);
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) acc[fb * KB + kb] = MP_MFMA_BF16(ghl, lh[kb], acc[fb * KB + kb]);
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) acc[fb * KB + kb] = MP_MFMA_BF16(ghm, mh[kb], acc[fb * KB + kb]);
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) acc[fb * KB + kb] = MP_MFMA_BF16(ghm, hm[kb], acc[fb * KB + kb]);
+    }
+  }
+  // Add the NW waves' sums in wave order and write sgn * them to dst, [GW][AW].
+  // Uses NW * GW * AW floats of `scratch`; contains barriers.
+  template <int NW>
+  __device__ __forceinline__ void store(float* __restrict__ scratch, float* __restrict__ dst, float sgn, int wave,
+                                        int lane) {
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < FB * KB; ++n) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        scratch[(wave * GW + 16 * (n / KB) + 4 * (lane >> 4) + v) * AW + 16 * (n % KB) + (lane & 15)] = acc[n][v];
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < GW * AW; t += blockDim.x) {
+      float sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) sum += scratch[w * GW * AW + t];
+      dst[t] = sgn * sum;
+    }
+    __syncthreads();
+  }
+};
+
+// Keep a wave's LDS stores ahead of its own reads of other lanes' data (LDS
+// operations of one wave complete in order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Indices of one edge per lane: receiver, sender, multiplicity, and the next
+// edge's receiver (-1 past the tile); past the tile's end those of e_last.
+struct EdgeIdx {
+  int ri, sj, md, nx;
+  __device__ __forceinline__ void fetch(const DevGraph& gr, int64_t k, int64_t e1, int64_t e_last) {
+    const int64_t kk = k < e1 ? k : e_last;
+    ri = gr.recv[kk];
+    sj = gr.col[kk];
+    md = gr.mult[kk];
+    nx = (k + 1 < e1) ? gr.recv[k + 1] : -1;
+  }
+  // Complete the loads here: the loop's entry state (or the stores that
+  // follow) then has no pending loads, else the compiler's wait for them
+  // also drains the stores.
+  __device__ __forceinline__ void settle() { asm volatile("" : "+v"(ri), "+v"(sj), "+v"(md), "+v"(nx)); }
+};
+
+// rows without incoming edges have g_P = 0
+template <int H>
+__device__ __forceinline__ void zero_empty_rows(const DevGraph& gr, int64_t r0, int64_t r1, float* __restrict__ g_P,
+                                                int lane) {
+  for (int64_t r = r0 + (lane >> 2); r < r1; r += 16) {
+    if (gr.rowptr[r] == gr.rowptr[r + 1]) {
+      float* dst = g_P + r * H;
+      for (int c = (lane & 3) * 4; c < H; c += 16) *reinterpret_cast<float4*>(dst + c) = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+}
+
+// g_P of one block: segmented sum of gh per receiver, the open row's partial
+// sum handed from lane 15 of one block to lane 0 of the next through LDS
+// (same wave, so no barrier is needed).  Lanes past the tile's last edge hold
+// gh = 0 and a key of their own, so they add nothing to any row's sum.
+template <int H>
+__device__ __forceinline__ void edge_gp(float (&t)[H / 4], float* __restrict__ carry, int& carry_key, int key,
+                                        bool last, float* __restrict__ dst, int j, int g) {
+  constexpr int NF = H / 4;
+  if (j == 0 && key == carry_key) {
+#pragma unroll
+    for (int i = 0; i < NF; i += 4) {
+      const float4 c = *reinterpret_cast<const float4*>(carry + i);
+      t[i] += c.x;
+      t[i + 1] += c.y;
+      t[i + 2] += c.z;
+      t[i + 3] += c.w;
+    }
+  }
+  seg_scan16<NF>(t, key);
+  if (last) store_row<H>(dst, g, t);
+  if (j == 15) {
+#pragma unroll
+    for (int i = 0; i < NF; i += 4) *reinterpret_cast<float4*>(carry + i) = make_float4(t[i], t[i + 1], t[i + 2], t[i + 3]);
+  }
+  carry_key = from_prev_lane_i(key);
+}
+
+}  // namespace mp

@@ -17,13 +17,12 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "mp_adjoint.hpp"
 #include "mp_device.hpp"
 #include "mp_kernels.hpp"
 
 namespace mp {
 
-constexpr size_t kLdsLimit = 160 * 1024 - 1024;
-constexpr int kWaves = 4;  // waves per workgroup in the row-MLP lock-step kernels
 
 // LDS staging of a ROWS-row block of a W-wide operand for the weight-gradient
 // products, whose reduction runs over the rows.
@@ -52,15 +51,6 @@ struct Stg {
 template <int W, bool BF, int ROWS = 64>
 constexpr size_t tile_bytes() { return BF ? size_t(W) * ROWS * 2 : size_t(W) * Stg<BF, ROWS>::RS * 4; }
 
-template <int W>
-__device__ __forceinline__ int stg_swz(int row) {
-  constexpr int U = W / 4;                 // 8-byte chunks per row
-  constexpr int RP = U >= 32 ? 1 : 32 / U;  // rows per 256 bytes of LDS
-  constexpr int KR = 8 / RP;               // such groups in 8 rows
-  const int k = (row & 15) / RP;
-  return ((k & (KR - 1)) << 2) | (((k / KR) & 1) << 1);
-}
-
 template <int W, bool BF, int ROWS = 64>
 __device__ __forceinline__ void stage_row(void* __restrict__ tile, int row, int g, const float (&v)[W / 4]) {
   if constexpr (BF) {
@@ -77,25 +67,6 @@ __device__ __forceinline__ void stage_row(void* __restrict__ tile, int row, int 
 #pragma unroll
     for (int i = 0; i < W / 4; ++i) t[(16 * (i / 4) + 4 * g + (i % 4)) * RS + row] = v[i];
   }
-}
-
-// MFMA operand of a staged BF16 tile, rows along K: lane (i, kk) receives
-// feature 16 fb + i of rows r0 + 4 kk + 0..3 and r0 + 16 + 4 kk + 0..3 (r0 a
-// multiple of 16; the same row order for both operands of a product).
-// tr_base: the lane's address for feature block fb.
-typedef __attribute__((address_space(3))) v4bf lds_v4bf;
-template <int W>
-__device__ __forceinline__ const char* tr_base(const void* __restrict__ tile, int fb, int lane) {
-  const int row = 4 * (lane >> 4) + ((lane & 15) >> 2);
-  return reinterpret_cast<const char*>(tile) + row * (W * 2) + (((4 * fb + (lane & 3)) ^ stg_swz<W>(row)) * 8);
-}
-__device__ __forceinline__ v4bf tr_read4(const char* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_v4bf*)(p));
-}
-template <int W>
-__device__ __forceinline__ v8bf tr_read8(const char* base, int r0) {
-  const v4bf lo = tr_read4(base + r0 * (W * 2)), hi = tr_read4(base + (r0 + 16) * (W * 2));
-  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
 template <int GW, int AW, int NW = kWaves>
@@ -252,26 +223,7 @@ __device__ __forceinline__ void dw_store(const v4f (&acc)[dw_tiles_per_wave<GW, 
   }
 }
 
-// Sum a per-lane row-block vector over all 16*NW rows of the workgroup (16
-// lanes x NW waves) in a fixed order and write the W sums to dst.  Uses
-// `scratch` (at least 16*NW*W floats of LDS); contains barriers.
-template <int W, int NW = kWaves>
-__device__ __forceinline__ void block_sum_vec(const float (&v)[W / 4], float* __restrict__ scratch,
-                                              float* __restrict__ dst, int wave, int lane) {
-  const int j = lane & 15, g = lane >> 4;
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < W / 4; ++i) scratch[(wave * 16 + j) * W + 16 * (i / 4) + 4 * g + (i % 4)] = v[i];
-  __syncthreads();
-  for (int t = threadIdx.x; t < W; t += blockDim.x) {
-    float s = 0.f;
-    for (int r = 0; r < 16 * NW; ++r) s += scratch[r * W + t];
-    dst[t] = s;
-  }
-  __syncthreads();
-}
-
-// The same for a vector reduced across each 16-lane group by sum16_scatter
+// block_sum_vec for a vector reduced across each 16-lane group by sum16_scatter
 // at H = 64 (one value per lane: lane j of group g holds feature
 // 16 (j / 4) + 4 g + j % 4): the lanes' values of all waves are added in
 // wave order.  Uses `scratch` (64 * NW floats of LDS); contains barriers.
@@ -309,40 +261,20 @@ __device__ __forceinline__ void stage_frags_rot(void* __restrict__ dst, const vo
 // ----------------------------------------------------------- edge adjoint
 
 
-template <int H, bool BF, int NWQ = 0>
+template <int H, int NWQ = 0>
 struct EdgeBwdCfg {
-  // Default: BF16 eight waves per workgroup (128 staged rows) so the
-  // fragments are shared by more waves; FP32 (MFMA-bound) and H=128: four
-  // waves.  NWQ (4 or 8) overrides it (a schedule dimension).
-  static constexpr int NW = NWQ ? NWQ : ((BF && H <= 64) ? 8 : 4);
+  // Default: eight waves per workgroup (128 staged rows) so the fragments are
+  // shared by more waves.  NWQ (4 or 8) overrides it (a schedule dimension).
+  static constexpr int NW = NWQ ? NWQ : 8;
   static constexpr int ROWS = 16 * NW;
-  // TP (FP32 at H = 64): two workgroups per CU, so two waves per SIMD (one
-  // wave's memory and LDS waits and barriers are covered by the other
-  // wave's work; FP32 matrix instructions do not issue beside VALU ones, so
-  // the gain is in the waits): the weight-gradient factors are staged in
-  // two rounds through one pair of tiles, only W1c and W2 sit in LDS (the
-  // transposed products read them at transposed addresses), db2 is a
-  // column sum of the staged gm tile and the LayerNorm-parameter sums are
-  // reduced across the block's lanes (sum16_scatter) into one register per
-  // lane, which brings the kernel to 245 VGPRs and 68 KB of LDS.  Measured on C4: 45.4 ->
-  // 40.6 ms per launch (one wave per SIMD with the next block's rows
-  // loaded ahead had given 47.7 -> 45.4); W1c / W2 in the rotated LDS
-  // layout (stage_frags_rot, no bank conflicts in the transposed reads):
-  // 40.1 -> 37.2 ms.
-  static constexpr bool TP = !BF && H == 64;
-  static constexpr int MINB = TP ? 2 : 1;
-  // BF16: bias / LayerNorm gradients are column sums of staged tiles instead
-  // of per-lane accumulators (frees registers); FP32 keeps them per lane.
-  static constexpr bool VEC = BF;
-  static constexpr int NTILES = TP ? 2 : (VEC ? 6 : 4);
-  static constexpr int NFRAG = TP ? 2 : 4;
-  static constexpr size_t FB = frag_bytes(H, H, BF);
-  static constexpr size_t TB = tile_bytes<H, BF, ROWS>();
+  static constexpr int NTILES = 6;
+  static constexpr size_t FB = frag_bytes(H, H, true);
+  static constexpr size_t TB = tile_bytes<H, true, ROWS>();
   static constexpr size_t STAGE = NTILES * TB;
-  static constexpr bool LDS_FRAG = NFRAG * FB + STAGE <= kLdsLimit;
   static constexpr size_t VECS = 2 * H * sizeof(float);  // b2 and the LayerNorm gain
   static constexpr size_t CARRY = NW * H * sizeof(float);  // per-wave open-row sums between blocks
-  static constexpr size_t LDS = STAGE + (LDS_FRAG ? NFRAG * FB : 0) + CARRY + VECS;
+  static constexpr size_t LDS = STAGE + 4 * FB + CARRY + VECS;
+  static_assert(LDS <= kLdsLimit, "weights and tiles in LDS");
 };
 
 // The rows one 16-edge block of the edge adjoint reads: e_k, P_i, Q_j,
@@ -376,34 +308,54 @@ struct EdgeBwdRows {
 // AM: the forward aggregated the MLP output, so the residual path carries
 // only the next layer's gradient (not Eq. 4b's).
 // ES: edge states and their gradients (e, g_e', g_e) stored as BF16.
-template <int H, bool BF, bool AM, int NWQ, bool ES>
-__global__ __launch_bounds__((64 * EdgeBwdCfg<H, BF, NWQ>::NW), (EdgeBwdCfg<H, BF, NWQ>::MINB)) void k_edge_bwd(EdgeBwdArgs a) {
-  using C = EdgeBwdCfg<H, BF, NWQ>;
-  constexpr int NF = H / 4, MB = H / 16, NW = C::NW, ROWS = C::ROWS, NT = dw_tiles_per_wave<H, H, NW>();
-  constexpr bool TP = C::TP;
+
+// A wave's tile in a group of NW consecutive tiles that the waves of a
+// workgroup walk in lock step, and the indices of its next 16-edge block.
+template <int NW>
+struct EdgeTile {
+  int64_t r0, r1, e0, e1, n_iter, e_last;
+  EdgeIdx ix;
+  // Tile bounds, clamped to the range end (a wave past it gets an empty
+  // tile); all loads are independent so they share one round trip.
+  __device__ __forceinline__ void open(const DevGraph& gr, const TileSched& ts, int64_t tg, int wave, int lane) {
+    const int64_t tile = tg + wave;
+    const int64_t tc0 = std::min<int64_t>(tile, ts.t1), tc1 = std::min<int64_t>(tile + 1, ts.t1);
+    r0 = gr.tile_r[tc0], r1 = gr.tile_r[tc1];
+    e0 = gr.tile_e[tc0], e1 = gr.tile_e[tc1];
+    // lock-step trip count: the most 16-edge blocks of any tile of the
+    // group; lane w < NW reads the bounds of tile tg + w
+    const int wl = lane < NW ? lane : 0;
+    const int32_t eb0 = gr.tile_e[std::min<int64_t>(tg + wl, ts.t1)];
+    const int32_t eb1 = gr.tile_e[std::min<int64_t>(tg + wl + 1, ts.t1)];
+    int nb = lane < NW ? (eb1 - eb0 + 15) / 16 : 0;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) nb = std::max(nb, __shfl_xor(nb, off));
+    n_iter = __builtin_amdgcn_readfirstlane(nb);  // the same in every lane and wave
+    e_last = e1 > e0 ? e1 - 1 : 0;                // in-bounds stand-in for absent edges
+    ix.fetch(gr, e0 + (lane & 15), e1, e_last);
+    ix.settle();
+  }
+};
+
+// BF16 products (k_edge_bwd_f32 is the FP32 form).
+template <int H, bool AM, int NWQ, bool ES>
+__global__ __launch_bounds__((64 * EdgeBwdCfg<H, NWQ>::NW), 1) void k_edge_bwd(EdgeBwdArgs a) {
+  using C = EdgeBwdCfg<H, NWQ>;
+  constexpr int NF = H / 4, NW = C::NW, ROWS = C::ROWS, NT = dw_tiles_per_wave<H, H, NW>();
   extern __shared__ uint4 smem[];
   char* tG2 = reinterpret_cast<char*>(smem);
   char* tA2 = tG2 + C::TB;
-  char* tG1 = TP ? tG2 : tA2 + C::TB;   // TP: the second round reuses the first round's tiles
-  char* tA1 = TP ? tA2 : tG1 + C::TB;
-  char* tGE = tA1 + C::TB;   // VEC: gE and gE * LN-normalised m, for dbeta / dgamma
+  char* tG1 = tA2 + C::TB;
+  char* tA1 = tG1 + C::TB;
+  char* tGE = tA1 + C::TB;   // gE and gE * LN-normalised m, for dbeta / dgamma
   char* tGM = tGE + C::TB;
-  const char* fr;
-  // TP's transposed products read W1c / W2 in the rotated layout
-  constexpr bool ROT = TP && C::LDS_FRAG;
-  if constexpr (C::LDS_FRAG) {
-    uint4* fl = smem + C::STAGE / 16;
-    if constexpr (ROT)
-      stage_frags_rot(fl, a.frag, C::NFRAG * C::FB);
-    else
-      stage_frags(fl, a.frag, C::NFRAG * C::FB);
-    fr = reinterpret_cast<const char*>(fl);
-  } else {
-    fr = reinterpret_cast<const char*>(a.frag);
-  }
+  uint4* fl = smem + C::STAGE / 16;
+  stage_wfrag<true, H, H>(fl, a.w1c.w);
+  stage_wfrag<true, H, H>(fl + C::FB / 16, a.w2.w);
+  stage_wfrag<true, H, H>(fl + 2 * C::FB / 16, WView{a.w2.w.p, a.w2.w.ld, 1});
+  stage_wfrag<true, H, H>(fl + 3 * C::FB / 16, WView{a.w1c.w.p, a.w1c.w.ld, 1});
+  const char* fr = reinterpret_cast<const char*>(fl);
   float* vecs = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + C::LDS - C::VECS);
-  // the open row's partial g_P sum, handed from lane 15 of one block to lane
-  // 0 of the next through LDS (same wave, so no barrier is needed)
   float* carry = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + C::LDS - C::VECS - C::CARRY) +
                  (threadIdx.x / 64) * H + (threadIdx.x / 16 % 4) * (H / 4);
   for (int t = threadIdx.x; t < 2 * H; t += blockDim.x) vecs[t] = t < H ? a.b2[t] : (a.ln ? a.lng[t - H] : 0.f);
@@ -415,77 +367,35 @@ __global__ __launch_bounds__((64 * EdgeBwdCfg<H, BF, NWQ>::NW), (EdgeBwdCfg<H, B
   v4f acc2[NT], acc1[NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n) acc2[n] = acc1[n] = v4f{0.f, 0.f, 0.f, 0.f};
-  constexpr int NV = (C::VEC || TP) ? 1 : NF;  // per-lane vector accumulators (FP32 path)
-  float db2[NV], dga[NV], dbe[NV];
-#pragma unroll
-  for (int i = 0; i < NV; ++i) db2[i] = dga[i] = dbe[i] = 0.f;
-  ColSum<H, NW> cs_b2, cs_ga, cs_be;  // BF16: MFMA column sums of the staged tiles
+  ColSum<H, NW> cs_b2, cs_ga, cs_be;  // MFMA column sums of the staged tiles
   cs_b2.zero();
   cs_ga.zero();
   cs_be.zero();
 
   // groups of NW consecutive tiles, one per wave, processed in lock step
+  EdgeTile<NW> tl;
   for (int64_t tg = ts.t0 + ts.rank * NW; tg < ts.t1; tg += ts.nr * NW) {
-    // Tile bounds, clamped to the range end (a wave past it gets an empty
-    // tile); all loads are independent so they share one round trip.
-    const int64_t tile = tg + wave;
-    const int64_t tc0 = std::min<int64_t>(tile, ts.t1), tc1 = std::min<int64_t>(tile + 1, ts.t1);
-    const int64_t r0 = gr.tile_r[tc0], r1 = gr.tile_r[tc1];
-    const int64_t e0 = gr.tile_e[tc0], e1 = gr.tile_e[tc1];
-    // lock-step trip count: the most 16-edge blocks of any tile of the
-    // group; lane w < NW reads the bounds of tile tg + w
-    const int wl = lane < NW ? lane : 0;
-    const int32_t eb0 = gr.tile_e[std::min<int64_t>(tg + wl, ts.t1)];
-    const int32_t eb1 = gr.tile_e[std::min<int64_t>(tg + wl + 1, ts.t1)];
-    int nb = lane < NW ? (eb1 - eb0 + 15) / 16 : 0;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) nb = std::max(nb, __shfl_xor(nb, off));
-    const int64_t n_iter = __builtin_amdgcn_readfirstlane(nb);  // the same in every lane and wave
+    tl.open(gr, ts, tg, wave, lane);
     int carry_key = 0;  // no open row at the start of a tile
-
-    // Index loads run one block ahead, so each block waits on a single
-    // round trip to memory (its rows), not on indices and then rows.
-    const int64_t e_last = e1 > e0 ? e1 - 1 : 0;  // in-bounds stand-in for absent edges
-    int ri_n, sj_n, md_n, nx_n;
-    {
-      const int64_t k = e0 + j, kk = k < e1 ? k : e_last;
-      ri_n = gr.recv[kk];
-      sj_n = gr.col[kk];
-      md_n = gr.mult[kk];
-      nx_n = (k + 1 < e1) ? gr.recv[k + 1] : -1;
-      // complete these loads here, so that the loop's entry state holds no
-      // pending loads (else the compiler's wait at the loop head, merged
-      // with the back edge, also drains the previous block's stores)
-      asm volatile("" : "+v"(ri_n), "+v"(sj_n), "+v"(md_n), "+v"(nx_n));
-    }
-
-    for (int64_t it = 0; it < n_iter; ++it) {
+    for (int64_t it = 0; it < tl.n_iter; ++it) {
       const char* frb = fr + opaque_zero();  // re-read the fragments each block
       const char* fW1c = frb;
       const char* fW2 = frb + C::FB;
       const char* fW2t = frb + 2 * C::FB;
       const char* fW1ct = frb + 3 * C::FB;
       const int srow = wave * 16 + j;
-      const int64_t k = e0 + it * 16 + j;
-      const bool valid = k < e1;
-      const int64_t kk = valid ? k : e_last;
-      const int ri = ri_n;
-      const int sj = sj_n;
-      const float inv_d = 1.f / (float)md_n;
-      const int next = nx_n;
-      const bool last = valid && next != ri;
+      const int64_t k = tl.e0 + it * 16 + j;
+      const bool valid = k < tl.e1;
+      const int64_t kk = valid ? k : tl.e_last;
+      const int ri = tl.ix.ri, sj = tl.ix.sj;
+      const float inv_d = 1.f / (float)tl.ix.md;
+      const bool last = valid && tl.ix.nx != ri;
       const int key = valid ? ri + 1 : -1;
 
       // next block's indices first (the only loads issued before this
       // block's stores that the next block waits on), then every row this
       // block reads, issued together
-      {
-        const int64_t k2 = k + 16, kk2 = k2 < e1 ? k2 : e_last;
-        ri_n = gr.recv[kk2];
-        sj_n = gr.col[kk2];
-        md_n = gr.mult[kk2];
-        nx_n = (k2 + 1 < e1) ? gr.recv[k2 + 1] : -1;
-      }
+      tl.ix.fetch(gr, k + 16, tl.e1, tl.e_last);
       EdgeBwdRows<H, ES> cur;
       cur.load(a, kk, ri, sj, g);
       float (&ev)[NF] = cur.ev;
@@ -498,13 +408,13 @@ __global__ __launch_bounds__((64 * EdgeBwdCfg<H, BF, NWQ>::NW), (EdgeBwdCfg<H, B
       // recompute the forward
 #pragma unroll
       for (int i = 0; i < NF; ++i) u[i] += t[i];
-      gemm<BF, MB, MB, ROT>(fW1c, ev, u, lane);
+      gemm_wf<true, H, H>(fW1c, ev, u, lane);
 #pragma unroll
       for (int i = 0; i < NF; ++i) u[i] = elu(u[i]);
       float mp[NF];
       const float* vb = vecs + opaque_zero();
       load_vec<H>(vb, g, mp);
-      gemm<BF, MB, MB, ROT>(fW2, u, mp, lane);
+      gemm_wf<true, H, H>(fW2, u, mp, lane);
 
       // gradient reaching e'
 #pragma unroll
@@ -521,28 +431,14 @@ __global__ __launch_bounds__((64 * EdgeBwdCfg<H, BF, NWQ>::NW), (EdgeBwdCfg<H, B
 #pragma unroll
         for (int i = 0; i < NF; ++i) {
           const float xh = (mp[i] - mean) * rstd;
-          if constexpr (!C::VEC && !TP) {
-            dga[i] += gE[i] * xh;
-            dbe[i] += gE[i];
-          } else {
-            t[i] = gE[i] * xh;
-          }
+          t[i] = gE[i] * xh;
           const float gx = gE[i] * gam[i];
           s1 += gx;
           s2 += gx * xh;
           mp[i] = xh;
         }
-        if constexpr (C::VEC) {
-          stage_row<H, BF, ROWS>(tGE, srow, g, gE);
-          stage_row<H, BF, ROWS>(tGM, srow, g, t);
-        }
-        if constexpr (TP) {  // dbeta += sum of gE, dgamma += sum of gE * x^ over the block's rows
-          float rs[1];
-          sum16_scatter<NF>(gE, rs, j);
-          dbe[0] += rs[0];
-          sum16_scatter<NF>(t, rs, j);
-          dga[0] += rs[0];
-        }
+        stage_row<H, true, ROWS>(tGE, srow, g, gE);
+        stage_row<H, true, ROWS>(tGM, srow, g, t);
         s1 = row_sum(s1) * (1.f / H);
         s2 = row_sum(s2) * (1.f / H);
         // rstd (gE gam - s1 - x^ s2) as two multiply-adds per feature
@@ -553,27 +449,16 @@ __global__ __launch_bounds__((64 * EdgeBwdCfg<H, BF, NWQ>::NW), (EdgeBwdCfg<H, B
 #pragma unroll
         for (int i = 0; i < NF; ++i) mp[i] = gE[i];
       }
-      if constexpr (TP) {
-        // db2: column sums of the staged gm tile after the first barrier
-      } else if constexpr (!C::VEC) {
-#pragma unroll
-        for (int i = 0; i < NF; ++i) db2[i] += mp[i];
-      }
-      stage_row<H, BF, ROWS>(tG2, srow, g, mp);
-      stage_row<H, BF, ROWS>(tA2, srow, g, u);
+      stage_row<H, true, ROWS>(tG2, srow, g, mp);
+      stage_row<H, true, ROWS>(tA2, srow, g, u);
       // gh = (W2^T gm) * ELU'(h); ELU'(h) = 1 for h > 0 else exp(h) = u + 1
 #pragma unroll
       for (int i = 0; i < NF; ++i) t[i] = 0.f;
-      if constexpr (TP)
-        gemm_f32_tr<H, ROT>(reinterpret_cast<const float*>(fW2), mp, t, lane);
-      else
-        gemm<BF, MB, MB>(fW2t, mp, t, lane);
+      gemm_wf<true, H, H>(fW2t, mp, t, lane);
 #pragma unroll
       for (int i = 0; i < NF; ++i) t[i] *= elu_deriv_from_value(u[i]);
-      if constexpr (!TP) {
-        stage_row<H, BF, ROWS>(tG1, srow, g, t);
-        stage_row<H, BF, ROWS>(tA1, srow, g, ev);
-      }
+      stage_row<H, true, ROWS>(tG1, srow, g, t);
+      stage_row<H, true, ROWS>(tA1, srow, g, ev);
       if constexpr (AM) {
         if (a.g_e_out) {
           load_row_t<H, ES>(a.g_e_out, kk, g, gE);
@@ -583,141 +468,262 @@ __global__ __launch_bounds__((64 * EdgeBwdCfg<H, BF, NWQ>::NW), (EdgeBwdCfg<H, B
         }
       }
       // g_e = gE + W1c^T gh
-      if constexpr (TP)
-        gemm_f32_tr<H, ROT>(reinterpret_cast<const float*>(fW1c), t, gE, lane);
-      else
-        gemm<BF, MB, MB>(fW1ct, t, gE, lane);
+      gemm_wf<true, H, H>(fW1ct, t, gE, lane);
       if (valid) {
         store_row_t<H, ES>(a.g_e_in, k, g, gE);
-        if constexpr (BF)
-          store_row_bf16<H>(reinterpret_cast<__bf16*>(a.g_h) + k * H, g, t);
-        else
-          store_row<H>(reinterpret_cast<float*>(a.g_h) + k * H, g, t);
+        store_row_bf16<H>(reinterpret_cast<__bf16*>(a.g_h) + k * H, g, t);
       }
-      if constexpr (TP) {
-        // round 1: dW2 and db2 from the staged (gm, u); then the same tiles
-        // take (gh, e).  db2: lane = feature (H = 64), wave w adds the staged
-        // rows 16w .. 16w+15 (four 16-byte LDS reads, conflict-free).
-        __syncthreads();
-        dw_tiles<H, H, BF, NW>(tG2, tA2, acc2, wave, lane);
-        {
-          const float* col = reinterpret_cast<const float*>(tG2) + lane * Stg<BF, ROWS>::RS + 16 * wave;
-          float s = 0.f;
-#pragma unroll
-          for (int r = 0; r < 16; r += 4) {
-            const float4 q = *reinterpret_cast<const float4*>(col + r);
-            s += ((q.x + q.y) + q.z) + q.w;
-          }
-          db2[0] += s;
-        }
-        __syncthreads();
-        stage_row<H, BF, ROWS>(tG1, srow, g, t);
-        stage_row<H, BF, ROWS>(tA1, srow, g, ev);
-      }
-      // g_P: segmented sum of gh per receiver.  Lanes past the tile's last
-      // edge hold gh = 0 (their gE is zeroed, so are gm and W2^T gm) and a
-      // key of their own, so they add nothing to any row's sum.
-      if (j == 0 && key == carry_key) {
-#pragma unroll
-        for (int i = 0; i < NF; i += 4) {
-          const float4 c = *reinterpret_cast<const float4*>(carry + i);
-          t[i] += c.x;
-          t[i + 1] += c.y;
-          t[i + 2] += c.z;
-          t[i + 3] += c.w;
-        }
-      }
-      seg_scan16<NF>(t, key);
-      if (last) store_row<H>(a.g_P + (int64_t)ri * H, g, t);
-      if (j == 15) {
-#pragma unroll
-        for (int i = 0; i < NF; i += 4) *reinterpret_cast<float4*>(carry + i) = make_float4(t[i], t[i + 1], t[i + 2], t[i + 3]);
-      }
-      carry_key = from_prev_lane_i(key);
+      edge_gp<H>(t, carry, carry_key, key, last, a.g_P + (int64_t)ri * H, j, g);
 
       __syncthreads();
-      if constexpr (!TP) dw_tiles<H, H, BF, NW>(tG2, tA2, acc2, wave, lane);
-      dw_tiles<H, H, BF, NW>(tG1, tA1, acc1, wave, lane);
-      if constexpr (C::VEC) {
-        cs_b2.add(tG2, wave, lane);
-        if (a.ln) {
-          cs_be.add(tGE, wave, lane);
-          cs_ga.add(tGM, wave, lane);
-        }
+      dw_tiles<H, H, true, NW>(tG2, tA2, acc2, wave, lane);
+      dw_tiles<H, H, true, NW>(tG1, tA1, acc1, wave, lane);
+      cs_b2.add(tG2, wave, lane);
+      if (a.ln) {
+        cs_be.add(tGE, wave, lane);
+        cs_ga.add(tGM, wave, lane);
       }
       __syncthreads();
     }
-    for (int64_t r = r0 + (lane >> 2); r < r1; r += 16) {
-      if (gr.rowptr[r] == gr.rowptr[r + 1]) {
-        float* dst = a.g_P + r * H;
-        for (int c = (lane & 3) * 4; c < H; c += 16) *reinterpret_cast<float4*>(dst + c) = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-    }
+    zero_empty_rows<H>(gr, tl.r0, tl.r1, a.g_P, lane);
   }
   float* slab = a.part + blockIdx.x * a.slab;
   dw_store<H, H, NW>(acc1, slab, H, wave, lane);
   dw_store<H, H, NW>(acc2, slab + H * H, H, wave, lane);
   float* scratch = reinterpret_cast<float*>(tG2);
-  if constexpr (C::VEC) {
-    cs_b2.store(scratch, slab + 2 * H * H, wave, lane);
-    cs_ga.store(scratch, slab + 2 * H * H + H, wave, lane);
-    cs_be.store(scratch, slab + 2 * H * H + 2 * H, wave, lane);
-  } else if constexpr (TP) {
-    // db2: lane l holds feature l (column sums of the staged gm); dgamma,
-    // dbeta: lane j of group g holds feature 16 (j / 4) + 4 g + j % 4 (H =
-    // 64: one value per lane after the reduce-scatter); waves added in order
-    __syncthreads();
-    scratch[(wave * 64 + lane) * 3 + 0] = db2[0];
-    scratch[(wave * 64 + lane) * 3 + 1] = dga[0];
-    scratch[(wave * 64 + lane) * 3 + 2] = dbe[0];
-    __syncthreads();
-    for (int t = threadIdx.x; t < 3 * H; t += blockDim.x) {
-      const int v = t / H, f = t % H;
-      const int l = v == 0 ? f : (4 * (f / 16) + f % 4) + 16 * ((f % 16) / 4);
-      float sum = 0.f;
-      for (int w = 0; w < NW; ++w) sum += scratch[(w * 64 + l) * 3 + v];
-      slab[2 * H * H + v * H + f] = sum;
-    }
-  } else {
-    block_sum_vec<H>(db2, scratch, slab + 2 * H * H, wave, lane);
-    block_sum_vec<H>(dga, scratch, slab + 2 * H * H + H, wave, lane);
-    block_sum_vec<H>(dbe, scratch, slab + 2 * H * H + 2 * H, wave, lane);
-  }
+  cs_b2.store(scratch, slab + 2 * H * H, wave, lane);
+  cs_ga.store(scratch, slab + 2 * H * H + H, wave, lane);
+  cs_be.store(scratch, slab + 2 * H * H + 2 * H, wave, lane);
 }
 
-template <int H, bool BF, bool AM, int NWQ, bool ES>
-static hipError_t launch_edge_bwd_es(const EdgeBwdArgs& a, int grid, hipStream_t s) {
-  using C = EdgeBwdCfg<H, BF, NWQ>;
-  (void)hipFuncSetAttribute((const void*)k_edge_bwd<H, BF, AM, NWQ, ES>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)C::LDS);
-  hipLaunchKernelGGL((k_edge_bwd<H, BF, AM, NWQ, ES>), dim3(grid), dim3(64 * C::NW), C::LDS, s, a);
+// FP32 products from BF16 parts (Op<false, W>).  Nothing saturates here (at
+// H = 64, per 16-edge block and SIMD: 4.7k cycles of matrix instructions, 5.9k
+// of vector instructions, 5k of LDS traffic, 4k of HBM traffic; with the FP32
+// matrix instructions 12.4k of matrix cycles alone), so what counts is that
+// they overlap.  Every wave is on its own: it accumulates the whole dW1c and
+// dW2 itself (DwWave, 128 registers at H = 64), walks its tiles independently
+// and loads the next block's first rows while it computes this one; at H = 64
+// that takes one wave per SIMD with up to 512 registers, at H = 32 there are
+// two.  W1c and W2 sit in LDS once, row major, for the plain and the
+// transposed products.  Per layer, against the FP32 matrix instructions: 3.5M
+// edges at H = 64 2.09 -> 1.62 ms, 0.67M at H = 32 167 -> 123 us; eight waves in
+// lock step, sharing the staged rows and the weight-gradient tiles: 1.71 ms
+// and 158 us.
+template <int H>
+struct EdgeBwdF32Cfg {
+  static constexpr int NW = 4;
+  static constexpr size_t WB = wrow_bytes(H, H, false);
+  using Dw = DwWave<H, H>;
+  static constexpr size_t WTILE = 2 * (Dw::TILE_G + Dw::TILE_A);  // (gm, u) and (gh, e) of one wave
+  static constexpr size_t VECS = 2 * H * sizeof(float);
+  static constexpr size_t CARRY = NW * H * sizeof(float);
+  static constexpr size_t LDS = NW * WTILE + 2 * WB + CARRY + VECS;
+  static_assert(LDS <= kLdsLimit && NW * WTILE >= NW * H * H * sizeof(float), "weights, tiles, final sums in LDS");
+};
+
+// The rows a block of the FP32 adjoint needs first: e_k, P_i, Q_j.
+template <int H>
+struct EdgeBwdHead {
+  static constexpr int NF = H / 4;
+  float ev[NF], u[NF], t[NF];
+  __device__ __forceinline__ void load(const EdgeBwdArgs& a, int64_t kk, int ri, int sj, int g) {
+    load_row<H>(reinterpret_cast<const float*>(a.e_in) + kk * H, g, ev);
+    load_row<H>(a.P + (int64_t)ri * H, g, u);
+    load_row<H>(a.Q + (int64_t)sj * H, g, t);
+  }
+  __device__ __forceinline__ void settle() {
+#pragma unroll
+    for (int i = 0; i < NF; ++i) asm volatile("" : "+v"(ev[i]), "+v"(u[i]), "+v"(t[i]));
+  }
+};
+
+template <int H, bool AM>
+__global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwdArgs a) {
+  using C = EdgeBwdF32Cfg<H>;
+  using Dw = typename C::Dw;
+  constexpr int NF = H / 4, NW = C::NW;
+  extern __shared__ uint4 smem[];
+  const int lane = lane_id(), j = lane & 15, g = lane >> 4, wave = threadIdx.x / 64;
+  char* tG2 = reinterpret_cast<char*>(smem) + wave * C::WTILE;
+  char* tA2 = tG2 + Dw::TILE_G;
+  char* tG1 = tA2 + Dw::TILE_A;
+  char* tA1 = tG1 + Dw::TILE_G;
+  char* wl = reinterpret_cast<char*>(smem) + NW * C::WTILE;
+  stage_wrow<false, H, H>(wl, a.w1c.w);
+  stage_wrow<false, H, H>(wl + C::WB, a.w2.w);
+  float* vecs = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + C::LDS - C::VECS);
+  float* carry = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + C::LDS - C::VECS - C::CARRY) + wave * H +
+                 g * (H / 4);
+  for (int t = threadIdx.x; t < 2 * H; t += blockDim.x) vecs[t] = t < H ? a.b2[t] : (a.ln ? a.lng[t - H] : 0.f);
+  __syncthreads();
+
+  const DevGraph& gr = a.g;
+  const TileSched ts = tile_sched(gr.n_tiles);
+  const uint32_t smask = dw_sign_mask();
+  Dw d2, d1;
+  d2.zero();
+  d1.zero();
+  float db2[NF], dga[NF], dbe[NF];
+#pragma unroll
+  for (int i = 0; i < NF; ++i) db2[i] = dga[i] = dbe[i] = 0.f;
+
+  for (int64_t tile = ts.t0 + ts.rank * NW + wave; tile < ts.t1; tile += ts.nr * NW) {
+    const int64_t r0 = gr.tile_r[tile], r1 = gr.tile_r[tile + 1];
+    const int64_t e0 = gr.tile_e[tile], e1 = gr.tile_e[tile + 1];
+    const int64_t e_last = e1 > e0 ? e1 - 1 : 0;  // in-bounds stand-in for absent edges
+    int carry_key = 0;  // no open row at the start of a tile
+    // indices run two blocks ahead, rows one; the first block's are complete
+    // before the loop, the next block's before this block's stores, so that
+    // no wait drains a store
+    EdgeIdx ic, in;
+    EdgeBwdHead<H> nx;
+    ic.fetch(gr, e0 + j, e1, e_last);
+    in.fetch(gr, e0 + 16 + j, e1, e_last);
+    ic.settle();
+    nx.load(a, e0 + j < e1 ? e0 + j : e_last, ic.ri, ic.sj, g);
+    in.settle();
+    nx.settle();
+    for (int64_t base = e0; base < e1; base += 16) {
+      // re-read the weights each block, and form the lane's LDS offsets anew
+      const int ln = lane + opaque_zero();
+      const char* w1c = wl + opaque_zero();
+      const char* w2 = w1c + C::WB;
+      const int64_t k = base + j;
+      const bool valid = k < e1;
+      const int64_t kk = valid ? k : e_last;
+      const int ri = ic.ri;
+      const float inv_d = 1.f / (float)ic.md;
+      const bool last = valid && ic.nx != ri;
+      const int key = valid ? ri + 1 : -1;
+      EdgeBwdHead<H> cur = nx;
+      float gE[NF], go[NF];  // needed two products later: not loaded ahead
+      load_row<H>(a.g_a + (int64_t)ri * H, g, gE);
+      if (a.g_e_out) {
+        load_row<H>(reinterpret_cast<const float*>(a.g_e_out) + kk * H, g, go);
+      } else {
+#pragma unroll
+        for (int i = 0; i < NF; ++i) go[i] = 0.f;
+      }
+      nx.load(a, k + 16 < e1 ? k + 16 : e_last, in.ri, in.sj, g);
+      ic = in;
+      in.fetch(gr, k + 32, e1, e_last);
+      float (&u)[NF] = cur.u;
+      float (&t)[NF] = cur.t;
+      __builtin_amdgcn_sched_barrier(0);  // all row loads issue first
+
+      // recompute the forward
+#pragma unroll
+      for (int i = 0; i < NF; ++i) u[i] += t[i];
+      Op<false, H> o;
+      make_op(cur.ev, o);
+      stage_op<H>(tA1, Dw::AP, ln & 15, ln >> 4, o);
+      gemm_wn<false, H, H>(w1c, o, u, ln);
+#pragma unroll
+      for (int i = 0; i < NF; ++i) u[i] = elu(u[i]);
+      float mp[NF];
+      const float* vb = vecs + opaque_zero();
+      load_vec<H>(vb, g, mp);
+      make_op(u, o);
+      stage_op<H>(tA2, Dw::AP, ln & 15, ln >> 4, o);
+      gemm_wn<false, H, H>(w2, o, mp, ln);
+
+      // gradient reaching e', LayerNorm adjoint (mp becomes gm)
+#pragma unroll
+      for (int i = 0; i < NF; ++i) {
+        const float v = gE[i] * inv_d + go[i];
+        gE[i] = valid ? v : 0.f;
+      }
+      if (a.ln) {
+        float mean, rstd, gam[NF];
+        ln_stats<H>(mp, a.eps, mean, rstd);
+        load_vec<H>(vb + H, g, gam);
+        float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+        for (int i = 0; i < NF; ++i) {
+          const float xh = (mp[i] - mean) * rstd;
+          dga[i] += gE[i] * xh;
+          dbe[i] += gE[i];
+          const float gx = gE[i] * gam[i];
+          s1 += gx;
+          s2 += gx * xh;
+          mp[i] = xh;
+        }
+        s1 = row_sum(s1) * (1.f / H);
+        s2 = row_sum(s2) * (1.f / H);
+        const float c1 = -rstd * s1, c2 = -rstd * s2;
+#pragma unroll
+        for (int i = 0; i < NF; ++i) mp[i] = fmaf(mp[i], c2, fmaf(gE[i] * gam[i], rstd, c1));
+      } else {
+#pragma unroll
+        for (int i = 0; i < NF; ++i) mp[i] = gE[i];
+      }
+#pragma unroll
+      for (int i = 0; i < NF; ++i) db2[i] += mp[i];
+      // gh = (W2^T gm) * ELU'(h); dW2 += gm u^T
+      make_op(mp, o);
+      gemm_wt<false, H, H, ACC_SET>(w2, o, t, ln);
+      flip_op(o, smask);
+      stage_op<H>(tG2, Dw::GP, ln & 15, ln >> 4, o);
+      wave_lds_fence();
+      d2.add(tG2, tA2, ln);
+#pragma unroll
+      for (int i = 0; i < NF; ++i) t[i] *= elu_deriv_from_value(u[i]);
+      if constexpr (AM) {  // the residual carries the next layer's gradient only
+#pragma unroll
+        for (int i = 0; i < NF; ++i) gE[i] = valid ? go[i] : 0.f;
+      }
+      // g_e = gE + W1c^T gh; dW1c += gh e^T
+      make_op(t, o);
+      gemm_wt<false, H, H, ACC_ADD>(w1c, o, gE, ln);
+      flip_op(o, smask);
+      stage_op<H>(tG1, Dw::GP, ln & 15, ln >> 4, o);
+      wave_lds_fence();
+      d1.add(tG1, tA1, ln);
+      nx.settle();
+      in.settle();
+      if (valid) {
+        store_row<H>(reinterpret_cast<float*>(a.g_e_in) + k * H, g, gE);
+        store_row<H>(reinterpret_cast<float*>(a.g_h) + k * H, g, t);
+      }
+      edge_gp<H>(t, carry, carry_key, key, last, a.g_P + (int64_t)ri * H, j, g);
+    }
+    zero_empty_rows<H>(gr, r0, r1, a.g_P, lane);
+  }
+  float* slab = a.part + blockIdx.x * a.slab;
+  float* scratch = reinterpret_cast<float*>(smem);
+  d1.template store<NW>(scratch, slab, dw_sign(), wave, lane);
+  d2.template store<NW>(scratch, slab + H * H, dw_sign(), wave, lane);
+  block_sum_vec<H, NW>(db2, scratch, slab + 2 * H * H, wave, lane);
+  block_sum_vec<H, NW>(dga, scratch, slab + 2 * H * H + H, wave, lane);
+  block_sum_vec<H, NW>(dbe, scratch, slab + 2 * H * H + 2 * H, wave, lane);
+}
+
+template <int H, bool AM, int NWQ>
+static hipError_t launch_edge_bwd_bf(const EdgeBwdArgs& a, int grid, hipStream_t s) {
+  using C = EdgeBwdCfg<H, NWQ>;
+  auto kern = a.es ? k_edge_bwd<H, AM, NWQ, true> : k_edge_bwd<H, AM, NWQ, false>;
+  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * C::NW), C::LDS, s, a);
   return hipGetLastError();
 }
-template <int H, bool BF, bool AM, int NWQ>
-static hipError_t launch_edge_bwd_am(const EdgeBwdArgs& a, int grid, hipStream_t s) {
-  if constexpr (BF) {
-    if (a.es) return launch_edge_bwd_es<H, BF, AM, NWQ, true>(a, grid, s);
+template <int H>
+static hipError_t launch_edge_bwd_h(const EdgeBwdArgs& a, int grid, hipStream_t s) {
+  if (a.bf) {
+    if (a.waves == 4) return a.am ? launch_edge_bwd_bf<H, true, 4>(a, grid, s) : launch_edge_bwd_bf<H, false, 4>(a, grid, s);
+    return a.am ? launch_edge_bwd_bf<H, true, 8>(a, grid, s) : launch_edge_bwd_bf<H, false, 8>(a, grid, s);
   }
-  return launch_edge_bwd_es<H, BF, AM, NWQ, false>(a, grid, s);
-}
-// Waves per workgroup: the default, or 4 (any width and type), or 8 (the
-// BF16 kernel at H <= 64, whose default it is); the C ABI validates it.
-template <int H, bool BF>
-static hipError_t launch_edge_bwd_t(const EdgeBwdArgs& a, int grid, hipStream_t s) {
-  if constexpr (BF && H <= 64) {
-    if (a.waves == 4)
-      return a.am ? launch_edge_bwd_am<H, BF, true, 4>(a, grid, s) : launch_edge_bwd_am<H, BF, false, 4>(a, grid, s);
-  }
-  return a.am ? launch_edge_bwd_am<H, BF, true, 0>(a, grid, s) : launch_edge_bwd_am<H, BF, false, 0>(a, grid, s);
+  using C = EdgeBwdF32Cfg<H>;
+  auto kern = a.am ? k_edge_bwd_f32<H, true> : k_edge_bwd_f32<H, false>;
+  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * C::NW), C::LDS, s, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_edge_bwd(const EdgeBwdArgs& a, int grid, hipStream_t s) {
   if (a.es && !a.bf) return hipErrorInvalidValue;
-#define MP_CASE(HH) \
-  if (a.H == HH) return a.bf ? launch_edge_bwd_t<HH, true>(a, grid, s) : launch_edge_bwd_t<HH, false>(a, grid, s);
-  MP_CASE(32) MP_CASE(64)  // wider layers: launch_edge_bwd_split
-#undef MP_CASE
-  return hipErrorInvalidValue;
+  if (a.H == 32) return launch_edge_bwd_h<32>(a, grid, s);
+  if (a.H == 64) return launch_edge_bwd_h<64>(a, grid, s);
+  return hipErrorInvalidValue;  // wider layers: launch_edge_bwd_split
 }
 
 // ------------------------------------------- split edge adjoint (wide H)
@@ -767,13 +773,17 @@ __global__ __launch_bounds__((64 * EdgeBwdSplitCfg<H, BF, NWQ>::NW)) void k_edge
   extern __shared__ uint4 smem[];
   const char* fr;
   if constexpr (C::LDS_FRAG) {
-    if constexpr (ROT)
-      stage_frags_rot(smem, a.frag, C::NFR * C::FB);
-    else
-      stage_frags(smem, a.frag, C::NFR * C::FB);
+    if constexpr (ROT) {
+      stage_frags_rot(smem, a.w1c.frag, C::NFR * C::FB);
+    } else {
+      stage_wfrag<BF, H, H>(smem, a.w1c.w);
+      stage_wfrag<BF, H, H>(smem + C::FB / 16, a.w2.w);
+      stage_wfrag<BF, H, H>(smem + 2 * C::FB / 16, WView{a.w2.w.p, a.w2.w.ld, 1});
+      stage_wfrag<BF, H, H>(smem + 3 * C::FB / 16, WView{a.w1c.w.p, a.w1c.w.ld, 1});
+    }
     fr = reinterpret_cast<const char*>(smem);
   } else {
-    fr = reinterpret_cast<const char*>(a.frag);
+    fr = reinterpret_cast<const char*>(a.w1c.frag);
   }
   float* vecs = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + C::LDS - C::VECS);
   float* carry = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + C::LDS - C::VECS - C::CARRY) +

@@ -133,8 +133,23 @@ DevGraph dev_graph(const mp_dev_graph* g) {
   return d;
 }
 
-int64_t n_tiles_for(int64_t E, int tile_edges) {
-  const int64_t te = tile_edges > 0 ? tile_edges : kTileEdges;
+// Edges per tile when the caller does not say: kTileEdges, and in FP32 fewer
+// (whole 16-edge blocks) where that leaves fewer tiles than the chip holds
+// waves of the kernel: 4096 of the forward, 1024 (H = 64) or 2048 of the
+// adjoint.  A wave walks its tile's blocks one after
+// the other, so a small graph's time is the longest such chain; a row-aligned
+// tile also fills its last block only partly, so below that size nothing is
+// gained (an adjoint of 0.5M edges in tiles of 32: 1.4 times slower than in
+// tiles of 128).  BF16 products keep kTileEdges at every size: the tiles group
+// the sums that are rounded to BF16 next.
+int default_tile_edges(int64_t E, int H, bool bf, bool bwd) {
+  if (bf) return kTileEdges;
+  const int64_t waves = !bwd ? 4096 : H == 64 ? 1024 : 2048;
+  const int64_t te = (E / waves + 15) / 16 * 16;
+  return (int)std::max<int64_t>(16, std::min<int64_t>(kTileEdges, te));
+}
+int64_t n_tiles_for(int64_t E, int tile_edges, int H, bool bf, bool bwd) {
+  const int64_t te = tile_edges > 0 ? tile_edges : default_tile_edges(E, H, bf, bwd);
   return std::max<int64_t>(1, (E + te - 1) / te);
 }
 
@@ -162,9 +177,18 @@ int check_cfg(const mp_layer_cfg* c) {
   return MP_OK;
 }
 
-// Grid sizes: persistent edge kernels give every wave at least ~64 edges.
-int edge_grid(int64_t E) { return (int)std::max<int64_t>(1, std::min<int64_t>(1024, E / 256)); }
+// Grid sizes of the persistent edge kernels: twice a wave per tile (each XCD's
+// share of the waves then covers its share of the tiles in one round whatever
+// the remainders) until the chip is full: the FP32 forward at H = 64 holds
+// three workgroups per CU, 50 KB of LDS each, the others four.
+int edge_grid(int64_t tiles, bool three) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(three ? 768 : 1024, (tiles + 1) / 2));
+}
 int edge_bwd_grid(int64_t E) { return (int)std::max<int64_t>(1, std::min<int64_t>(512, E / 256)); }
+// FP32 adjoint, H <= 64: workgroups of four waves, one (H = 64) or two per CU
+int edge_bwd_f32_grid(int64_t tiles, int H) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(H == 64 ? 256 : 512, (tiles + 3) / 4));
+}
 int row_grid(int64_t N) { return (int)std::max<int64_t>(1, std::min<int64_t>(1024, (N + 63) / 64)); }
 int row_bwd_grid(int64_t N) { return (int)std::max<int64_t>(1, std::min<int64_t>(512, (N + 255) / 256)); }
 
@@ -193,11 +217,13 @@ struct LayerWs {
   int64_t n_tiles;
   LayerWs(const mp_layer_cfg* c, const mp_dev_graph* g, bool bwd) : fr(c->H, c->gemm_dtype == MP_BF16) {
     const size_t H = c->H, N = g->n_rows, E = g->n_edges;
-    ge = c->edge_grid > 0 ? c->edge_grid : edge_grid(E);
-    gbe = c->edge_bwd_grid > 0 ? c->edge_bwd_grid : edge_bwd_grid(E);
+    n_tiles = n_tiles_for(E, c->tile_edges, c->H, c->gemm_dtype == MP_BF16, bwd);
+    ge = c->edge_grid > 0 ? c->edge_grid : edge_grid(n_tiles, c->gemm_dtype != MP_BF16 && H == 64);
+    gbe = c->edge_bwd_grid > 0                         ? c->edge_bwd_grid
+          : c->gemm_dtype != MP_BF16 && !edge_bwd_split(H) ? edge_bwd_f32_grid(n_tiles, H)
+                                                           : edge_bwd_grid(E);
     gn = row_grid(N);
     gbn = row_bwd_grid(N);
-    n_tiles = n_tiles_for(E, c->tile_edges);
     size_t o = fr.total;
     tile_r = o; o = align_up(o + (size_t)(n_tiles + 1) * 4);
     tile_e = o; o = align_up(o + (size_t)(n_tiles + 1) * 4);
@@ -284,8 +310,24 @@ int check_layer_params(const mp_layer_cfg* c, const mp_layer_params* p) {
   return MP_OK;
 }
 
+TileJob tile_job(const DevGraph& d) {
+  return TileJob{d.rowptr, d.n_rows, d.n_tiles, const_cast<int32_t*>(d.tile_r), const_cast<int32_t*>(d.tile_e), d.queue};
+}
+
 char* ws_at(void* ws, size_t off) { return reinterpret_cast<char*>(ws) + off; }
 float* wsf(void* ws, size_t off) { return reinterpret_cast<float*>(ws_at(ws, off)); }
+
+// The edge MLP's matrices: the FP32 views and, where packed, their fragments.
+struct LayerWeights {
+  WSrc w1a, w1b, w1c, w2;
+  LayerWeights(const mp_layer_cfg* c, const mp_layer_params* p, void* ws, const LayerWs& W) {
+    const int H = c->H;
+    w1a = WSrc{WView{p->We1, 3 * H, 0}, ws_at(ws, W.fr.proj)};
+    w1b = WSrc{WView{p->We1 + H, 3 * H, 0}, ws_at(ws, W.fr.proj + W.fr.f1)};
+    w1c = WSrc{WView{p->We1 + 2 * H, 3 * H, 0}, ws_at(ws, W.fr.edge)};
+    w2 = WSrc{WView{p->We2, H, 0}, ws_at(ws, W.fr.edge + W.fr.f1)};
+  }
+};
 
 }  // namespace
 
@@ -421,17 +463,18 @@ int layer_forward_launch(const mp_layer_cfg* cfg, const mp_layer_params* p, cons
   float* P = pq_out ? pq_out : wsf(ws, W.P);
   float* Q = pq_out ? pq_out + (size_t)g->n_rows * cfg->H : wsf(ws, W.Q);
   float* a = a_star_out ? a_star_out : wsf(ws, W.a);
-  if ((rc = run("tiles", s, [&] {
-         return launch_tiles(d, reinterpret_cast<int32_t*>(ws_at(ws, W.tile_r)),
-                             reinterpret_cast<int32_t*>(ws_at(ws, W.tile_e)), d.queue, s);
+  if (!raw_weights(H, bf) &&
+      (rc = run("pack", s, [&] { return launch_pack(layer_jobs(cfg, p, W.fr, false), ws, s); })))
+    return rc;
+  const LayerWeights LW(cfg, p, ws, W);
+  if ((rc = run("proj", s, [&] {
+         return launch_proj(H, bf, g->n_rows, x_in, LW.w1a, LW.w1b, p->be1, P, Q, W.gn, tile_job(d), s);
        })))
     return rc;
-  if ((rc = run("pack", s, [&] { return launch_pack(layer_jobs(cfg, p, W.fr, false), ws, s); }))) return rc;
-  if ((rc = run("proj", s, [&] { return launch_proj(H, bf, d, x_in, ws_at(ws, W.fr.proj), p->be1, P, Q, W.gn, s); }))) return rc;
   const bool es = cfg->estate_dtype == MP_BF16;
   if ((rc = run("edge_fwd", s, [&] {
          return launch_edge_fwd(H, cfg->layernorm != 0, bf, cfg->aggregate != 0, cfg->edge_fwd_queue != 0, es, d, P,
-                                Q, e_in, ws_at(ws, W.fr.edge), p->be2, p->ge, p->bge, cfg->ln_eps, e_out, a, W.ge, s);
+                                Q, e_in, LW.w1c, LW.w2, p->be2, p->ge, p->bge, cfg->ln_eps, e_out, a, W.ge, s);
        })))
     return rc;
   if (cfg->halo && (rc = run("halo", s, [&] { return launch_halo(H, d, a, s); }))) return rc;
@@ -451,6 +494,8 @@ int layer_forward_launch(const mp_layer_cfg* cfg, const mp_layer_params* p, cons
   m.lng = p->gn;
   m.lnb = p->bgn;
   m.eps = cfg->ln_eps;
+  m.W0 = p->Wn1;
+  m.W1 = p->Wn2;
   m.frag0 = ws_at(ws, W.fr.node);
   m.frag1 = ws_at(ws, W.fr.node + W.fr.f2);
   m.out = x_out;
@@ -574,18 +619,18 @@ extern "C" int mp_layer_backward(const mp_layer_cfg* cfg, const mp_layer_params*
   const float* P = pq ? pq : wsf(ws, W.P);
   const float* Q = pq ? pq + (size_t)g->n_rows * H : wsf(ws, W.Q);
   float* ga = wsf(ws, W.a);
-  if ((rc = run("tiles", s, [&] {
-         return launch_tiles(d, reinterpret_cast<int32_t*>(ws_at(ws, W.tile_r)),
-                             reinterpret_cast<int32_t*>(ws_at(ws, W.tile_e)), d.queue, s);
-       })))
-    return rc;
   float* gP = wsf(ws, W.gP);
   void* gh = ws_at(ws, W.gh);
   if ((rc = run("pack", s, [&] { return launch_pack(layer_jobs(cfg, p, W.fr, true), ws, s); }))) return rc;
-  if (!pq && (rc = run("proj", s, [&] {
-                return launch_proj(H, bf, d, x_in, ws_at(ws, W.fr.proj), p->be1, wsf(ws, W.P), wsf(ws, W.Q), W.gn, s);
-              })))
+  const LayerWeights LW(cfg, p, ws, W);
+  if (pq) {
+    if ((rc = run("tiles", s, [&] { return launch_tiles(tile_job(d), s); }))) return rc;
+  } else if ((rc = run("proj", s, [&] {
+                return launch_proj(H, bf, g->n_rows, x_in, LW.w1a, LW.w1b, p->be1, wsf(ws, W.P), wsf(ws, W.Q), W.gn,
+                                   tile_job(d), s);
+              }))) {
     return rc;
+  }
   // node MLP adjoint: g_a* and g_x (residual + node-MLP part)
   MlpBwdArgs m{};
   m.n_rows = g->n_rows;
@@ -668,7 +713,8 @@ extern "C" int mp_layer_backward(const mp_layer_cfg* cfg, const mp_layer_params*
   eb.e_in = e_in;
   eb.g_e_out = g_e_out;
   eb.g_a = ga;
-  eb.frag = ws_at(ws, W.fr.edge);
+  eb.w1c = LW.w1c;
+  eb.w2 = LW.w2;
   eb.b2 = p->be2;
   eb.lng = p->ge;
   eb.lnb = p->bge;
@@ -852,7 +898,9 @@ extern "C" int mp_mlp_forward(const mp_mlp_cfg* cfg, const mp_mlp_params* p, int
   const MlpWs W(cfg, n_rows, false);
   if (ws_bytes < W.total) return mp_fail(MP_ENOMEM, "mp_mlp_forward: workspace %zu < %zu bytes", ws_bytes, W.total);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if ((rc = run("pack", s, [&] { return launch_pack(mlp_jobs(cfg, p, W, false), ws, s); }))) return rc;
+  if (!raw_weights(cfg->H, cfg->gemm_dtype == MP_BF16) &&
+      (rc = run("pack", s, [&] { return launch_pack(mlp_jobs(cfg, p, W, false), ws, s); })))
+    return rc;
   MlpFwdArgs m{};
   m.n_rows = n_rows;
   m.src0 = in;

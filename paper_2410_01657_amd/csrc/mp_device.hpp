@@ -27,6 +27,7 @@ namespace mp {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
@@ -59,7 +60,7 @@ __device__ __forceinline__ void store_row(float* __restrict__ ptr, int g, const 
 }
 
 // BF16 storage of a row (round to nearest even) and its FP32 read-back.
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
 typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 template <int W>
@@ -234,6 +235,227 @@ __device__ __forceinline__ void gemm_bf16(const uint4* __restrict__ frag, const 
   }
 }
 
+// ------------------------------- FP32 products on the BF16 matrix unit
+//
+// An FP32 value is the exact sum of three BF16 parts, x = h + m + l: h its
+// upper half, m the rounded remainder, l what then is left (8 + 8 + 8 bits).
+// Six of the nine part products give W x: the dropped m*l, l*m and l*l are
+// below 2^-22 of |w||x| and symmetric, and the products summed are exact in
+// FP32.  The five small ones are summed apart and added once, so the large
+// sum takes K/32 roundings instead of the FP32 instruction's K/4: against FP64 (K = 64, normal values) the rms error is 4.6e-8 of the result,
+// 1.4e-7 with v_mfma_f32_16x16x4f32.  The rate: six v_mfma_f32_16x16x32_bf16
+// take 96 cycles for what eight 32-cycle FP32 instructions do, and unlike
+// those they issue beside vector instructions.  Infinite inputs give NaN
+// (their remainder is inf - inf), as a NaN input does.
+//
+// Op<BF, W>: a W-wide row in the row-block layout as matrix operand; lane
+// value q of chunk t is in[8t + q].
+template <bool BF, int W>
+struct Op;
+template <int W>
+struct Op<true, W> {
+  v8bf h[W / 32];
+};
+template <int W>
+struct Op<false, W> {
+  v8bf h[W / 32], m[W / 32], l[W / 32];
+};
+
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void split3_pair(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l) {
+  const uint32_t b0 = __builtin_bit_cast(uint32_t, x0), b1 = __builtin_bit_cast(uint32_t, x1);
+  h = __builtin_amdgcn_perm(b1, b0, 0x07060302);  // upper halves
+  float r0 = x0 - __builtin_bit_cast(float, b0 & 0xffff0000u);
+  float r1 = x1 - __builtin_bit_cast(float, b1 & 0xffff0000u);
+  m = __builtin_bit_cast(uint32_t, v2bf{(__bf16)r0, (__bf16)r1});
+  r0 -= __builtin_bit_cast(float, m << 16);
+  r1 -= __builtin_bit_cast(float, m & 0xffff0000u);
+  l = __builtin_bit_cast(uint32_t, v2bf{(__bf16)r0, (__bf16)r1});
+}
+__device__ __forceinline__ void split3_8(const float* x, v8bf& h, v8bf& m, v8bf& l) {
+  v4u hh, mm, ll;
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    uint32_t a, b, c;
+    split3_pair(x[2 * p], x[2 * p + 1], a, b, c);
+    hh[p] = a;
+    mm[p] = b;
+    ll[p] = c;
+  }
+  h = __builtin_bit_cast(v8bf, hh);
+  m = __builtin_bit_cast(v8bf, mm);
+  l = __builtin_bit_cast(v8bf, ll);
+}
+
+template <int W>
+__device__ __forceinline__ void make_op(const float (&x)[W / 4], Op<true, W>& o) {
+#pragma unroll
+  for (int t = 0; t < W / 32; ++t) o.h[t] = to_bf8(&x[8 * t]);
+}
+template <int W>
+__device__ __forceinline__ void make_op(const float (&x)[W / 4], Op<false, W>& o) {
+#pragma unroll
+  for (int t = 0; t < W / 32; ++t) split3_8(&x[8 * t], o.h[t], o.m[t], o.l[t]);
+}
+
+#define MP_MFMA_BF16(A, B, C) __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B, C, 0, 0, 0)
+
+// acc += W in over K/32 chunks, W's operand of (chunk t, output block mb) from
+// wf(t, mb, part) with part 0, 1, 2 = h, m, l (BF16: part 0 only).
+// How a product meets its accumulator: it starts from it (the large part
+// products are summed onto it), starts from zero and replaces it, or starts
+// from zero and is added at the end (one rounding; eight more registers).
+enum Acc { ACC_START, ACC_SET, ACC_ADD };
+
+template <int MB, int T, Acc MODE, class F>
+__device__ __forceinline__ void gemm_op(F&& wf, const Op<true, 32 * T>& in, float (&acc)[4 * MB]) {
+  v4f c[MB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+    c[mb] = MODE == ACC_SET ? v4f{0.f, 0.f, 0.f, 0.f}
+                            : v4f{acc[4 * mb], acc[4 * mb + 1], acc[4 * mb + 2], acc[4 * mb + 3]};
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) c[mb] = MP_MFMA_BF16(wf(t, mb, 0), in.h[t], c[mb]);
+  }
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[4 * mb + r] = c[mb][r];
+  }
+}
+template <int MB, int T, Acc MODE, class F>
+__device__ __forceinline__ void gemm_op(F&& wf, const Op<false, 32 * T>& in, float (&acc)[4 * MB]) {
+  // two output blocks at a time: each weight part is read once, and no two
+  // consecutive matrix instructions add to the same registers
+  constexpr int G = MB % 2 == 0 ? 2 : 1;
+#pragma unroll
+  for (int m0 = 0; m0 < MB; m0 += G) {
+    v4f ch[G], cs[G];
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      const int mb = m0 + i;
+      cs[i] = v4f{0.f, 0.f, 0.f, 0.f};
+      ch[i] = MODE == ACC_START ? v4f{acc[4 * mb], acc[4 * mb + 1], acc[4 * mb + 2], acc[4 * mb + 3]} : cs[i];
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      v8bf wh[G], wm[G], wl[G];
+#pragma unroll
+      for (int i = 0; i < G; ++i) {
+        wl[i] = wf(t, m0 + i, 2);
+        wm[i] = wf(t, m0 + i, 1);
+        wh[i] = wf(t, m0 + i, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < G; ++i) cs[i] = MP_MFMA_BF16(wl[i], in.h[t], cs[i]);
+#pragma unroll
+      for (int i = 0; i < G; ++i) cs[i] = MP_MFMA_BF16(wm[i], in.m[t], cs[i]);
+#pragma unroll
+      for (int i = 0; i < G; ++i) cs[i] = MP_MFMA_BF16(wh[i], in.l[t], cs[i]);
+#pragma unroll
+      for (int i = 0; i < G; ++i) cs[i] = MP_MFMA_BF16(wm[i], in.h[t], cs[i]);
+#pragma unroll
+      for (int i = 0; i < G; ++i) ch[i] = MP_MFMA_BF16(wh[i], in.h[t], ch[i]);
+#pragma unroll
+      for (int i = 0; i < G; ++i) cs[i] = MP_MFMA_BF16(wh[i], in.m[t], cs[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        acc[4 * (m0 + i) + r] =
+            MODE == ACC_ADD ? acc[4 * (m0 + i) + r] + (ch[i][r] + cs[i][r]) : ch[i][r] + cs[i][r];
+    }
+  }
+}
+
+// A weight matrix in device memory: element (r, c) at p[r*ld + c], or with
+// trans at p[c*ld + r].
+struct WView {
+  const float* p;
+  int ld, trans;
+};
+
+// Weights in LDS as MFMA fragments: BF16 products one BF16 matrix, FP32
+// products its three parts one after the other.  Staged by the kernel itself
+// from the FP32 matrix (a few KB per workgroup of a persistent grid, so no
+// packing launch is needed before it).  A weight whose upper part would round
+// to infinity keeps its upper half instead.
+__host__ __device__ constexpr size_t w_bytes(int M, int K, bool bf) { return size_t(M) * K * 2 * (bf ? 1 : 3); }
+
+template <bool BF>
+__device__ __forceinline__ void split_w8(const float* x, v8bf& h, v8bf& m, v8bf& l) {
+  if constexpr (BF) {
+    h = to_bf8(x);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const uint32_t b = __builtin_bit_cast(uint32_t, x[q]);
+      __bf16 hq = (__bf16)x[q];
+      if ((b & 0x7fffffffu) >= 0x7f7f8000u)
+        hq = __builtin_bit_cast(__bf16, (uint16_t)(b >> 16));
+      const float r = x[q] - (float)hq;
+      const __bf16 mq = (__bf16)r;
+      h[q] = hq;
+      m[q] = mq;
+      l[q] = (__bf16)(r - (float)mq);
+    }
+  }
+}
+
+// Stage the M x K matrix w as fragments: 16-byte piece (mb*(K/32) + t)*64 +
+// lane holds A[16 mb + lane%16][32t + 16(q/4) + 4(lane/16) + q%4], q = 0..7;
+// the parts M*K*2 bytes apart.  All threads of the workgroup; no barrier.
+template <bool BF, int M, int K>
+__device__ __forceinline__ void stage_wfrag(void* __restrict__ dst, const WView& w) {
+  constexpr int T = K / 32;
+  uint4* d = reinterpret_cast<uint4*>(dst);
+  for (int e = threadIdx.x; e < M * K / 8; e += blockDim.x) {
+    const int lane = e % 64, t = (e / 64) % T, mb = e / (64 * T);
+    const int row = 16 * mb + lane % 16, col = 32 * t + 4 * (lane / 16);
+    float x[8];
+    if (!w.trans) {
+      const float4 a = *reinterpret_cast<const float4*>(w.p + (int64_t)row * w.ld + col);
+      const float4 b = *reinterpret_cast<const float4*>(w.p + (int64_t)row * w.ld + col + 16);
+      x[0] = a.x, x[1] = a.y, x[2] = a.z, x[3] = a.w;
+      x[4] = b.x, x[5] = b.y, x[6] = b.z, x[7] = b.w;
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = w.p[(int64_t)(col + 16 * (q / 4) + q % 4) * w.ld + row];
+    }
+    v8bf h, m, l;
+    split_w8<BF>(x, h, m, l);
+    d[e] = __builtin_bit_cast(uint4, h);
+    if constexpr (!BF) {
+      d[e + M * K / 8] = __builtin_bit_cast(uint4, m);
+      d[e + 2 * (M * K / 8)] = __builtin_bit_cast(uint4, l);
+    }
+  }
+}
+
+// acc += W in, W staged by stage_wfrag.
+template <bool BF, int M, int K>
+__device__ __forceinline__ void gemm_wf(const void* __restrict__ w, const Op<BF, K>& in, float (&acc)[M / 4],
+                                        int lane) {
+  const uint4* f = reinterpret_cast<const uint4*>(w) + lane;
+  constexpr int T = K / 32;
+  gemm_op<M / 16, T, ACC_START>(
+      [&](int t, int mb, int part) {
+        return __builtin_bit_cast(v8bf, f[(part * (M / 16) * T + mb * T + t) * 64]);
+      },
+      in, acc);
+}
+template <bool BF, int M, int K>
+__device__ __forceinline__ void gemm_wf(const void* __restrict__ w, const float (&in)[K / 4], float (&acc)[M / 4],
+                                        int lane) {
+  Op<BF, K> o;
+  make_op(in, o);
+  gemm_wf<BF, M, K>(w, o, acc, lane);
+}
+
 // Dispatch on the GEMM operand type.  frag points at the fragments of one
 // matrix (FP32: M*K floats; BF16: M*K bf16 values).
 template <bool BF, int MB, int KB, bool ROT = false>
@@ -243,6 +465,118 @@ __device__ __forceinline__ void gemm(const void* frag, const float (&in)[4 * KB]
     gemm_bf16<MB, KB>(reinterpret_cast<const uint4*>(frag), in, acc, lane);
   else
     gemm_f32<MB, KB, ROT>(reinterpret_cast<const float*>(frag), in, acc, lane);
+}
+
+// ---------------------------------------------- row-major BF16 tiles in LDS
+//
+// [rows][W] BF16 with the 8-byte chunk c of row r at chunk c ^ stg_swz(r):
+// with 32 chunks per LDS bank cycle the 32 lanes of a half wave hit all banks
+// once, in row accesses (16 rows, two chunks each) and in the transposing
+// reads below (8 rows, four chunks each), with no padding.
+template <int W>
+__device__ __forceinline__ int stg_swz(int row) {
+  constexpr int U = W / 4;                 // 8-byte chunks per row
+  constexpr int RP = U >= 32 ? 1 : 32 / U;  // rows per 256 bytes of LDS
+  constexpr int KR = 8 / RP;               // such groups in 8 rows
+  const int k = (row & 15) / RP;
+  return ((k & (KR - 1)) << 2) | (((k / KR) & 1) << 1);
+}
+
+// MFMA operand of a tile, its rows along K: lane (i, kk) receives feature 16 fb + i of rows r0 + 4 kk + 0..3 and r0 + 16 + 4 kk + 0..3 (r0 a
+// multiple of 16; the same row order for both operands of a product).
+// tr_base: the lane's address for feature block fb.
+typedef __attribute__((address_space(3))) v4bf lds_v4bf;
+template <int W>
+__device__ __forceinline__ const char* tr_base(const void* __restrict__ tile, int fb, int lane) {
+  const int row = 4 * (lane >> 4) + ((lane & 15) >> 2);
+  return reinterpret_cast<const char*>(tile) + row * (W * 2) + (((4 * fb + (lane & 3)) ^ stg_swz<W>(row)) * 8);
+}
+__device__ __forceinline__ v4bf tr_read4(const char* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_v4bf*)(p));
+}
+template <int W>
+__device__ __forceinline__ v8bf tr_read8(const char* base, int r0) {
+  const v4bf lo = tr_read4(base + r0 * (W * 2)), hi = tr_read4(base + (r0 + 16) * (W * 2));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// Row `row` of an operand into a tile (FP32: three tiles, part_bytes apart).
+template <int W>
+__device__ __forceinline__ void put_row(char* __restrict__ t, int g, int sz, const v8bf (&v)[W / 32]) {
+#pragma unroll
+  for (int b = 0; b < W / 16; ++b) {
+    const v4u q = __builtin_bit_cast(v4u, v[b / 2]);
+    *reinterpret_cast<u32x2*>(t + ((4 * b + g) ^ sz) * 8) = b % 2 ? u32x2{q[2], q[3]} : u32x2{q[0], q[1]};
+  }
+}
+template <int W>
+__device__ __forceinline__ void stage_op(void* __restrict__ tile, int part_bytes, int row, int g,
+                                         const Op<false, W>& o) {
+  const int sz = stg_swz<W>(row);
+  char* t = reinterpret_cast<char*>(tile) + row * (W * 2);
+  put_row<W>(t, g, sz, o.h);
+  put_row<W>(t + part_bytes, g, sz, o.m);
+  put_row<W>(t + 2 * part_bytes, g, sz, o.l);
+}
+
+// Weights row major in LDS for both products: gemm_wn reads W's operand,
+// lane (i, g) columns 32 t + 4 g + 0..3 and 32 t + 16 + 4 g + 0..3 of row
+// 16 mb + i, gemm_wt (W^T in) reads the same copy through the transposing
+// load.  Groups of 16 rows are 16 bytes apart, so that no two 8-byte reads of
+// an operand lie a multiple of 512 bytes from another's: the compiler would
+// pair those into one read and then move every register into place (147 of
+// 1425 vector instructions per block of the FP32 edge adjoint).
+__host__ __device__ constexpr int wrow_at(int row, int K) { return row * (K * 2) + (row >> 4) * 16; }
+__host__ __device__ constexpr int wrow_part(int M, int K) { return wrow_at(M, K); }
+__host__ __device__ constexpr size_t wrow_bytes(int M, int K, bool bf) { return size_t(wrow_part(M, K)) * (bf ? 1 : 3); }
+
+// Stage the M x K matrix w (not transposed).  All threads of the workgroup; no
+// barrier.
+template <bool BF, int M, int K>
+__device__ __forceinline__ void stage_wrow(void* __restrict__ dst, const WView& w) {
+  for (int e = threadIdx.x; e < M * K / 8; e += blockDim.x) {
+    const int row = e / (K / 8), c = e % (K / 8) * 2;  // chunks c, c + 1
+    const float4 a = *reinterpret_cast<const float4*>(w.p + (int64_t)row * w.ld + 4 * c);
+    const float4 b = *reinterpret_cast<const float4*>(w.p + (int64_t)row * w.ld + 4 * c + 4);
+    const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    v8bf p[3];
+    split_w8<BF>(x, p[0], p[1], p[2]);
+    const int sz = stg_swz<K>(row);
+    char* t = reinterpret_cast<char*>(dst) + wrow_at(row, K);
+#pragma unroll
+    for (int q = 0; q < (BF ? 1 : 3); ++q) {
+      const v4u v = __builtin_bit_cast(v4u, p[q]);
+      *reinterpret_cast<u32x2*>(t + q * wrow_part(M, K) + (c ^ sz) * 8) = u32x2{v[0], v[1]};
+      *reinterpret_cast<u32x2*>(t + q * wrow_part(M, K) + ((c + 1) ^ sz) * 8) = u32x2{v[2], v[3]};
+    }
+  }
+}
+// acc += W in (ACC_SET: acc = W in)
+template <bool BF, int M, int K, Acc MODE = ACC_START>
+__device__ __forceinline__ void gemm_wn(const char* __restrict__ w, const Op<BF, K>& in, float (&acc)[M / 4],
+                                        int lane) {
+  const int i = lane & 15, g = lane >> 4, sz = stg_swz<K>(i);
+  const char* p = w + i * (K * 2);
+  gemm_op<M / 16, K / 32, MODE>(
+      [&](int t, int mb, int part) {
+        const char* q = p + part * wrow_part(M, K) + wrow_at(16 * mb, K);
+        const v4bf lo = __builtin_bit_cast(v4bf, *reinterpret_cast<const u32x2*>(q + ((8 * t + g) ^ sz) * 8));
+        const v4bf hi = __builtin_bit_cast(v4bf, *reinterpret_cast<const u32x2*>(q + ((8 * t + 4 + g) ^ sz) * 8));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      },
+      in, acc);
+}
+// acc += W^T in (ACC_SET: acc = W^T in)
+template <bool BF, int M, int K, Acc MODE = ACC_START>
+__device__ __forceinline__ void gemm_wt(const char* __restrict__ w, const Op<BF, M>& in, float (&acc)[K / 4],
+                                        int lane) {
+  gemm_op<K / 16, M / 32, MODE>(
+      [&](int t, int mb, int part) {
+        const char* q = tr_base<K>(w + part * wrow_part(M, K), mb, lane);
+        const v4bf lo = tr_read4(q + wrow_at(32 * t, K)), hi = tr_read4(q + wrow_at(32 * t + 16, K));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      },
+      in, acc);
 }
 
 // Bytes of the packed fragments of an M x K matrix.

@@ -70,29 +70,78 @@ __device__ __forceinline__ void stage_to_lds(uint4* __restrict__ dst, const void
 
 // ------------------------------------------------------------ projections
 
+// Row-aligned tiles of about kTileEdges edges: tile t starts at the first
+// row whose first edge index is at least floor(t * E / T); the last tile
+// ends at n_rows.  One thread per boundary.
+__device__ __forceinline__ void tile_bounds(const TileJob& j, int64_t t) {
+  if (j.queue && t < 8) j.queue[t] = 0;
+  if (t > j.n_tiles) return;
+  const int64_t E = j.rowptr[j.n_rows];
+  int64_t r = (t == 0) ? 0 : (t == j.n_tiles ? j.n_rows : lower_bound_i32(j.rowptr, j.n_rows + 1, (t * E) / j.n_tiles));
+  if (r > j.n_rows) r = j.n_rows;
+  j.tile_r[t] = (int32_t)r;
+  j.tile_e[t] = j.rowptr[r];
+}
+
+__global__ __launch_bounds__(256) void k_tiles(TileJob j) {
+  tile_bounds(j, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+hipError_t launch_tiles(const TileJob& j, hipStream_t s) {
+  const int grid = (int)((j.n_tiles + 1 + 255) / 256);
+  hipLaunchKernelGGL(k_tiles, dim3(grid), dim3(256), 0, s, j);
+  return hipGetLastError();
+}
+
+// Waves per workgroup and resident waves per SIMD the forward kernels are
+// compiled for, given the matrices' bytes in LDS.  FP32 products keep three
+// BF16 parts of each weight (48 KB for two 64 x 64 matrices, 72 KB for the
+// node update's) and want about 160 registers: three workgroups of four waves
+// (or two of six) fill a CU with three waves per SIMD.
+template <bool BF>
+constexpr int fwd_waves(size_t lds_w) { return !BF && lds_w > 50 * 1024 && lds_w <= 80 * 1024 ? 6 : 4; }
+template <int H, bool BF>
+constexpr int fwd_occ(size_t lds_w) { return H > 64 ? 1 : (!BF && lds_w > 40 * 1024 ? 3 : 4); }
+
+// Workgroups of a persistent row grid: `grid` counts four-wave workgroups;
+// never more than the CUs hold at once (the rest would run as a second, nearly
+// empty round: 768 resident workgroups of 1024 take as long as 1536).
+static int fit_grid(int grid, int waves, int occ, size_t lds) {
+  const int per_cu = std::max<int>(1, std::min<int>(4 * occ / waves, (int)((160 * 1024) / std::max<size_t>(lds, 1))));
+  return std::max(1, std::min((grid * 4 + waves - 1) / waves, 256 * per_cu));
+}
+
 // P = W1a x + b1, Q = W1b x: the receiver and sender parts of the first
 // edge-MLP Linear applied once per node instead of once per edge.  This
 // splits the Linear of Eq. 4a over its concatenated input; the products
-// are the same, only the summation grouping differs.
+// are the same, only the summation grouping differs.  The workgroups from
+// `n_main` on compute the edge kernels' tile bounds, which the next launch
+// needs too (a launch of their own costs about 5 us of a small layer).
 template <int H, bool BF>
-__global__ __launch_bounds__(256, (H <= 64 ? 4 : 1)) void k_proj(int64_t n_rows, const float* __restrict__ x,
-                                              const void* __restrict__ frag, const float* __restrict__ b1,
-                                              float* __restrict__ P, float* __restrict__ Q) {
+__global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (fwd_occ<H, BF>(2 * w_bytes(H, H, BF)))) void k_proj(
+    int64_t n_rows, const float* __restrict__ x, WSrc wa, WSrc wb, const float* __restrict__ b1,
+    float* __restrict__ P, float* __restrict__ Q, int n_main, TileJob tj) {
   constexpr int NF = H / 4, MB = H / 16;
-  constexpr size_t FB = frag_bytes(H, H, BF);
-  constexpr bool LDS = 2 * FB <= kProjLdsBudget;
+  constexpr bool RAW = raw_weights(H, BF);
+  constexpr size_t FB = RAW ? w_bytes(H, H, BF) : frag_bytes(H, H, BF);
+  static_assert(2 * FB <= kProjLdsBudget, "both matrices in LDS");
   extern __shared__ uint4 smem[];
-  const char* fr;
-  if constexpr (LDS) {
-    stage_to_lds(smem, frag, 2 * FB);
-    __syncthreads();
-    fr = reinterpret_cast<const char*>(smem);
-  } else {
-    fr = reinterpret_cast<const char*>(frag);
+  if ((int)blockIdx.x >= n_main) {
+    tile_bounds(tj, (int64_t)((int)blockIdx.x - n_main) * blockDim.x + threadIdx.x);
+    return;
   }
+  if constexpr (RAW) {
+    stage_wfrag<BF, H, H>(smem, wa.w);
+    stage_wfrag<BF, H, H>(smem + FB / 16, wb.w);
+  } else {
+    stage_to_lds(smem, wa.frag, FB);
+    stage_to_lds(smem + FB / 16, wb.frag, FB);
+  }
+  __syncthreads();
+  const char* fr = reinterpret_cast<const char*>(smem);
   const int lane = lane_id(), j = lane & 15, g = lane >> 4;
   const int nw = blockDim.x / 64;
-  const int64_t nblk = (n_rows + 15) / 16, stride = (int64_t)gridDim.x * nw;
+  const int64_t nblk = (n_rows + 15) / 16, stride = (int64_t)n_main * nw;
   // one block ahead: the next block's x row loads before this block computes
   int64_t blk = (int64_t)blockIdx.x * nw + threadIdx.x / 64;
   float xn[NF];
@@ -110,8 +159,16 @@ __global__ __launch_bounds__(256, (H <= 64 ? 4 : 1)) void k_proj(int64_t n_rows,
     load_vec<H>(b1, g, p);
 #pragma unroll
     for (int i = 0; i < NF; ++i) q[i] = 0.f;
-    gemm<BF, MB, MB>(fr, xv, p, lane);
-    gemm<BF, MB, MB>(fr + FB, xv, q, lane);
+    if constexpr (RAW) {
+      const char* frb = fr + opaque_zero();
+      Op<BF, H> xo;
+      make_op(xv, xo);
+      gemm_wf<BF, H, H>(frb, xo, p, lane);
+      gemm_wf<BF, H, H>(frb + FB, xo, q, lane);
+    } else {
+      gemm<BF, MB, MB>(fr, xv, p, lane);
+      gemm<BF, MB, MB>(fr + FB, xv, q, lane);
+    }
 #pragma unroll
     for (int i = 0; i < NF; ++i) asm volatile("" : "+v"(xn[i]));  // before this block's stores
     if (valid) {
@@ -121,49 +178,32 @@ __global__ __launch_bounds__(256, (H <= 64 ? 4 : 1)) void k_proj(int64_t n_rows,
   }
 }
 
+// grid: 4-wave workgroups' worth of row blocks.
 template <int H, bool BF>
-static hipError_t launch_proj_t(const DevGraph& gr, const float* x, const void* frag, const float* b1,
-                                float* P, float* Q, int grid, hipStream_t s) {
-  constexpr size_t FB = frag_bytes(H, H, BF);
-  const size_t lds = (2 * FB <= kProjLdsBudget) ? 2 * FB : 0;
-  if (lds > 64 * 1024) (void)hipFuncSetAttribute((const void*)k_proj<H, BF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((k_proj<H, BF>), dim3(grid), dim3(256), lds, s, gr.n_rows, x, frag, b1, P, Q);
+static hipError_t launch_proj_t(int64_t n_rows, const float* x, const WSrc& wa, const WSrc& wb, const float* b1,
+                                float* P, float* Q, int grid, const TileJob& tj, hipStream_t s) {
+  constexpr size_t FB = raw_weights(H, BF) ? w_bytes(H, H, BF) : frag_bytes(H, H, BF);
+  constexpr int NW = fwd_waves<BF>(2 * FB);
+  const int n_main = fit_grid(grid, NW, H > 64 ? 2 : fwd_occ<H, BF>(2 * FB), 2 * FB);
+  const int n_tile = (int)((tj.n_tiles + 1 + 64 * NW - 1) / (64 * NW));
+  if (2 * FB > 64 * 1024)
+    (void)hipFuncSetAttribute((const void*)k_proj<H, BF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2 * FB));
+  hipLaunchKernelGGL((k_proj<H, BF>), dim3(n_main + n_tile), dim3(64 * NW), 2 * FB, s, n_rows, x, wa, wb, b1, P, Q,
+                     n_main, tj);
   return hipGetLastError();
 }
 
-hipError_t launch_proj(int H, bool bf, const DevGraph& g, const float* x, const void* frag, const float* b1,
-                       float* P, float* Q, int grid, hipStream_t s) {
-#define MP_CASE(HH)                                                            \
-  if (H == HH) return bf ? launch_proj_t<HH, true>(g, x, frag, b1, P, Q, grid, s) \
-                         : launch_proj_t<HH, false>(g, x, frag, b1, P, Q, grid, s);
+hipError_t launch_proj(int H, bool bf, int64_t n_rows, const float* x, const WSrc& wa, const WSrc& wb,
+                       const float* b1, float* P, float* Q, int grid, const TileJob& tj, hipStream_t s) {
+#define MP_CASE(HH)                                                                        \
+  if (H == HH) return bf ? launch_proj_t<HH, true>(n_rows, x, wa, wb, b1, P, Q, grid, tj, s) \
+                         : launch_proj_t<HH, false>(n_rows, x, wa, wb, b1, P, Q, grid, tj, s);
   MP_CASE(32) MP_CASE(64) MP_CASE(128)
 #undef MP_CASE
   return hipErrorInvalidValue;
 }
 
 // --------------------------------------------- edge update + aggregation
-
-// Row-aligned tiles of about kTileEdges edges: tile t starts at the first
-// row whose first edge index is at least floor(t * E / T); the last tile
-// ends at n_rows.  One thread per boundary.
-__global__ __launch_bounds__(256) void k_tiles(const int32_t* __restrict__ rowptr, int64_t n_rows, int64_t T,
-                                               int32_t* __restrict__ tile_r, int32_t* __restrict__ tile_e,
-                                               int32_t* __restrict__ queue) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (queue && t < 8) queue[t] = 0;
-  if (t > T) return;
-  const int64_t E = rowptr[n_rows];
-  int64_t r = (t == 0) ? 0 : (t == T ? n_rows : lower_bound_i32(rowptr, n_rows + 1, (t * E) / T));
-  if (r > n_rows) r = n_rows;
-  tile_r[t] = (int32_t)r;
-  tile_e[t] = rowptr[r];
-}
-
-hipError_t launch_tiles(const DevGraph& g, int32_t* tile_r, int32_t* tile_e, int32_t* queue, hipStream_t s) {
-  const int grid = (int)((g.n_tiles + 1 + 255) / 256);
-  hipLaunchKernelGGL(k_tiles, dim3(grid), dim3(256), 0, s, g.rowptr, g.n_rows, g.n_tiles, tile_r, tile_e, queue);
-  return hipGetLastError();
-}
 
 // Eq. 4a-b, one row-aligned tile at a time per wave (schedule: tile_sched).
 // For every directed edge k (receiver i, sender j):
@@ -179,30 +219,32 @@ hipError_t launch_tiles(const DevGraph& g, int32_t* tile_r, int32_t* tile_e, int
 // the fixed round robin of tile_sched.  ES: e_in and e_out hold BF16 (the
 // update and the aggregation run in FP32; e' is rounded where it is stored).
 template <int H, bool BF, bool AM, bool DQ, bool ES>
-__global__ __launch_bounds__(256, (H <= 64 ? 4 : 2)) void k_edge_fwd(DevGraph gr, const float* __restrict__ P,
+__global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (H > 64 ? 2 : fwd_occ<H, BF>(2 * w_bytes(H, H, BF)))) void k_edge_fwd(DevGraph gr, const float* __restrict__ P,
                                                   const float* __restrict__ Q, const void* __restrict__ e_in,
-                                                  const void* __restrict__ frag, const float* __restrict__ b2,
+                                                  WSrc w1c, WSrc w2, const float* __restrict__ b2,
                                                   const float* __restrict__ lng, const float* __restrict__ lnb,
                                                   int ln, float eps, void* __restrict__ e_out,
                                                   float* __restrict__ a_out) {
   constexpr int NF = H / 4, MB = H / 16;
-  constexpr size_t FB = frag_bytes(H, H, BF);
-  constexpr bool LDS = 2 * FB <= kEdgeLdsBudget;
+  constexpr bool RAW = raw_weights(H, BF);
+  constexpr size_t FB = RAW ? w_bytes(H, H, BF) : frag_bytes(H, H, BF);
+  static_assert(2 * FB <= kEdgeLdsBudget, "both matrices in LDS");
   extern __shared__ uint4 smem[];
-  const char* fr;
+  const char* fr = reinterpret_cast<const char*>(smem);
   // per-feature vectors (b2, LayerNorm gain and shift) live in LDS after the
   // fragments and are re-read per block rather than held in registers
-  float* vecs = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + (LDS ? 2 * FB : 0));
+  float* vecs = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + 2 * FB);
   // the open row's partial sum, handed from lane 15 of one block to lane 0
   // of the next through LDS (same wave, so no barrier is needed)
   float* carry = vecs + 3 * H + (threadIdx.x / 64) * H + (threadIdx.x / 16 % 4) * (H / 4);
   for (int t = threadIdx.x; t < 3 * H; t += blockDim.x)
     vecs[t] = t < H ? b2[t] : (ln ? (t < 2 * H ? lng[t - H] : lnb[t - 2 * H]) : 0.f);
-  if constexpr (LDS) {
-    stage_to_lds(smem, frag, 2 * FB);
-    fr = reinterpret_cast<const char*>(smem);
+  if constexpr (RAW) {
+    stage_wfrag<BF, H, H>(smem, w1c.w);
+    stage_wfrag<BF, H, H>(smem + FB / 16, w2.w);
   } else {
-    fr = reinterpret_cast<const char*>(frag);
+    stage_to_lds(smem, w1c.frag, FB);
+    stage_to_lds(smem + FB / 16, w2.frag, FB);
   }
   __syncthreads();
   const int lane = lane_id(), j = lane & 15, g = lane >> 4;
@@ -261,13 +303,19 @@ __global__ __launch_bounds__(256, (H <= 64 ? 4 : 2)) void k_edge_fwd(DevGraph gr
       __builtin_amdgcn_sched_barrier(0);  // all row loads issue before any use
 #pragma unroll
       for (int i = 0; i < NF; ++i) h[i] += q[i];
-      gemm<BF, MB, MB>(frb, ev, h, lane);
+      if constexpr (RAW)
+        gemm_wf<BF, H, H>(frb, ev, h, lane);
+      else
+        gemm<BF, MB, MB>(frb, ev, h, lane);
 #pragma unroll
       for (int i = 0; i < NF; ++i) h[i] = elu(h[i]);
       float m[NF];
       const float* vb = vecs + opaque_zero();
       load_vec<H>(vb, g, m);
-      gemm<BF, MB, MB>(frb + FB, h, m, lane);
+      if constexpr (RAW)
+        gemm_wf<BF, H, H>(frb + FB, h, m, lane);
+      else
+        gemm<BF, MB, MB>(frb + FB, h, m, lane);
       if (ln) {
         float mean, rstd, gam[NF], bet[NF];
         ln_stats<H>(m, eps, mean, rstd);
@@ -315,43 +363,44 @@ __global__ __launch_bounds__(256, (H <= 64 ? 4 : 2)) void k_edge_fwd(DevGraph gr
 
 template <int H, bool BF, bool AM, bool DQ, bool ES>
 static hipError_t launch_edge_fwd_t(const DevGraph& g, const float* P, const float* Q, const void* e_in,
-                                    const void* frag, const float* b2, const float* lng, const float* lnb, int ln,
+                                    const WSrc& w1c, const WSrc& w2, const float* b2, const float* lng, const float* lnb, int ln,
                                     float eps, void* e_out, float* a_out, int grid, hipStream_t s) {
-  constexpr size_t FB = frag_bytes(H, H, BF);
-  // fragments, 3 per-feature vectors, per-wave carries (4 waves)
-  const size_t lds = ((2 * FB <= kEdgeLdsBudget) ? 2 * FB : 0) + 3 * H * sizeof(float) + 4 * H * sizeof(float);
+  constexpr size_t FB = raw_weights(H, BF) ? w_bytes(H, H, BF) : frag_bytes(H, H, BF);
+  constexpr int NW = fwd_waves<BF>(2 * FB);
+  // fragments, 3 per-feature vectors, per-wave carries
+  constexpr size_t lds = 2 * FB + (3 + NW) * H * sizeof(float);
   if (lds > 64 * 1024)
     (void)hipFuncSetAttribute((const void*)k_edge_fwd<H, BF, AM, DQ, ES>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
-  hipLaunchKernelGGL((k_edge_fwd<H, BF, AM, DQ, ES>), dim3(grid), dim3(256), lds, s, g, P, Q, e_in, frag, b2, lng, lnb,
+  hipLaunchKernelGGL((k_edge_fwd<H, BF, AM, DQ, ES>), dim3(grid), dim3(64 * NW), lds, s, g, P, Q, e_in, w1c, w2, b2, lng, lnb,
                      ln, eps, e_out, a_out);
   return hipGetLastError();
 }
 
 template <int H, bool BF, bool ES>
 static hipError_t launch_edge_fwd_am(bool am, bool dq, const DevGraph& g, const float* P, const float* Q,
-                                     const void* e_in, const void* frag, const float* b2, const float* lng,
+                                     const void* e_in, const WSrc& w1c, const WSrc& w2, const float* b2, const float* lng,
                                      const float* lnb, int ln, float eps, void* e_out, float* a_out, int grid,
                                      hipStream_t s) {
 #define MP_EFWD(AMV, DQV) \
-  launch_edge_fwd_t<H, BF, AMV, DQV, ES>(g, P, Q, e_in, frag, b2, lng, lnb, ln, eps, e_out, a_out, grid, s)
+  launch_edge_fwd_t<H, BF, AMV, DQV, ES>(g, P, Q, e_in, w1c, w2, b2, lng, lnb, ln, eps, e_out, a_out, grid, s)
   if (dq) return am ? MP_EFWD(true, true) : MP_EFWD(false, true);
   return am ? MP_EFWD(true, false) : MP_EFWD(false, false);
 #undef MP_EFWD
 }
 
 hipError_t launch_edge_fwd(int H, bool ln, bool bf, bool am, bool dq, bool es, const DevGraph& g, const float* P,
-                           const float* Q, const void* e_in, const void* frag, const float* b2, const float* lng,
+                           const float* Q, const void* e_in, const WSrc& w1c, const WSrc& w2, const float* b2, const float* lng,
                            const float* lnb, float eps, void* e_out, float* a_out, int grid, hipStream_t s) {
   if (es && !bf) return hipErrorInvalidValue;  // BF16 edge states go with BF16 products
 #define MP_CASE(HH)                                                                                              \
   if (H == HH) {                                                                                                 \
     if (bf && es)                                                                                                \
-      return launch_edge_fwd_am<HH, true, true>(am, dq, g, P, Q, e_in, frag, b2, lng, lnb, ln, eps, e_out, a_out, \
+      return launch_edge_fwd_am<HH, true, true>(am, dq, g, P, Q, e_in, w1c, w2, b2, lng, lnb, ln, eps, e_out, a_out, \
                                                 grid, s);                                                        \
-    return bf ? launch_edge_fwd_am<HH, true, false>(am, dq, g, P, Q, e_in, frag, b2, lng, lnb, ln, eps, e_out,    \
+    return bf ? launch_edge_fwd_am<HH, true, false>(am, dq, g, P, Q, e_in, w1c, w2, b2, lng, lnb, ln, eps, e_out,    \
                                                     a_out, grid, s)                                              \
-              : launch_edge_fwd_am<HH, false, false>(am, dq, g, P, Q, e_in, frag, b2, lng, lnb, ln, eps, e_out,   \
+              : launch_edge_fwd_am<HH, false, false>(am, dq, g, P, Q, e_in, w1c, w2, b2, lng, lnb, ln, eps, e_out,   \
                                                      a_out, grid, s);                                            \
   }
   MP_CASE(32) MP_CASE(64) MP_CASE(128)
@@ -448,9 +497,13 @@ struct MlpFwdIn {
 
 template <int H, int KIN, bool TIN, bool TOUT, bool BF>
 struct MlpFwdCfg {
-  static constexpr size_t F0 = TIN ? 0 : frag_bytes(H, KIN, BF);
-  static constexpr size_t F1 = TOUT ? 0 : frag_bytes(H, H, BF);
+  static constexpr bool RAW = raw_weights(H, BF);
+  static constexpr size_t F0 = TIN ? 0 : RAW ? w_bytes(H, KIN, BF) : frag_bytes(H, KIN, BF);
+  static constexpr size_t F1 = TOUT ? 0 : RAW ? w_bytes(H, H, BF) : frag_bytes(H, H, BF);
   static constexpr bool LDS_FRAG = (F0 + F1) <= kRowMlpLdsBudget;
+  static constexpr int NW = RAW ? fwd_waves<BF>(F0 + F1) : 4;
+  static constexpr int OCC = fwd_occ<H, BF>(F0 + F1);
+  static_assert(LDS_FRAG || !RAW, "weights staged from their FP32 matrices sit in LDS");
   static constexpr size_t SMALL = (TIN || TOUT) ? 16 * H : 0;  // small W0 [H][4] or W1 [4][H]
   static constexpr size_t VECS = 4 * H * sizeof(float);        // b0, b1, LayerNorm gain, shift
   // when both do not fit (FP32, H = 128, 2H inputs), W0 alone may: the larger
@@ -463,7 +516,7 @@ struct MlpFwdCfg {
 // OB: the H-wide output is stored as BF16 (the edge encoder's output, an
 // edge state, when edge states are BF16).
 template <int H, int KIN, bool TIN, bool TOUT, bool BF, bool OB>
-__global__ __launch_bounds__(256, (H <= 64 ? 4 : 1)) void k_mlp_fwd(MlpFwdArgs a) {
+__global__ __launch_bounds__((64 * MlpFwdCfg<H, KIN, TIN, TOUT, BF>::NW), (MlpFwdCfg<H, KIN, TIN, TOUT, BF>::OCC)) void k_mlp_fwd(MlpFwdArgs a) {
   using C = MlpFwdCfg<H, KIN, TIN, TOUT, BF>;
   constexpr int NF = H / 4, MB = H / 16, KB = TIN ? 1 : KIN / 16;
   extern __shared__ uint4 smem[];
@@ -478,7 +531,12 @@ __global__ __launch_bounds__(256, (H <= 64 ? 4 : 1)) void k_mlp_fwd(MlpFwdArgs a
     const int q = t / H, f = t % H;
     vecs[t] = q == 0 ? a.b0[f] : q == 1 ? (TOUT ? 0.f : a.b1[f]) : q == 2 ? (a.ln ? a.lng[f] : 0.f) : (a.ln ? a.lnb[f] : 0.f);
   }
-  if constexpr (C::LDS_FRAG) {
+  if constexpr (C::RAW) {
+    if constexpr (!TIN) stage_wfrag<BF, H, KIN>(smem, WView{a.W0, KIN, 0});
+    if constexpr (!TOUT) stage_wfrag<BF, H, H>(smem + C::F0 / 16, WView{a.W1, H, 0});
+    f0 = reinterpret_cast<const char*>(smem);
+    f1 = f0 + C::F0;
+  } else if constexpr (C::LDS_FRAG) {
     if (C::F0) stage_to_lds(smem, a.frag0, C::F0);
     if (C::F1) stage_to_lds(smem + C::F0 / 16, a.frag1, C::F1);
     f0 = reinterpret_cast<const char*>(smem);
@@ -515,6 +573,8 @@ __global__ __launch_bounds__(256, (H <= 64 ? 4 : 1)) void k_mlp_fwd(MlpFwdArgs a
     load_vec<H>(vb, g, z);
     if constexpr (TIN) {
       small_in_linear<H>(small + opaque_zero(), cur.in, g, z);
+    } else if constexpr (C::RAW) {
+      gemm_wf<BF, H, KIN>(f0 + opaque_zero(), cur.in, z, lane);
     } else {
       gemm<BF, MB, KB>(f0 + opaque_zero(), cur.in, z, lane);
     }
@@ -536,7 +596,10 @@ __global__ __launch_bounds__(256, (H <= 64 ? 4 : 1)) void k_mlp_fwd(MlpFwdArgs a
     } else {
       float y[NF];
       load_vec<H>(vb + H, g, y);
-      gemm<BF, MB, MB>(f1 + opaque_zero(), z, y, lane);
+      if constexpr (C::RAW)
+        gemm_wf<BF, H, H>(f1 + opaque_zero(), z, y, lane);
+      else
+        gemm<BF, MB, MB>(f1 + opaque_zero(), z, y, lane);
       if (a.ln) {
         float mean, rstd, gm[NF], bt[NF];
         load_vec<H>(vb + 2 * H, g, gm);
@@ -570,7 +633,7 @@ static hipError_t launch_mlp_fwd_t(const MlpFwdArgs& a, int grid, hipStream_t s)
   if (C::LDS > 64 * 1024)
     (void)hipFuncSetAttribute((const void*)k_mlp_fwd<H, KIN, TIN, TOUT, BF, OB>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
-  hipLaunchKernelGGL((k_mlp_fwd<H, KIN, TIN, TOUT, BF, OB>), dim3(grid), dim3(256), C::LDS, s, a);
+  hipLaunchKernelGGL((k_mlp_fwd<H, KIN, TIN, TOUT, BF, OB>), dim3(fit_grid(grid, C::NW, H > 64 ? 2 : C::OCC, C::LDS)), dim3(64 * C::NW), C::LDS, s, a);
   return hipGetLastError();
 }
 

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mp_device.hpp"
+
 namespace mp {
 
 // One matrix to pack into MFMA fragments: element (r, c) of the packed
@@ -46,20 +48,36 @@ struct DevGraph {
 
 // Edges per tile of the edge kernels' schedule.
 constexpr int kTileEdges = 128;
-// Also zeroes queue[0..7] when queue is not null.
-hipError_t launch_tiles(const DevGraph& g, int32_t* tile_r, int32_t* tile_e, int32_t* queue, hipStream_t s);
+// The tile bounds to compute (also zeroes queue[0..7] when queue is not null).
+struct TileJob {
+  const int32_t* rowptr;
+  int64_t n_rows, n_tiles;
+  int32_t *tile_r, *tile_e, *queue;
+};
+hipError_t launch_tiles(const TileJob& j, hipStream_t s);
+
+// Where a kernel takes a weight matrix from: the FP32 matrix itself, staged by
+// the kernel (raw_weights), or fragments packed by launch_pack.  FP32 products
+// at H = 128 use the FP32 matrix instructions and packed fragments: the three
+// BF16 parts of two 128 x 128 matrices (192 KB) do not fit in LDS.
+constexpr bool raw_weights(int H, bool bf) { return bf || H <= 64; }
+struct WSrc {
+  WView w;
+  const void* frag;
+};
 
 // Launch helpers; each returns the hipError_t of the launch.
 hipError_t launch_pack(const PackJobs& jobs, void* dst, hipStream_t s);
 
-hipError_t launch_proj(int H, bool bf, const DevGraph& g, const float* x, const void* frag_ab,
-                       const float* b1, float* P, float* Q, int grid, hipStream_t s);
+// also computes the tile bounds tj
+hipError_t launch_proj(int H, bool bf, int64_t n_rows, const float* x, const WSrc& wa, const WSrc& wb,
+                       const float* b1, float* P, float* Q, int grid, const TileJob& tj, hipStream_t s);
 
 // am: aggregate the edge MLP's output (message) instead of the updated state;
 // dq: waves take tiles from per-XCD atomic counters (g.queue) instead of a
 // fixed round robin; es: edge states e_in / e_out stored as BF16 (with bf only)
 hipError_t launch_edge_fwd(int H, bool ln, bool bf, bool am, bool dq, bool es, const DevGraph& g, const float* P,
-                           const float* Q, const void* e_in, const void* frag_c2, const float* b2,
+                           const float* Q, const void* e_in, const WSrc& w1c, const WSrc& w2, const float* b2,
                            const float* lng, const float* lnb, float eps, void* e_out, float* a_out, int grid,
                            hipStream_t s);
 
@@ -75,15 +93,15 @@ struct MlpFwdArgs {
   const float* src1;
   const float* resid;
   int k0, k1, H, n_out, ln, bf;
-  const float* W0;  // raw weights (small-input form)
+  const float* W0;  // the FP32 matrices
   const float* b0;
-  const float* W1;  // raw weights (small-output form)
+  const float* W1;
   const float* b1;
   const float* lng;
   const float* lnb;
   float eps;
-  const void* frag0;  // packed W0 (when k0 >= 16)
-  const void* frag1;  // packed W1 (when n_out == H)
+  const void* frag0;  // packed W0 (k0 >= 16, without raw_weights)
+  const void* frag1;  // packed W1 (n_out == H, without raw_weights)
   void* out;          // [n][n_out], FP32, or BF16 with out_bf
   int out_bf;         // small-input form with BF16 GEMMs and n_out == H only
 };
@@ -131,7 +149,7 @@ struct EdgeBwdArgs {
   DevGraph g;
   int H, ln, bf;
   int am;  // the forward aggregated the MLP output (message), not e'
-  int waves;  // waves per workgroup: 0 (default), 4, or 8 (fused kernel: BF16, H <= 64; split kernel: any)
+  int waves;  // waves per workgroup: 0 (default), 4 or 8 (fused BF16 kernel and split kernel; the fused FP32 kernel has 8)
   int es;     // edge states and their gradients (e_in, g_e_out, g_e_in) stored as BF16 (with bf only)
 
   const float* P;
@@ -139,7 +157,7 @@ struct EdgeBwdArgs {
   const void* e_in;
   const void* g_e_out;   // may be null
   const float* g_a;      // gradient of a (after the adjoint halo sum)
-  const void* frag;      // W1c, W2, W2^T, W1c^T fragments, consecutive
+  WSrc w1c, w2;          // with packed fragments: W1c, W2, W2^T, W1c^T, consecutive from w1c.frag
   const float* b2;
   const float* lng;
   const float* lnb;

@@ -1,0 +1,85 @@
+"""FP32 products formed from three BF16 parts per value, at H = 32 and 64.
+
+An FP32 value must pass through a product unchanged (identity weights: every
+one of its 24 bits), whatever its magnitude, and the adjoint must be exactly
+linear in powers of two.  Neither check needs a tolerance.  The meshes end
+inside a 16-edge block, inside a tile and inside a workgroup's tiles; the
+larger one has more tiles than workgroups.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from mpinputs import box_mesh, slab_partition
+
+from _util import layer_params
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+MESHES = {"tail": ((1, 1, 1), 1, 1), "odd": ((3, 5, 2), 3, 2), "many_tiles": ((7, 6, 8), 5, 4)}
+
+
+def _graph(name):
+    from paper_2410_01657_amd import DeviceGraph, build_graph
+    nel, P, R = MESHES[name]
+    m = box_mesh(nel, P)
+    part = slab_partition(nel, R) if R > 1 else np.zeros(m.n_elem, np.int32)
+    return DeviceGraph(build_graph(m.elem_gid, P, part, R), DEV)
+
+
+def _zero_params(H):
+    _, o, names = layer_params(H, False)
+    return {k: torch.zeros(o[v].shape, device=DEV) for k, v in names.items()}
+
+
+def _full_bits(gen, *shape):
+    """Positive FP32 values with random mantissas over 2^-40 .. 2^40."""
+    m = torch.randint(0, 1 << 23, shape, generator=gen, dtype=torch.int32)
+    ex = torch.randint(127 - 40, 127 + 40, shape, generator=gen, dtype=torch.int32)
+    return ((ex << 23) | m).view(torch.float32).to(DEV)
+
+
+@pytest.mark.parametrize("mesh", sorted(MESHES))
+@pytest.mark.parametrize("H", [32, 64])
+def test_identity_weights_keep_every_bit(mesh, H):
+    from paper_2410_01657_amd.ops import layer_backward, layer_cfg, layer_forward
+    dg = _graph(mesh)
+    eye = torch.eye(H, device=DEV)
+    p = _zero_params(H)
+    p["We1"][:, 2 * H:] = eye          # h = e, u = e, m = e: e' = 2 e
+    p["We2"] += eye
+    p["Wn1"][:, H:] = eye              # x' = 2 x
+    p["Wn2"] += eye
+    gen = torch.Generator().manual_seed(H)
+    x, e = _full_bits(gen, dg.n_rows, H), _full_bits(gen, dg.n_edges, H)
+    cfg = layer_cfg(H, False)
+    x2, e2, a = layer_forward(cfg, p, dg, x, e)
+    assert torch.equal(e2, 2 * e)
+    assert torch.equal(x2, 2 * x)
+    ge = _full_bits(gen, dg.n_edges, H)
+    gx = _full_bits(gen, dg.n_rows, H)
+    g_x, g_e, grads = layer_backward(cfg, p, dg, x, e, a, gx, ge)
+    assert torch.equal(g_x, 2 * gx)    # the residual path plus Wn1^T Wn2^T
+    assert torch.equal(g_e, 2 * ge)    # no gradient reaches a*
+
+
+@pytest.mark.parametrize("mesh", sorted(MESHES))
+@pytest.mark.parametrize("H,ln", [(32, False), (32, True), (64, False), (64, True)])
+def test_adjoint_is_linear_in_powers_of_two(mesh, H, ln):
+    from paper_2410_01657_amd.ops import layer_backward, layer_cfg, layer_forward
+    dg = _graph(mesh)
+    _, o, names = layer_params(H, ln)
+    p = {k: torch.from_numpy(o[v].copy()).to(DEV) for k, v in names.items()}
+    gen = torch.Generator().manual_seed(3)
+    r = lambda n: torch.randn(n, H, generator=gen).to(DEV)
+    x, e, gx, ge = r(dg.n_rows), r(dg.n_edges), r(dg.n_rows), r(dg.n_edges)
+    cfg = layer_cfg(H, ln)
+    _, _, a = layer_forward(cfg, p, dg, x, e)
+    ref = layer_backward(cfg, p, dg, x, e, a, gx, ge)
+    for s in (2.0 ** -40, 2.0 ** 40):
+        out = layer_backward(cfg, p, dg, x, e, a, gx * s, ge * s)
+        assert torch.equal(out[0], ref[0] * s) and torch.equal(out[1], ref[1] * s)
+        for k in names:
+            assert torch.equal(out[2][k], ref[2][k] * s), k
