@@ -31,26 +31,13 @@ __device__ __forceinline__ void block_sum_vec(const float (&v)[W / 4], float* __
 }
 
 // The BF16 matrix instruction loses low bits of its partial sums downwards: a
-// bias of some 2^-27 of a term, nothing in one product, but a weight gradient
-// adds millions of terms of either sign and the bias then outgrows their sum
-// (3.5M edges: 4.5e-6 of the gradient, 1.5e-6 with FP32 instructions).  Every
-// other workgroup of an XCD therefore sums -G^T A (the staged parts of G with
-// their signs flipped) and negates its result, so the bias cancels: 0.9e-6.
-__device__ __forceinline__ uint32_t dw_sign_mask() { return (blockIdx.x >> 3) & 1 ? 0x80008000u : 0u; }
+// bias of some 2^-27 of a term, nothing in one product, but a weight or bias
+// gradient adds millions of terms of either sign and the bias then outgrows
+// their sum (3.5M edges: 4.5e-6 of a weight gradient, 1.5e-6 with FP32
+// instructions; 3.6e-6 of db1, from W2^T gm alone).  Every other workgroup of
+// an XCD therefore runs its FP32 adjoint on the negated gradients and negates
+// what it writes, so the bias cancels: 0.9e-6.
 __device__ __forceinline__ float dw_sign() { return (blockIdx.x >> 3) & 1 ? -1.f : 1.f; }
-template <int W>
-__device__ __forceinline__ void flip_op(Op<false, W>& o, uint32_t mask) {
-#pragma unroll
-  for (int t = 0; t < W / 32; ++t) {
-    v4u h = __builtin_bit_cast(v4u, o.h[t]), m = __builtin_bit_cast(v4u, o.m[t]), l = __builtin_bit_cast(v4u, o.l[t]);
-    h ^= mask;
-    m ^= mask;
-    l ^= mask;
-    o.h[t] = __builtin_bit_cast(v8bf, h);
-    o.m[t] = __builtin_bit_cast(v8bf, m);
-    o.l[t] = __builtin_bit_cast(v8bf, l);
-  }
-}
 
 // FP32 weight gradients dW += G^T A over the 16 rows one wave holds, from the
 // three BF16 parts of both factors staged in that wave's own LDS tiles

@@ -559,7 +559,7 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
 
   const DevGraph& gr = a.g;
   const TileSched ts = tile_sched(gr.n_tiles);
-  const uint32_t smask = dw_sign_mask();
+  const float sgn = dw_sign();  // all gradients in the loop carry this sign
   Dw d2, d1;
   d2.zero();
   d1.zero();
@@ -592,7 +592,7 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       const bool valid = k < e1;
       const int64_t kk = valid ? k : e_last;
       const int ri = ic.ri;
-      const float inv_d = 1.f / (float)ic.md;
+      const float inv_d = sgn / (float)ic.md;
       const bool last = valid && ic.nx != ri;
       const int key = valid ? ri + 1 : -1;
       EdgeBwdHead<H> cur = nx;
@@ -630,6 +630,7 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       // gradient reaching e', LayerNorm adjoint (mp becomes gm)
 #pragma unroll
       for (int i = 0; i < NF; ++i) {
+        go[i] *= sgn;
         const float v = gE[i] * inv_d + go[i];
         gE[i] = valid ? v : 0.f;
       }
@@ -662,7 +663,6 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       // gh = (W2^T gm) * ELU'(h); dW2 += gm u^T
       make_op(mp, o);
       gemm_wt<false, H, H, ACC_SET>(w2, o, t, ln);
-      flip_op(o, smask);
       stage_op<H>(tG2, Dw::GP, ln & 15, ln >> 4, o);
       wave_lds_fence();
       d2.add(tG2, tA2, ln);
@@ -675,10 +675,11 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       // g_e = gE + W1c^T gh; dW1c += gh e^T
       make_op(t, o);
       gemm_wt<false, H, H, ACC_ADD>(w1c, o, gE, ln);
-      flip_op(o, smask);
       stage_op<H>(tG1, Dw::GP, ln & 15, ln >> 4, o);
       wave_lds_fence();
       d1.add(tG1, tA1, ln);
+#pragma unroll
+      for (int i = 0; i < NF; ++i) gE[i] *= sgn, t[i] *= sgn;
       nx.settle();
       in.settle();
       if (valid) {
@@ -691,8 +692,10 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
   }
   float* slab = a.part + blockIdx.x * a.slab;
   float* scratch = reinterpret_cast<float*>(smem);
-  d1.template store<NW>(scratch, slab, dw_sign(), wave, lane);
-  d2.template store<NW>(scratch, slab + H * H, dw_sign(), wave, lane);
+  d1.template store<NW>(scratch, slab, sgn, wave, lane);
+  d2.template store<NW>(scratch, slab + H * H, sgn, wave, lane);
+#pragma unroll
+  for (int i = 0; i < NF; ++i) db2[i] *= sgn, dga[i] *= sgn, dbe[i] *= sgn;
   block_sum_vec<H, NW>(db2, scratch, slab + 2 * H * H, wave, lane);
   block_sum_vec<H, NW>(dga, scratch, slab + 2 * H * H + H, wave, lane);
   block_sum_vec<H, NW>(dbe, scratch, slab + 2 * H * H + 2 * H, wave, lane);

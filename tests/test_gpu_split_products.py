@@ -83,3 +83,25 @@ def test_adjoint_is_linear_in_powers_of_two(mesh, H, ln):
         assert torch.equal(out[0], ref[0] * s) and torch.equal(out[1], ref[1] * s)
         for k in names:
             assert torch.equal(out[2][k], ref[2][k] * s), k
+
+
+@pytest.mark.parametrize("H", [32, 64])
+def test_edge_sums_have_no_bias(H):
+    """db1 = W2^T (sum of g_e') for zero We1 and ELU' = 1.  Errors of either
+    sign in the E products add up to some sqrt(E) 2^-24 of a term; a one-sided
+    error of 2^-27 of a term would be E 2^-27, ten times the bound."""
+    from paper_2410_01657_amd.ops import layer_backward, layer_cfg, layer_forward
+    dg = _graph("many_tiles")
+    E = dg.n_edges
+    p = _zero_params(H)
+    gen = torch.Generator().manual_seed(H)
+    p["We2"] += torch.randn(H, H, generator=gen).to(DEV) * H ** -0.5
+    p["be1"] += 1.0
+    x, e = torch.zeros(dg.n_rows, H, device=DEV), torch.zeros(E, H, device=DEV)
+    ge = torch.randn(E, H, generator=gen).to(DEV)
+    cfg = layer_cfg(H, False)
+    _, _, a = layer_forward(cfg, p, dg, x, e)
+    _, _, grads = layer_backward(cfg, p, dg, x, e, a, torch.zeros_like(x), ge)
+    ref = ge.double().sum(0) @ p["We2"].double()
+    err = (grads["be1"].double() - ref).square().mean().sqrt().item()
+    assert err <= 2.0 ** -22 * E ** 0.5
