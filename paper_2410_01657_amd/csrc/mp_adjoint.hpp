@@ -39,53 +39,78 @@ __device__ __forceinline__ void block_sum_vec(const float (&v)[W / 4], float* __
 // what it writes, so the bias cancels: 0.9e-6.
 __device__ __forceinline__ float dw_sign() { return (blockIdx.x >> 3) & 1 ? -1.f : 1.f; }
 
-// FP32 weight gradients dW += G^T A over the 16 rows one wave holds, from the
-// three BF16 parts of both factors staged in that wave's own LDS tiles
-// (stage_op, 16 rows): no other wave takes part, so nothing waits.  Sixteen
-// rows fill half of the matrix instruction's 32-long reduction; the other half
-// takes the same rows of another part: [Gh|Gm] [Ah|Am] = hh + mm, [Gh|Gm]
-// [Am|Ah] = hm + mh, [Gh|Gl] [Al|Ah] = hl + lh, so three instructions do the
-// six products, added straight onto the running sum (one third of the
-// roundings of the FP32 instruction's).
-template <int GW, int AW>
+// FP32 weight gradients dW += G^T A (and, with SUM, the column sums of G) over
+// the 16 rows one wave holds, from the three BF16 parts of both factors staged
+// in that wave's own LDS tiles (stage_op, 16 rows): no other wave takes part,
+// so nothing waits.  Sixteen rows fill half of the matrix instruction's 32-long
+// reduction; the other half takes the same rows of another part: [Gh|Gm]
+// [Ah|Am] = hh + mm, [Gh|Gm] [Am|Ah] = hm + mh, [Gh|Gl] [Al|Ah] = hl + lh, so
+// three instructions do the six products, added straight onto the running sum
+// (fewer roundings than the FP32 instruction's four).  The column sums are
+// products with ones, [Gh|Gm] [1|1] and [Gh|Gl] [0|1]: on the vector unit they
+// would move through the accumulation registers every block.
+template <int GW, int AW, bool SUM>
 struct DwWave {
   static constexpr int FB = GW / 16, KB = AW / 16;
   static constexpr int GP = 16 * GW * 2, AP = 16 * AW * 2;  // bytes of one part
   static constexpr int TILE_G = 3 * GP, TILE_A = 3 * AP;
-  v4f acc[FB * KB];
+  v4f acc[FB * KB], cs[SUM ? FB : 1];
   __device__ __forceinline__ void zero() {
 #pragma unroll
     for (int n = 0; n < FB * KB; ++n) acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int n = 0; n < (SUM ? FB : 1); ++n) cs[n] = v4f{0.f, 0.f, 0.f, 0.f};
   }
   static __device__ __forceinline__ v8bf two(const char* p0, const char* p1) {
     return __builtin_shufflevector(tr_read4(p0), tr_read4(p1), 0, 1, 2, 3, 4, 5, 6, 7);
   }
-  __device__ __forceinline__ void add(const char* __restrict__ tG, const char* __restrict__ tA, int lane) {
-    v8bf hm[KB], mh[KB], lh[KB];
+  // The operands of one block, so that a caller can read them early and put
+  // the products where they overlap vector work.
+  struct Frags {
+    v8bf hm[KB], mh[KB], lh[KB], ghm[FB], ghl[FB];
+  };
+  static __device__ __forceinline__ void load(Frags& f, const char* __restrict__ tG, const char* __restrict__ tA,
+                                              int lane) {
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
       const char* p = tr_base<AW>(tA, kb, lane);
-      hm[kb] = two(p, p + AP);
-      mh[kb] = two(p + AP, p);
-      lh[kb] = two(p + 2 * AP, p);
+      f.hm[kb] = two(p, p + AP);
+      f.mh[kb] = two(p + AP, p);
+      f.lh[kb] = two(p + 2 * AP, p);
     }
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb) {
       const char* p = tr_base<GW>(tG, fb, lane);
-      const v8bf ghm = two(p, p + GP), ghl = two(p, p + 2 * GP);
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) acc[fb * KB + kb] = MP_MFMA_BF16(ghl, lh[kb], acc[fb * KB + kb]);
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) acc[fb * KB + kb] = MP_MFMA_BF16(ghm, mh[kb], acc[fb * KB + kb]);
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) acc[fb * KB + kb] = MP_MFMA_BF16(ghm, hm[kb], acc[fb * KB + kb]);
+      f.ghm[fb] = two(p, p + GP);
+      f.ghl[fb] = two(p, p + 2 * GP);
     }
   }
-  // Add the NW waves' sums in wave order and write sgn * them to dst, [GW][AW].
-  // Uses NW * GW * AW floats of `scratch`; contains barriers.
+  __device__ __forceinline__ void mma(const Frags& f) {
+    const uint32_t one2 = 0x3F803F80u;
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb) {
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) acc[fb * KB + kb] = MP_MFMA_BF16(f.ghl[fb], f.lh[kb], acc[fb * KB + kb]);
+      if constexpr (SUM) cs[fb] = MP_MFMA_BF16(f.ghl[fb], __builtin_bit_cast(v8bf, (v4u{0, 0, one2, one2})), cs[fb]);
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) acc[fb * KB + kb] = MP_MFMA_BF16(f.ghm[fb], f.mh[kb], acc[fb * KB + kb]);
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) acc[fb * KB + kb] = MP_MFMA_BF16(f.ghm[fb], f.hm[kb], acc[fb * KB + kb]);
+      if constexpr (SUM)
+        cs[fb] = MP_MFMA_BF16(f.ghm[fb], __builtin_bit_cast(v8bf, (v4u{one2, one2, one2, one2})), cs[fb]);
+    }
+  }
+  __device__ __forceinline__ void add(const char* __restrict__ tG, const char* __restrict__ tA, int lane) {
+    Frags f;
+    load(f, tG, tA, lane);
+    mma(f);
+  }
+  // Add the NW waves' sums in wave order and write sgn * them: dst [GW][AW],
+  // with SUM dst_cs [GW].  Uses NW * GW * AW floats of `scratch`; contains
+  // barriers.
   template <int NW>
-  __device__ __forceinline__ void store(float* __restrict__ scratch, float* __restrict__ dst, float sgn, int wave,
-                                        int lane) {
+  __device__ __forceinline__ void store(float* __restrict__ scratch, float* __restrict__ dst,
+                                        float* __restrict__ dst_cs, float sgn, int wave, int lane) {
     __syncthreads();
 #pragma unroll
     for (int n = 0; n < FB * KB; ++n) {
@@ -101,14 +126,30 @@ struct DwWave {
       dst[t] = sgn * sum;
     }
     __syncthreads();
+    if constexpr (SUM) {
+      if ((lane & 15) == 0) {
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) scratch[wave * GW + 16 * fb + 4 * (lane >> 4) + v] = cs[fb][v];
+        }
+      }
+      __syncthreads();
+      for (int t = threadIdx.x; t < GW; t += blockDim.x) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) sum += scratch[w * GW + t];
+        dst_cs[t] = sgn * sum;
+      }
+      __syncthreads();
+    }
   }
 };
 
 // Keep a wave's LDS stores ahead of its own reads of other lanes' data (LDS
 // operations of one wave complete in order).
 __device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  asm volatile("" ::: "memory");
 }
 
 // Indices of one edge per lane: receiver, sender, multiplicity, and the next

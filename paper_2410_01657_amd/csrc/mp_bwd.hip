@@ -513,7 +513,7 @@ template <int H>
 struct EdgeBwdF32Cfg {
   static constexpr int NW = 4;
   static constexpr size_t WB = wrow_bytes(H, H, false);
-  using Dw = DwWave<H, H>;
+  using Dw = DwWave<H, H, false>;
   static constexpr size_t WTILE = 2 * (Dw::TILE_G + Dw::TILE_A);  // (gm, u) and (gh, e) of one wave
   static constexpr size_t VECS = 2 * H * sizeof(float);
   static constexpr size_t CARRY = NW * H * sizeof(float);
@@ -692,8 +692,8 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
   }
   float* slab = a.part + blockIdx.x * a.slab;
   float* scratch = reinterpret_cast<float*>(smem);
-  d1.template store<NW>(scratch, slab, sgn, wave, lane);
-  d2.template store<NW>(scratch, slab + H * H, sgn, wave, lane);
+  d1.template store<NW>(scratch, slab, nullptr, sgn, wave, lane);
+  d2.template store<NW>(scratch, slab + H * H, nullptr, sgn, wave, lane);
 #pragma unroll
   for (int i = 0; i < NF; ++i) db2[i] *= sgn, dga[i] *= sgn, dbe[i] *= sgn;
   block_sum_vec<H, NW>(db2, scratch, slab + 2 * H * H, wave, lane);
@@ -1242,9 +1242,33 @@ struct GqCfg {
   // gradients are summed from g_P, g_Q and x by launch_row_dw.
   static constexpr bool SPLIT = gq_split(H, BF);
   static constexpr size_t STAGE = SPLIT ? 0 : tile_bytes<2 * H, BF, ROWS>() + tile_bytes<H, BF, ROWS>();
-  static constexpr bool LDS_FRAG = FB + STAGE <= kLdsLimit;
-  static constexpr size_t LDS = STAGE + (LDS_FRAG ? FB : 0);
+  static constexpr size_t LDS = STAGE + FB;
+  static_assert(LDS <= kLdsLimit, "fragments and tiles in LDS");
 };
+
+// [W1a | W1b]^T (H x 2H: element (k, c) is W1[c % H][k + H (c / H)]) as MFMA
+// fragments, from the FP32 matrix.  All threads; no barrier.
+template <int H, bool BF>
+__device__ __forceinline__ void stage_abt(void* __restrict__ dst, const WView& w) {
+  auto el = [&](int k, int c) { return w.p[(int64_t)(c % H) * w.ld + k + H * (c / H)]; };
+  if constexpr (BF) {
+    constexpr int T = 2 * H / 32;
+    for (int e = threadIdx.x; e < H * 2 * H / 8; e += blockDim.x) {
+      const int lane = e % 64, t = (e / 64) % T, mb = e / (64 * T);
+      v8bf v;
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        v[q] = (__bf16)el(16 * mb + lane % 16, 32 * t + 16 * (q / 4) + 4 * (lane / 16) + q % 4);
+      reinterpret_cast<uint4*>(dst)[e] = __builtin_bit_cast(uint4, v);
+    }
+  } else {
+    constexpr int S = 2 * H / 4;
+    for (int e = threadIdx.x; e < H * 2 * H; e += blockDim.x) {
+      const int lane = e % 64, s = (e / 64) % S, mb = e / (64 * S);
+      reinterpret_cast<float*>(dst)[e] = el(16 * mb + lane % 16, 16 * (s / 4) + 4 * (lane / 16) + s % 4);
+    }
+  }
+}
 
 // Per node j: g_Q[j] = sum of g_h over j's outgoing edges, read as the
 // reverse edges of j's incoming edges (in ascending order), then
@@ -1262,14 +1286,8 @@ __global__ __launch_bounds__((64 * GqCfg<H, BF>::NW), (GqCfg<H, BF>::MINB)) void
   extern __shared__ uint4 smem[];
   char* tG = reinterpret_cast<char*>(smem);
   char* tA = tG + (C::SPLIT ? 0 : tile_bytes<2 * H, BF, ROWS>());
-  const char* fr;
-  if constexpr (C::LDS_FRAG) {
-    uint4* fl = smem + C::STAGE / 16;
-    stage_frags(fl, a.frag_abt, C::FB);
-    fr = reinterpret_cast<const char*>(fl);
-  } else {
-    fr = reinterpret_cast<const char*>(a.frag_abt);
-  }
+  stage_abt<H, BF>(smem + C::STAGE / 16, a.w);
+  const char* fr = reinterpret_cast<const char*>(smem + C::STAGE / 16);
   __syncthreads();
   const DevGraph& gr = a.g;
   const int lane = lane_id(), j = lane & 15, g = lane >> 4, wave = threadIdx.x / 64;

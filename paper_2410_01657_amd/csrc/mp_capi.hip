@@ -193,18 +193,17 @@ int row_grid(int64_t N) { return (int)std::max<int64_t>(1, std::min<int64_t>(102
 int row_bwd_grid(int64_t N) { return (int)std::max<int64_t>(1, std::min<int64_t>(512, (N + 255) / 256)); }
 
 // Packed fragments of one layer, in this order:
-// W1a W1b | W1c W2 W2^T W1c^T | Wn1 Wn2 Wn2^T Wn1^T | [W1a|W1b]^T
+// W1a W1b | W1c W2 W2^T W1c^T | Wn1 Wn2 Wn2^T Wn1^T
 struct LayerFrags {
   size_t f1, f2;  // bytes of an H x H and an H x 2H matrix
-  size_t proj, edge, node, gq, total;
+  size_t proj, edge, node, total;
   LayerFrags(int H, bool bf) {
     f1 = frag_bytes(H, H, bf);
     f2 = frag_bytes(H, 2 * H, bf);
     proj = 0;
     edge = proj + 2 * f1;
     node = edge + 4 * f1;
-    gq = node + 2 * f2 + 2 * f1;
-    total = align_up(gq + f2);
+    total = align_up(node + 2 * f2 + 2 * f1);
   }
 };
 
@@ -280,19 +279,22 @@ PackJobs layer_jobs(const mp_layer_cfg* c, const mp_layer_params* p, const Layer
   PackJobs J;
   J.n = 0;
   J.bf = c->gemm_dtype == MP_BF16;
-  add_job(J, H, H, view(p->We1, 3 * H, 0, 0), F.proj);                     // W1a
-  add_job(J, H, H, view(p->We1, 3 * H, H, 0), F.proj + F.f1);              // W1b
-  add_job(J, H, H, view(p->We1, 3 * H, 2 * H, 0), F.edge);                 // W1c
-  add_job(J, H, H, view(p->We2, H, 0, 0), F.edge + F.f1);                  // W2
+  const bool raw = raw_weights(H, J.bf);  // the edge kernels stage these themselves
+  if (!raw) {
+    add_job(J, H, H, view(p->We1, 3 * H, 0, 0), F.proj);                     // W1a
+    add_job(J, H, H, view(p->We1, 3 * H, H, 0), F.proj + F.f1);              // W1b
+    add_job(J, H, H, view(p->We1, 3 * H, 2 * H, 0), F.edge);                 // W1c
+    add_job(J, H, H, view(p->We2, H, 0, 0), F.edge + F.f1);                  // W2
+  }
   add_job(J, H, 2 * H, view(p->Wn1, 2 * H, 0, 0), F.node);                 // Wn1
   add_job(J, H, H, view(p->Wn2, H, 0, 0), F.node + F.f2);                  // Wn2
   if (bwd) {
-    add_job(J, H, H, view(p->We2, H, 0, 1), F.edge + 2 * F.f1);            // W2^T
-    add_job(J, H, H, view(p->We1, 3 * H, 2 * H, 1), F.edge + 3 * F.f1);    // W1c^T
+    if (!raw) {
+      add_job(J, H, H, view(p->We2, H, 0, 1), F.edge + 2 * F.f1);          // W2^T
+      add_job(J, H, H, view(p->We1, 3 * H, 2 * H, 1), F.edge + 3 * F.f1);  // W1c^T
+    }
     add_job(J, H, H, view(p->Wn2, H, 0, 1), F.node + F.f2 + F.f1);         // Wn2^T
     add_job(J, 2 * H, H, view(p->Wn1, 2 * H, 0, 1), F.node + F.f2 + 2 * F.f1);  // Wn1^T
-    // [W1a | W1b]^T: element (k, c) = c < H ? We1[c][k] : We1[c-H][H+k]
-    add_job(J, H, 2 * H, view(p->We1, 3 * H, 0, 1), F.gq, view(p->We1, 3 * H, H, 1), H);
   }
   return J;
 }
@@ -759,7 +761,7 @@ extern "C" int mp_layer_backward(const mp_layer_cfg* cfg, const mp_layer_params*
   q.x = x_in;
   q.g_P = gP;
   q.g_h = gh;
-  q.frag_abt = ws_at(ws, W.fr.gq);
+  q.w = LW.w1a.w;
   q.g_x = g_x_in;
   q.part = wsf(ws, W.part_q);
   q.slab = gq_slab(H);
@@ -1049,6 +1051,53 @@ int deep_grad_sums(const char* name, const float* rec, int64_t n_rows, int rs, i
   return run("wreduce", s, [&] { return launch_wreduce(R, s); });
 }
 
+// Width 32 with few enough extra layers runs on the matrix unit.
+bool deep32(const mp_deep_layer_cfg* c) { return c->H == 32 && c->n_hidden <= kDeep32MaxHidden; }
+
+// Tiles of the deep forward, whose bounds sit in the caller's x_out until the
+// node update writes it (the forward has no workspace): as many as fit there.
+int64_t deep32_fwd_tiles(const mp_dev_graph* g) {
+  const int64_t fit = (g->n_rows * 32 - 8) / 2 - 1;
+  return std::max<int64_t>(1, std::min(n_tiles_for(g->n_edges, 0, 32, false, false), fit));
+}
+
+struct Deep32Ws {
+  size_t tile_r = 0, tile_e = 0, queue = 0, P = 0, Q = 0, ga = 0, gP = 0, gh = 0, partN = 0, partE = 0, partQ = 0,
+         total = 0;
+  int64_t n_tiles = 0, slabN = 0, slabE = 0;
+  int gr, gn, ge, gq, passes = 1;
+  Deep32Ws(const mp_deep_layer_cfg* c, const mp_dev_graph* g) {
+    const int ln = c->layernorm != 0;
+    const size_t N = g->n_rows, E = g->n_edges;
+    n_tiles = n_tiles_for(E, 0, 64, false, true);  // one wave per SIMD, as the FP32 adjoint at H = 64
+    slabN = deep_theta_floats(64, 32, c->n_hidden, 32, ln);
+    slabE = deep32_edge_slab(c->n_hidden, ln);
+    gr = row_grid(N);
+    gn = (int)std::min<int64_t>(256, std::max<int64_t>(1, ((int64_t)N + 63) / 64));
+    ge = (int)std::min<int64_t>(256, std::max<int64_t>(1, (n_tiles + 3) / 4));
+    // at least eight tiles per wave and pass: with fewer, uneven shares would cost more
+    passes = c->n_hidden && n_tiles >= 16 * 4 * ge ? 2 : 1;
+    gq = row_bwd_grid(N);
+    size_t o = 0;
+    auto take = [&](size_t& slot, size_t bytes) {
+      slot = o;
+      o = align_up(o + bytes);
+    };
+    take(tile_r, (size_t)(n_tiles + 1) * 4);
+    take(tile_e, (size_t)(n_tiles + 1) * 4);
+    take(queue, 8 * 4);
+    take(P, N * 32 * 4);
+    take(Q, N * 32 * 4);
+    take(ga, N * 32 * 4);
+    take(gP, N * 32 * 4);
+    take(gh, E * 32 * 4);
+    take(partN, (size_t)gn * slabN * 4);
+    take(partE, (size_t)ge * passes * slabE * 4);
+    take(partQ, (size_t)gq * gq_slab(32) * 4);
+    total = o;
+  }
+};
+
 struct DeepLayerWs {
   size_t recN = 0, recE = 0, ga = 0, gxn = 0, gxi = 0, gxj = 0, partN = 0, partE = 0, total = 0;
   int rsN = 0, rsE = 0;
@@ -1112,7 +1161,7 @@ extern "C" int mp_deep_layer_workspace_size(const mp_deep_layer_cfg* cfg, const 
   int rc;
   if ((rc = check_deep_layer_cfg(cfg)) || (rc = check_graph(g, false))) return rc;
   if (!bytes) return mp_fail(MP_EINVAL, "bytes is NULL");
-  *bytes = backward ? DeepLayerWs(cfg, g).total : 0;
+  *bytes = !backward ? 0 : deep32(cfg) ? Deep32Ws(cfg, g).total : DeepLayerWs(cfg, g).total;
   return MP_OK;
 }
 
@@ -1142,7 +1191,18 @@ extern "C" int mp_deep_layer_forward(const mp_deep_layer_cfg* cfg, const float* 
   ea.e_in = e_in;
   ea.e_out = e_out;
   ea.a_out = a_star_out;
-  if ((rc = run("deep_edge_fwd", s, [&] { return launch_deep_edge(ea, H, false, s); }))) return rc;
+  const bool d32 = deep32(cfg);
+  if (d32) {
+    int32_t* t = reinterpret_cast<int32_t*>(x_out);
+    ea.g.n_tiles = deep32_fwd_tiles(g);
+    ea.g.queue = t;
+    ea.g.tile_r = t + 8;
+    ea.g.tile_e = t + 8 + ea.g.n_tiles + 1;
+    if ((rc = run("tiles", s, [&] { return launch_tiles(tile_job(ea.g), s); }))) return rc;
+    if ((rc = run("deep_edge_fwd", s, [&] { return launch_deep32_edge_fwd(ea, s); }))) return rc;
+  } else if ((rc = run("deep_edge_fwd", s, [&] { return launch_deep_edge(ea, H, false, s); }))) {
+    return rc;
+  }
   if (cfg->halo && (rc = run("halo", s, [&] { return launch_halo(H, d, a_star_out, s); }))) return rc;
   DeepRowArgs na{};
   na.n_rows = g->n_rows;
@@ -1156,8 +1216,92 @@ extern "C" int mp_deep_layer_forward(const mp_deep_layer_cfg* cfg, const float* 
   na.src_b = x_in;
   na.resid = 1;
   na.out = x_out;
-  return run("deep_node_fwd", s, [&] { return launch_deep_row(na, H, DeepRowKind::kNode, false, s); });
+  return run("deep_node_fwd", s, [&] {
+    return d32 ? launch_deep32_node_fwd(na, s) : launch_deep_row(na, H, DeepRowKind::kNode, false, s);
+  });
 }
+
+namespace {
+
+// The adjoint of a width-32 layer on the matrix unit (arguments validated).
+int deep32_backward(const mp_deep_layer_cfg* cfg, const float* theta_edge, const float* theta_node,
+                    const mp_dev_graph* g, const float* x_in, const float* e_in, const float* a_star,
+                    const float* g_x_out, const float* g_e_out, float* g_x_in, float* g_e_in, float* g_theta_edge,
+                    float* g_theta_node, void* ws, const Deep32Ws& W, hipStream_t s) {
+  int rc;
+  const int NH = cfg->n_hidden, ln = cfg->layernorm != 0;
+  DevGraph d = dev_graph(g);
+  d.n_tiles = W.n_tiles;
+  d.tile_r = reinterpret_cast<const int32_t*>(ws_at(ws, W.tile_r));
+  d.tile_e = reinterpret_cast<const int32_t*>(ws_at(ws, W.tile_e));
+  d.queue = reinterpret_cast<int32_t*>(ws_at(ws, W.queue));
+  float *P = wsf(ws, W.P), *Q = wsf(ws, W.Q), *ga = wsf(ws, W.ga), *gP = wsf(ws, W.gP), *gh = wsf(ws, W.gh);
+  // the first edge Linear's node parts: W0 = [W0a | W0b | W0c], [32][96]
+  const WSrc wa{WView{theta_edge, 96, 0}, nullptr}, wb{WView{theta_edge + 32, 96, 0}, nullptr};
+  if ((rc = run("proj", s, [&] {
+         return launch_proj(32, false, g->n_rows, x_in, wa, wb, theta_edge + 32 * 96, P, Q, W.gr, tile_job(d), s);
+       })))
+    return rc;
+  Deep32NodeBwdArgs na{};
+  na.n_rows = g->n_rows;
+  na.theta = theta_node;
+  na.NH = NH;
+  na.ln = ln;
+  na.eps = cfg->ln_eps;
+  na.a_star = a_star;
+  na.x = x_in;
+  na.g_out = g_x_out;
+  na.g_a = ga;
+  na.g_x = g_x_in;
+  na.part = wsf(ws, W.partN);
+  na.slab = W.slabN;
+  if ((rc = run("deep_node_bwd", s, [&] { return launch_deep32_node_bwd(na, W.gn, s); }))) return rc;
+  if (cfg->halo && (rc = run("halo_adj", s, [&] { return launch_halo(32, d, ga, s); }))) return rc;
+  Deep32EdgeBwdArgs ea{};
+  ea.g = d;
+  ea.theta = theta_edge;
+  ea.NH = NH;
+  ea.ln = ln;
+  ea.am = cfg->aggregate != 0;
+  ea.eps = cfg->ln_eps;
+  ea.P = P;
+  ea.Q = Q;
+  ea.e_in = e_in;
+  ea.g_a = ga;
+  ea.g_e_out = g_e_out;
+  ea.g_e_in = g_e_in;
+  ea.g_h = gh;
+  ea.g_P = gP;
+  ea.part = wsf(ws, W.partE);
+  ea.slab = W.slabE;
+  ea.passes = W.passes;
+  if ((rc = run("deep_edge_bwd", s, [&] { return launch_deep32_edge_bwd(ea, W.ge, s); }))) return rc;
+  GqArgs q{};
+  q.g = d;
+  q.H = 32;
+  q.x = x_in;
+  q.g_P = gP;
+  q.g_h = gh;
+  q.w = wa.w;
+  q.g_x = g_x_in;
+  q.part = wsf(ws, W.partQ);
+  q.slab = gq_slab(32);
+  if ((rc = run("gq", s, [&] { return launch_gq(q, W.gq, s); }))) return rc;
+  ReduceSegs R;
+  R.n = 0;
+  auto seg = [&](const float* part, int n_slabs, int64_t slab, int64_t off, int rows, int cols, float* dst, int ld,
+                 int col0) { R.seg[R.n++] = ReduceSeg{part, n_slabs, slab, off, rows, cols, dst, ld, col0}; };
+  seg(na.part, W.gn, W.slabN, 0, 1, (int)W.slabN, g_theta_node, (int)W.slabN, 0);
+  seg(ea.part, W.ge * W.passes, W.slabE, 0, 32, 32, g_theta_edge, 96, 64);
+  const int rest = (int)(W.slabE - 32 * 32);
+  seg(ea.part, W.ge * W.passes, W.slabE, 32 * 32, 1, rest, g_theta_edge + 32 * 96 + 32, rest, 0);
+  seg(q.part, W.gq, q.slab, 0, 32, 32, g_theta_edge, 96, 0);
+  seg(q.part, W.gq, q.slab, 32 * 32, 32, 32, g_theta_edge, 96, 32);
+  seg(q.part, W.gq, q.slab, 2 * 32 * 32, 1, 32, g_theta_edge + 32 * 96, 32, 0);
+  return run("wreduce", s, [&] { return launch_wreduce(R, s); });
+}
+
+}  // namespace
 
 extern "C" int mp_deep_layer_backward(const mp_deep_layer_cfg* cfg, const float* theta_edge,
                                       const float* theta_node, const mp_dev_graph* g, const float* x_in,
@@ -1175,6 +1319,13 @@ extern "C" int mp_deep_layer_backward(const mp_deep_layer_cfg* cfg, const float*
   if (g_e_out && !aligned16(g_e_out)) return mp_fail(MP_EINVAL, "mp_deep_layer_backward: g_e_out not aligned");
   if (g_x_in == g_x_out || (const float*)g_e_in == g_e_out || g_x_in == x_in || g_e_in == e_in)
     return mp_fail(MP_EINVAL, "mp_deep_layer_backward: gradient outputs must not alias inputs");
+  if (deep32(cfg)) {
+    const Deep32Ws W(cfg, g);
+    if (ws_bytes < W.total)
+      return mp_fail(MP_ENOMEM, "mp_deep_layer_backward: workspace %zu < %zu bytes", ws_bytes, W.total);
+    return deep32_backward(cfg, theta_edge, theta_node, g, x_in, e_in, a_star, g_x_out, g_e_out, g_x_in, g_e_in,
+                           g_theta_edge, g_theta_node, ws, W, reinterpret_cast<hipStream_t>(stream));
+  }
   const DeepLayerWs W(cfg, g);
   if (ws_bytes < W.total)
     return mp_fail(MP_ENOMEM, "mp_deep_layer_backward: workspace %zu < %zu bytes", ws_bytes, W.total);

@@ -105,6 +105,15 @@ __device__ __forceinline__ void load_vec(const float* __restrict__ p, int g, flo
   load_row<W>(p, g, v);
 }
 
+// An opaque zero: adding it to an LDS offset inside a loop keeps the
+// compiler from hoisting every weight-fragment read out of the loop (which
+// would pin the whole matrix in registers and cut occupancy).
+__device__ __forceinline__ int opaque_zero() {
+  int z = 0;
+  asm volatile("" : "+v"(z));
+  return z;
+}
+
 // ------------------------------------------------------------- GEMMs
 
 // acc[f] += sum_k A[f][k] in[k]  (A packed as FP32 fragments; MB = M/16,
@@ -329,8 +338,11 @@ __device__ __forceinline__ void gemm_op(F&& wf, const Op<true, 32 * T>& in, floa
 template <int MB, int T, Acc MODE, class F>
 __device__ __forceinline__ void gemm_op(F&& wf, const Op<false, 32 * T>& in, float (&acc)[4 * MB]) {
   // two output blocks at a time: each weight part is read once, and no two
-  // consecutive matrix instructions add to the same registers
+  // consecutive matrix instructions add to the same registers.  With one chunk
+  // the large product comes last on the small ones' sum (one rounding at full
+  // size, no second accumulator).
   constexpr int G = MB % 2 == 0 ? 2 : 1;
+  constexpr bool ONE = T == 1;
 #pragma unroll
   for (int m0 = 0; m0 < MB; m0 += G) {
     v4f ch[G], cs[G];
@@ -357,17 +369,28 @@ __device__ __forceinline__ void gemm_op(F&& wf, const Op<false, 32 * T>& in, flo
       for (int i = 0; i < G; ++i) cs[i] = MP_MFMA_BF16(wh[i], in.l[t], cs[i]);
 #pragma unroll
       for (int i = 0; i < G; ++i) cs[i] = MP_MFMA_BF16(wm[i], in.h[t], cs[i]);
+      if constexpr (ONE) {
 #pragma unroll
-      for (int i = 0; i < G; ++i) ch[i] = MP_MFMA_BF16(wh[i], in.h[t], ch[i]);
+        for (int i = 0; i < G; ++i) cs[i] = MP_MFMA_BF16(wh[i], in.m[t], cs[i]);
 #pragma unroll
-      for (int i = 0; i < G; ++i) cs[i] = MP_MFMA_BF16(wh[i], in.m[t], cs[i]);
+        for (int i = 0; i < G; ++i) cs[i] = MP_MFMA_BF16(wh[i], in.h[t], cs[i]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < G; ++i) ch[i] = MP_MFMA_BF16(wh[i], in.h[t], ch[i]);
+#pragma unroll
+        for (int i = 0; i < G; ++i) cs[i] = MP_MFMA_BF16(wh[i], in.m[t], cs[i]);
+      }
     }
 #pragma unroll
     for (int i = 0; i < G; ++i) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        acc[4 * (m0 + i) + r] =
-            MODE == ACC_ADD ? acc[4 * (m0 + i) + r] + (ch[i][r] + cs[i][r]) : ch[i][r] + cs[i][r];
+      for (int r = 0; r < 4; ++r) {
+        float& o = acc[4 * (m0 + i) + r];
+        if constexpr (ONE)
+          o = MODE == ACC_SET ? cs[i][r] : o + cs[i][r];
+        else
+          o = MODE == ACC_ADD ? o + (ch[i][r] + cs[i][r]) : ch[i][r] + cs[i][r];
+      }
     }
   }
 }
@@ -378,6 +401,13 @@ struct WView {
   const float* p;
   int ld, trans;
 };
+// Four consecutive floats, 16-byte aligned (al) or not.
+__device__ __forceinline__ float4 load4w(const float* __restrict__ p, bool al) {
+  return al ? *reinterpret_cast<const float4*>(p) : make_float4(p[0], p[1], p[2], p[3]);
+}
+__device__ __forceinline__ bool w_aligned(const WView& w) {
+  return (reinterpret_cast<uintptr_t>(w.p) & 15) == 0 && (w.ld & 3) == 0;
+}
 
 // Weights in LDS as MFMA fragments: BF16 products one BF16 matrix, FP32
 // products its three parts one after the other.  Staged by the kernel itself
@@ -413,13 +443,14 @@ template <bool BF, int M, int K>
 __device__ __forceinline__ void stage_wfrag(void* __restrict__ dst, const WView& w) {
   constexpr int T = K / 32;
   uint4* d = reinterpret_cast<uint4*>(dst);
+  const bool al = w_aligned(w);
   for (int e = threadIdx.x; e < M * K / 8; e += blockDim.x) {
     const int lane = e % 64, t = (e / 64) % T, mb = e / (64 * T);
     const int row = 16 * mb + lane % 16, col = 32 * t + 4 * (lane / 16);
     float x[8];
     if (!w.trans) {
-      const float4 a = *reinterpret_cast<const float4*>(w.p + (int64_t)row * w.ld + col);
-      const float4 b = *reinterpret_cast<const float4*>(w.p + (int64_t)row * w.ld + col + 16);
+      const float4 a = load4w(w.p + (int64_t)row * w.ld + col, al);
+      const float4 b = load4w(w.p + (int64_t)row * w.ld + col + 16, al);
       x[0] = a.x, x[1] = a.y, x[2] = a.z, x[3] = a.w;
       x[4] = b.x, x[5] = b.y, x[6] = b.z, x[7] = b.w;
     } else {
@@ -534,10 +565,11 @@ __host__ __device__ constexpr size_t wrow_bytes(int M, int K, bool bf) { return 
 // barrier.
 template <bool BF, int M, int K>
 __device__ __forceinline__ void stage_wrow(void* __restrict__ dst, const WView& w) {
+  const bool al = w_aligned(w);
   for (int e = threadIdx.x; e < M * K / 8; e += blockDim.x) {
     const int row = e / (K / 8), c = e % (K / 8) * 2;  // chunks c, c + 1
-    const float4 a = *reinterpret_cast<const float4*>(w.p + (int64_t)row * w.ld + 4 * c);
-    const float4 b = *reinterpret_cast<const float4*>(w.p + (int64_t)row * w.ld + 4 * c + 4);
+    const float4 a = load4w(w.p + (int64_t)row * w.ld + 4 * c, al);
+    const float4 b = load4w(w.p + (int64_t)row * w.ld + 4 * c + 4, al);
     const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
     v8bf p[3];
     split_w8<BF>(x, p[0], p[1], p[2]);
@@ -551,45 +583,73 @@ __device__ __forceinline__ void stage_wrow(void* __restrict__ dst, const WView& 
     }
   }
 }
+// One operand fragment of W (chunk t of K, output block mb of M) and of W^T
+// (chunk t of M, output block mb of K).
+template <int M, int K>
+__device__ __forceinline__ v8bf wn_frag(const char* __restrict__ w, int t, int mb, int part, int lane) {
+  const int i = lane & 15, g = lane >> 4, sz = stg_swz<K>(i);
+  const char* q = w + i * (K * 2) + part * wrow_part(M, K) + wrow_at(16 * mb, K);
+  const v4bf lo = __builtin_bit_cast(v4bf, *reinterpret_cast<const u32x2*>(q + ((8 * t + g) ^ sz) * 8));
+  const v4bf hi = __builtin_bit_cast(v4bf, *reinterpret_cast<const u32x2*>(q + ((8 * t + 4 + g) ^ sz) * 8));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+template <int M, int K>
+__device__ __forceinline__ v8bf wt_frag(const char* __restrict__ w, int t, int mb, int part, int lane) {
+  const char* q = tr_base<K>(w + part * wrow_part(M, K), mb, lane);
+  const v4bf lo = tr_read4(q + wrow_at(32 * t, K)), hi = tr_read4(q + wrow_at(32 * t + 16, K));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
 // acc += W in (ACC_SET: acc = W in)
 template <bool BF, int M, int K, Acc MODE = ACC_START>
 __device__ __forceinline__ void gemm_wn(const char* __restrict__ w, const Op<BF, K>& in, float (&acc)[M / 4],
                                         int lane) {
-  const int i = lane & 15, g = lane >> 4, sz = stg_swz<K>(i);
-  const char* p = w + i * (K * 2);
+  // at K = 32 neighbouring row groups are within a paired read's reach: hide
+  // that they share a base
+  const char* w1 = w + (K == 32 ? opaque_zero() : 0);
   gemm_op<M / 16, K / 32, MODE>(
-      [&](int t, int mb, int part) {
-        const char* q = p + part * wrow_part(M, K) + wrow_at(16 * mb, K);
-        const v4bf lo = __builtin_bit_cast(v4bf, *reinterpret_cast<const u32x2*>(q + ((8 * t + g) ^ sz) * 8));
-        const v4bf hi = __builtin_bit_cast(v4bf, *reinterpret_cast<const u32x2*>(q + ((8 * t + 4 + g) ^ sz) * 8));
-        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      },
-      in, acc);
+      [&](int t, int mb, int part) { return wn_frag<M, K>(mb % 2 ? w1 : w, t, mb, part, lane); }, in, acc);
 }
 // acc += W^T in (ACC_SET: acc = W^T in)
 template <bool BF, int M, int K, Acc MODE = ACC_START>
 __device__ __forceinline__ void gemm_wt(const char* __restrict__ w, const Op<BF, M>& in, float (&acc)[K / 4],
                                         int lane) {
-  gemm_op<K / 16, M / 32, MODE>(
-      [&](int t, int mb, int part) {
-        const char* q = tr_base<K>(w + part * wrow_part(M, K), mb, lane);
-        const v4bf lo = tr_read4(q + wrow_at(32 * t, K)), hi = tr_read4(q + wrow_at(32 * t + 16, K));
-        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      },
-      in, acc);
+  gemm_op<K / 16, M / 32, MODE>([&](int t, int mb, int part) { return wt_frag<M, K>(w, t, mb, part, lane); }, in,
+                                acc);
 }
+
+// All fragments of a small FP32 matrix, read ahead of the product.
+template <int T, int MB>
+struct WFrags {
+  v8bf f[T][MB][3];
+  template <int M, int K>
+  __device__ __forceinline__ void load_n(const char* __restrict__ w, int lane) {
+    static_assert(T == K / 32 && MB == M / 16, "plain product");
+    const char* w1 = w + (K == 32 ? opaque_zero() : 0);
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) f[t][mb][p] = wn_frag<M, K>(mb % 2 ? w1 : w, t, mb, p, lane);
+  }
+  template <int M, int K>
+  __device__ __forceinline__ void load_t(const char* __restrict__ w, int lane) {
+    static_assert(T == M / 32 && MB == K / 16, "transposed product");
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) f[t][mb][p] = wt_frag<M, K>(w, t, mb, p, lane);
+  }
+  template <Acc MODE>
+  __device__ __forceinline__ void gemm(const Op<false, 32 * T>& in, float (&acc)[4 * MB]) const {
+    gemm_op<MB, T, MODE>([&](int t, int mb, int part) { return f[t][mb][part]; }, in, acc);
+  }
+};
 
 // Bytes of the packed fragments of an M x K matrix.
 __host__ __device__ constexpr size_t frag_bytes(int M, int K, bool bf) { return size_t(M) * K * (bf ? 2 : 4); }
-
-// An opaque zero: adding it to an LDS offset inside a loop keeps the
-// compiler from hoisting every weight-fragment read out of the loop (which
-// would pin the whole matrix in registers and cut occupancy).
-__device__ __forceinline__ int opaque_zero() {
-  int z = 0;
-  asm volatile("" : "+v"(z));
-  return z;
-}
 
 // --------------------------------------------------- elementwise helpers
 

@@ -236,7 +236,7 @@ struct GqArgs {
   const float* x;
   const float* g_P;
   const void* g_h;       // [E][H], FP32 or (BF16 path) BF16
-  const void* frag_abt;  // [W1a | W1b]^T as an H x 2H matrix
+  WView w;               // [W1a | W1b | ...], H rows: the first Linear's matrix
   float* g_x;            // accumulated: g_x += W1a^T g_P + W1b^T g_Q
   float* part;
   int64_t slab;
@@ -301,6 +301,48 @@ struct DeepEdgeArgs {
 hipError_t launch_deep_edge(const DeepEdgeArgs& a, int H, bool bwd, hipStream_t s);
 hipError_t launch_deep_gather(int H, const DevGraph& g, const float* gxn, const float* gxi, const float* gxj,
                               float* gx, hipStream_t s);
+
+// Width 32 with up to kDeep32MaxHidden extra layers on the matrix unit.  The
+// forward takes DeepEdgeArgs / DeepRowArgs (with the graph's tile bounds); the
+// adjoint splits W0's node parts off (P = W0a x + b0, Q = W0b x given, their
+// adjoint left to launch_gq).
+constexpr int kDeep32MaxHidden = 5;
+struct Deep32EdgeBwdArgs {
+  DevGraph g;
+  const float* theta;
+  int NH, ln, am;
+  float eps;
+  const float* P;
+  const float* Q;
+  const float* e_in;
+  const float* g_a;
+  const float* g_e_out;  // may be null
+  float* g_e_in;
+  float* g_h;            // [E][32] gradient of the first pre-activation
+  float* g_P;            // [N][32] its sum over each row's incoming edges
+  float* part;           // one slab of deep32_edge_slab floats per workgroup and pass
+  int64_t slab;
+  int passes;            // width 32: parts of a workgroup's tiles, summed apart
+};
+struct Deep32NodeBwdArgs {
+  int64_t n_rows;
+  const float* theta;
+  int NH, ln;
+  float eps;
+  const float* a_star;
+  const float* x;
+  const float* g_out;
+  float* g_a;
+  float* g_x;            // includes g_out (the residual path)
+  float* part;           // one slab in the flat parameter layout per workgroup
+  int64_t slab;
+};
+// [dW0's edge part 32 x 32][hidden W, b pairs][last W, b][gain, shift]
+constexpr int64_t deep32_edge_slab(int NH, int ln) { return 32 * 32 + (NH + 1) * (32 * 32 + 32) + (ln ? 64 : 0); }
+hipError_t launch_deep32_edge_fwd(const DeepEdgeArgs& a, hipStream_t s);
+hipError_t launch_deep32_node_fwd(const DeepRowArgs& a, hipStream_t s);
+hipError_t launch_deep32_edge_bwd(const Deep32EdgeBwdArgs& a, int grid, hipStream_t s);
+hipError_t launch_deep32_node_bwd(const Deep32NodeBwdArgs& a, int grid, hipStream_t s);
 
 // Per-row records of rs columns are stored in blocks of kRecRows rows,
 // column by column inside a block: column c of row r is at
