@@ -1061,39 +1061,54 @@ int64_t deep32_fwd_tiles(const mp_dev_graph* g) {
   return std::max<int64_t>(1, std::min(n_tiles_for(g->n_edges, 0, 32, false, false), fit));
 }
 
-struct Deep32Ws {
+// Width 8 has its own adjoint kernels (mp_deep8.hip).
+bool deep8(const mp_deep_layer_cfg* c) { return c->H == 8 && c->n_hidden <= kDeep8MaxHidden; }
+
+struct DeepSplitWs {
   size_t tile_r = 0, tile_e = 0, queue = 0, P = 0, Q = 0, ga = 0, gP = 0, gh = 0, partN = 0, partE = 0, partQ = 0,
          total = 0;
-  int64_t n_tiles = 0, slabN = 0, slabE = 0;
-  int gr, gn, ge, gq, passes = 1;
-  Deep32Ws(const mp_deep_layer_cfg* c, const mp_dev_graph* g) {
-    const int ln = c->layernorm != 0;
+  int64_t n_tiles = 0, slabN = 0, slabE = 0, slabQ = 0;
+  int gr = 0, gn, ge, gq, passes = 1;
+  DeepSplitWs(const mp_deep_layer_cfg* c, const mp_dev_graph* g) {
+    const int ln = c->layernorm != 0, H = c->H;
     const size_t N = g->n_rows, E = g->n_edges;
-    n_tiles = n_tiles_for(E, 0, 64, false, true);  // one wave per SIMD, as the FP32 adjoint at H = 64
-    slabN = deep_theta_floats(64, 32, c->n_hidden, 32, ln);
-    slabE = deep32_edge_slab(c->n_hidden, ln);
-    gr = row_grid(N);
-    gn = (int)std::min<int64_t>(256, std::max<int64_t>(1, ((int64_t)N + 63) / 64));
-    ge = (int)std::min<int64_t>(256, std::max<int64_t>(1, (n_tiles + 3) / 4));
-    // at least eight tiles per wave and pass: with fewer, uneven shares would cost more
-    passes = c->n_hidden && n_tiles >= 16 * 4 * ge ? 2 : 1;
-    gq = row_bwd_grid(N);
+    slabN = deep_theta_floats(2 * H, H, c->n_hidden, H, ln);
+    slabE = deep_edge_slab(H, c->n_hidden, ln);
+    slabQ = 2 * H * H + H;
+    auto grid = [](int64_t most, int64_t n, int64_t per) {
+      return (int)std::min<int64_t>(most, std::max<int64_t>(1, (n + per - 1) / per));
+    };
+    if (H == 8) {  // four waves of 128 (edge) or 64 rows per workgroup
+      gn = grid(512, N, 256);
+      ge = grid(512, E, 512);
+      gq = grid(1024, N, 256);
+    } else {
+      n_tiles = n_tiles_for(E, 0, 64, false, true);  // one wave per SIMD, as the FP32 adjoint at H = 64
+      gr = row_grid(N);
+      gn = grid(256, N, 64);
+      ge = grid(256, n_tiles, 4);
+      // eight tiles per wave and pass: less, and uneven shares would cost more than the sums gain
+      passes = c->n_hidden && n_tiles >= 16 * 4 * ge ? 2 : 1;
+      gq = row_bwd_grid(N);
+    }
     size_t o = 0;
     auto take = [&](size_t& slot, size_t bytes) {
       slot = o;
       o = align_up(o + bytes);
     };
-    take(tile_r, (size_t)(n_tiles + 1) * 4);
-    take(tile_e, (size_t)(n_tiles + 1) * 4);
-    take(queue, 8 * 4);
-    take(P, N * 32 * 4);
-    take(Q, N * 32 * 4);
-    take(ga, N * 32 * 4);
-    take(gP, N * 32 * 4);
-    take(gh, E * 32 * 4);
+    if (H == 32) {
+      take(tile_r, (size_t)(n_tiles + 1) * 4);
+      take(tile_e, (size_t)(n_tiles + 1) * 4);
+      take(queue, 8 * 4);
+      take(gP, N * H * 4);
+    }
+    take(P, N * H * 4);
+    take(Q, N * H * 4);
+    take(ga, N * H * 4);
+    take(gh, E * H * 4);
     take(partN, (size_t)gn * slabN * 4);
     take(partE, (size_t)ge * passes * slabE * 4);
-    take(partQ, (size_t)gq * gq_slab(32) * 4);
+    take(partQ, (size_t)gq * slabQ * 4);
     total = o;
   }
 };
@@ -1161,7 +1176,7 @@ extern "C" int mp_deep_layer_workspace_size(const mp_deep_layer_cfg* cfg, const 
   int rc;
   if ((rc = check_deep_layer_cfg(cfg)) || (rc = check_graph(g, false))) return rc;
   if (!bytes) return mp_fail(MP_EINVAL, "bytes is NULL");
-  *bytes = !backward ? 0 : deep32(cfg) ? Deep32Ws(cfg, g).total : DeepLayerWs(cfg, g).total;
+  *bytes = !backward ? 0 : deep32(cfg) || deep8(cfg) ? DeepSplitWs(cfg, g).total : DeepLayerWs(cfg, g).total;
   return MP_OK;
 }
 
@@ -1223,26 +1238,30 @@ extern "C" int mp_deep_layer_forward(const mp_deep_layer_cfg* cfg, const float* 
 
 namespace {
 
-// The adjoint of a width-32 layer on the matrix unit (arguments validated).
-int deep32_backward(const mp_deep_layer_cfg* cfg, const float* theta_edge, const float* theta_node,
-                    const mp_dev_graph* g, const float* x_in, const float* e_in, const float* a_star,
-                    const float* g_x_out, const float* g_e_out, float* g_x_in, float* g_e_in, float* g_theta_edge,
-                    float* g_theta_node, void* ws, const Deep32Ws& W, hipStream_t s) {
+// The adjoint with W0's node parts split off, width 8 or 32 (arguments validated).
+int deep_split_backward(const mp_deep_layer_cfg* cfg, const float* theta_edge, const float* theta_node,
+                        const mp_dev_graph* g, const float* x_in, const float* e_in, const float* a_star,
+                        const float* g_x_out, const float* g_e_out, float* g_x_in, float* g_e_in,
+                        float* g_theta_edge, float* g_theta_node, void* ws, const DeepSplitWs& W, hipStream_t s) {
   int rc;
-  const int NH = cfg->n_hidden, ln = cfg->layernorm != 0;
+  const int H = cfg->H, NH = cfg->n_hidden, ln = cfg->layernorm != 0;
+  const bool d8 = H == 8;
   DevGraph d = dev_graph(g);
-  d.n_tiles = W.n_tiles;
-  d.tile_r = reinterpret_cast<const int32_t*>(ws_at(ws, W.tile_r));
-  d.tile_e = reinterpret_cast<const int32_t*>(ws_at(ws, W.tile_e));
-  d.queue = reinterpret_cast<int32_t*>(ws_at(ws, W.queue));
-  float *P = wsf(ws, W.P), *Q = wsf(ws, W.Q), *ga = wsf(ws, W.ga), *gP = wsf(ws, W.gP), *gh = wsf(ws, W.gh);
-  // the first edge Linear's node parts: W0 = [W0a | W0b | W0c], [32][96]
-  const WSrc wa{WView{theta_edge, 96, 0}, nullptr}, wb{WView{theta_edge + 32, 96, 0}, nullptr};
+  float *P = wsf(ws, W.P), *Q = wsf(ws, W.Q), *ga = wsf(ws, W.ga), *gh = wsf(ws, W.gh);
+  // the first edge Linear's node parts: W0 = [W0a | W0b | W0c], [H][3 H]
+  const WSrc wa{WView{theta_edge, 3 * H, 0}, nullptr}, wb{WView{theta_edge + H, 3 * H, 0}, nullptr};
+  if (!d8) {
+    d.n_tiles = W.n_tiles;
+    d.tile_r = reinterpret_cast<const int32_t*>(ws_at(ws, W.tile_r));
+    d.tile_e = reinterpret_cast<const int32_t*>(ws_at(ws, W.tile_e));
+    d.queue = reinterpret_cast<int32_t*>(ws_at(ws, W.queue));
+  }
   if ((rc = run("proj", s, [&] {
-         return launch_proj(32, false, g->n_rows, x_in, wa, wb, theta_edge + 32 * 96, P, Q, W.gr, tile_job(d), s);
+         return d8 ? launch_deep8_proj(g->n_rows, x_in, theta_edge, P, Q, s)
+                   : launch_proj(32, false, g->n_rows, x_in, wa, wb, theta_edge + 32 * 96, P, Q, W.gr, tile_job(d), s);
        })))
     return rc;
-  Deep32NodeBwdArgs na{};
+  DeepSplitNodeArgs na{};
   na.n_rows = g->n_rows;
   na.theta = theta_node;
   na.NH = NH;
@@ -1255,9 +1274,12 @@ int deep32_backward(const mp_deep_layer_cfg* cfg, const float* theta_edge, const
   na.g_x = g_x_in;
   na.part = wsf(ws, W.partN);
   na.slab = W.slabN;
-  if ((rc = run("deep_node_bwd", s, [&] { return launch_deep32_node_bwd(na, W.gn, s); }))) return rc;
-  if (cfg->halo && (rc = run("halo_adj", s, [&] { return launch_halo(32, d, ga, s); }))) return rc;
-  Deep32EdgeBwdArgs ea{};
+  if ((rc = run("deep_node_bwd", s, [&] {
+         return d8 ? launch_deep8_node_bwd(na, W.gn, s) : launch_deep32_node_bwd(na, W.gn, s);
+       })))
+    return rc;
+  if (cfg->halo && (rc = run("halo_adj", s, [&] { return launch_halo(H, d, ga, s); }))) return rc;
+  DeepSplitEdgeArgs ea{};
   ea.g = d;
   ea.theta = theta_edge;
   ea.NH = NH;
@@ -1271,33 +1293,43 @@ int deep32_backward(const mp_deep_layer_cfg* cfg, const float* theta_edge, const
   ea.g_e_out = g_e_out;
   ea.g_e_in = g_e_in;
   ea.g_h = gh;
-  ea.g_P = gP;
+  ea.g_P = wsf(ws, W.gP);
   ea.part = wsf(ws, W.partE);
   ea.slab = W.slabE;
   ea.passes = W.passes;
-  if ((rc = run("deep_edge_bwd", s, [&] { return launch_deep32_edge_bwd(ea, W.ge, s); }))) return rc;
-  GqArgs q{};
-  q.g = d;
-  q.H = 32;
-  q.x = x_in;
-  q.g_P = gP;
-  q.g_h = gh;
-  q.w = wa.w;
-  q.g_x = g_x_in;
-  q.part = wsf(ws, W.partQ);
-  q.slab = gq_slab(32);
-  if ((rc = run("gq", s, [&] { return launch_gq(q, W.gq, s); }))) return rc;
+  if ((rc = run("deep_edge_bwd", s, [&] {
+         return d8 ? launch_deep8_edge_bwd(ea, W.ge, s) : launch_deep32_edge_bwd(ea, W.ge, s);
+       })))
+    return rc;
+  float* partQ = wsf(ws, W.partQ);
+  if (d8) {
+    const Deep8GqArgs q{d, theta_edge, x_in, gh, g_x_in, partQ, W.slabQ};
+    rc = run("gq", s, [&] { return launch_deep8_gq(q, W.gq, s); });
+  } else {
+    GqArgs q{};
+    q.g = d;
+    q.H = 32;
+    q.x = x_in;
+    q.g_P = ea.g_P;
+    q.g_h = gh;
+    q.w = wa.w;
+    q.g_x = g_x_in;
+    q.part = partQ;
+    q.slab = W.slabQ;
+    rc = run("gq", s, [&] { return launch_gq(q, W.gq, s); });
+  }
+  if (rc) return rc;
   ReduceSegs R;
   R.n = 0;
   auto seg = [&](const float* part, int n_slabs, int64_t slab, int64_t off, int rows, int cols, float* dst, int ld,
                  int col0) { R.seg[R.n++] = ReduceSeg{part, n_slabs, slab, off, rows, cols, dst, ld, col0}; };
+  const int HH = H * H, rest = (int)(W.slabE - HH);
   seg(na.part, W.gn, W.slabN, 0, 1, (int)W.slabN, g_theta_node, (int)W.slabN, 0);
-  seg(ea.part, W.ge * W.passes, W.slabE, 0, 32, 32, g_theta_edge, 96, 64);
-  const int rest = (int)(W.slabE - 32 * 32);
-  seg(ea.part, W.ge * W.passes, W.slabE, 32 * 32, 1, rest, g_theta_edge + 32 * 96 + 32, rest, 0);
-  seg(q.part, W.gq, q.slab, 0, 32, 32, g_theta_edge, 96, 0);
-  seg(q.part, W.gq, q.slab, 32 * 32, 32, 32, g_theta_edge, 96, 32);
-  seg(q.part, W.gq, q.slab, 2 * 32 * 32, 1, 32, g_theta_edge + 32 * 96, 32, 0);
+  seg(ea.part, W.ge * W.passes, W.slabE, 0, H, H, g_theta_edge, 3 * H, 2 * H);
+  seg(ea.part, W.ge * W.passes, W.slabE, HH, 1, rest, g_theta_edge + 3 * HH + H, rest, 0);
+  seg(partQ, W.gq, W.slabQ, 0, H, H, g_theta_edge, 3 * H, 0);
+  seg(partQ, W.gq, W.slabQ, HH, H, H, g_theta_edge, 3 * H, H);
+  seg(partQ, W.gq, W.slabQ, 2 * HH, 1, H, g_theta_edge + 3 * HH, H, 0);
   return run("wreduce", s, [&] { return launch_wreduce(R, s); });
 }
 
@@ -1319,12 +1351,12 @@ extern "C" int mp_deep_layer_backward(const mp_deep_layer_cfg* cfg, const float*
   if (g_e_out && !aligned16(g_e_out)) return mp_fail(MP_EINVAL, "mp_deep_layer_backward: g_e_out not aligned");
   if (g_x_in == g_x_out || (const float*)g_e_in == g_e_out || g_x_in == x_in || g_e_in == e_in)
     return mp_fail(MP_EINVAL, "mp_deep_layer_backward: gradient outputs must not alias inputs");
-  if (deep32(cfg)) {
-    const Deep32Ws W(cfg, g);
+  if (deep32(cfg) || deep8(cfg)) {
+    const DeepSplitWs W(cfg, g);
     if (ws_bytes < W.total)
       return mp_fail(MP_ENOMEM, "mp_deep_layer_backward: workspace %zu < %zu bytes", ws_bytes, W.total);
-    return deep32_backward(cfg, theta_edge, theta_node, g, x_in, e_in, a_star, g_x_out, g_e_out, g_x_in, g_e_in,
-                           g_theta_edge, g_theta_node, ws, W, reinterpret_cast<hipStream_t>(stream));
+    return deep_split_backward(cfg, theta_edge, theta_node, g, x_in, e_in, a_star, g_x_out, g_e_out, g_x_in,
+                               g_e_in, g_theta_edge, g_theta_node, ws, W, reinterpret_cast<hipStream_t>(stream));
   }
   const DeepLayerWs W(cfg, g);
   if (ws_bytes < W.total)

@@ -353,7 +353,7 @@ struct Bwd32 {
 // in a.passes parts, each its own slab (2M edges, NH = 5, gradient error
 // against FP64: 9.0e-7 in one part, 7.0e-7 in two; FP32 instructions 8.9e-7).
 template <int NH>
-__global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) void k_deep32_edge_bwd(Deep32EdgeBwdArgs a) {
+__global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) void k_deep32_edge_bwd(DeepSplitEdgeArgs a) {
   using B = Bwd32<NH, 32>;
   extern __shared__ uint4 smem[];
   const int lane = lane_id(), j = lane & 15, g = lane >> 4, wave = threadIdx.x / 64;
@@ -457,7 +457,7 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) voi
 // Adjoint of the node update: g_a (gradient at a*) and g_x = g_out + the MLP's
 // part, and all its weight gradients.
 template <int NH>
-__global__ __launch_bounds__((64 * Bwd32<NH, 64>::NW), (Bwd32<NH, 64>::OCC)) void k_deep32_node_bwd(Deep32NodeBwdArgs a) {
+__global__ __launch_bounds__((64 * Bwd32<NH, 64>::NW), (Bwd32<NH, 64>::OCC)) void k_deep32_node_bwd(DeepSplitNodeArgs a) {
   using B = Bwd32<NH, 64>;
   extern __shared__ uint4 smem[];
   const int lane = lane_id(), j = lane & 15, g = lane >> 4, wave = threadIdx.x / 64;
@@ -530,7 +530,7 @@ hipError_t node_fwd(const DeepRowArgs& a, int64_t waves, hipStream_t s) {
   return hipGetLastError();
 }
 template <int NH>
-hipError_t edge_bwd(const Deep32EdgeBwdArgs& a, int grid, hipStream_t s) {
+hipError_t edge_bwd(const DeepSplitEdgeArgs& a, int grid, hipStream_t s) {
   using B = Bwd32<NH, 32>;
   auto kern = k_deep32_edge_bwd<NH>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)B::LDS);
@@ -538,7 +538,7 @@ hipError_t edge_bwd(const Deep32EdgeBwdArgs& a, int grid, hipStream_t s) {
   return hipGetLastError();
 }
 template <int NH>
-hipError_t node_bwd(const Deep32NodeBwdArgs& a, int grid, hipStream_t s) {
+hipError_t node_bwd(const DeepSplitNodeArgs& a, int grid, hipStream_t s) {
   using B = Bwd32<NH, 64>;
   auto kern = k_deep32_node_bwd<NH>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)B::LDS);
@@ -573,7 +573,7 @@ hipError_t launch_deep32_node_fwd(const DeepRowArgs& a, hipStream_t s) {
   }
   return hipErrorInvalidValue;
 }
-hipError_t launch_deep32_edge_bwd(const Deep32EdgeBwdArgs& a, int grid, hipStream_t s) {
+hipError_t launch_deep32_edge_bwd(const DeepSplitEdgeArgs& a, int grid, hipStream_t s) {
   switch (a.NH) {
     case 0: return edge_bwd<0>(a, grid, s);
     case 1: return edge_bwd<1>(a, grid, s);
@@ -584,7 +584,7 @@ hipError_t launch_deep32_edge_bwd(const Deep32EdgeBwdArgs& a, int grid, hipStrea
   }
   return hipErrorInvalidValue;
 }
-hipError_t launch_deep32_node_bwd(const Deep32NodeBwdArgs& a, int grid, hipStream_t s) {
+hipError_t launch_deep32_node_bwd(const DeepSplitNodeArgs& a, int grid, hipStream_t s) {
   switch (a.NH) {
     case 0: return node_bwd<0>(a, grid, s);
     case 1: return node_bwd<1>(a, grid, s);

@@ -302,12 +302,14 @@ hipError_t launch_deep_edge(const DeepEdgeArgs& a, int H, bool bwd, hipStream_t 
 hipError_t launch_deep_gather(int H, const DevGraph& g, const float* gxn, const float* gxi, const float* gxj,
                               float* gx, hipStream_t s);
 
-// Width 32 with up to kDeep32MaxHidden extra layers on the matrix unit.  The
-// forward takes DeepEdgeArgs / DeepRowArgs (with the graph's tile bounds); the
-// adjoint splits W0's node parts off (P = W0a x + b0, Q = W0b x given, their
-// adjoint left to launch_gq).
+// Width 32 with up to kDeep32MaxHidden extra layers on the matrix unit, and the
+// adjoint of width 8 with up to kDeep8MaxHidden.  The width-32 forward takes
+// DeepEdgeArgs / DeepRowArgs (with the graph's tile bounds); the adjoints split
+// W0's node parts off (P = W0a x + b0, Q = W0b x given, their adjoint left to
+// launch_gq and launch_deep8_gq).
 constexpr int kDeep32MaxHidden = 5;
-struct Deep32EdgeBwdArgs {
+constexpr int kDeep8MaxHidden = 5;
+struct DeepSplitEdgeArgs {
   DevGraph g;
   const float* theta;
   int NH, ln, am;
@@ -318,13 +320,13 @@ struct Deep32EdgeBwdArgs {
   const float* g_a;
   const float* g_e_out;  // may be null
   float* g_e_in;
-  float* g_h;            // [E][32] gradient of the first pre-activation
-  float* g_P;            // [N][32] its sum over each row's incoming edges
-  float* part;           // one slab of deep32_edge_slab floats per workgroup and pass
+  float* g_h;            // [E][H] gradient of the first pre-activation
+  float* g_P;            // [N][32] its sum over each row's incoming edges (width 32)
+  float* part;           // one slab of deep_edge_slab floats per workgroup and pass
   int64_t slab;
   int passes;            // width 32: parts of a workgroup's tiles, summed apart
 };
-struct Deep32NodeBwdArgs {
+struct DeepSplitNodeArgs {
   int64_t n_rows;
   const float* theta;
   int NH, ln;
@@ -337,12 +339,25 @@ struct Deep32NodeBwdArgs {
   float* part;           // one slab in the flat parameter layout per workgroup
   int64_t slab;
 };
-// [dW0's edge part 32 x 32][hidden W, b pairs][last W, b][gain, shift]
-constexpr int64_t deep32_edge_slab(int NH, int ln) { return 32 * 32 + (NH + 1) * (32 * 32 + 32) + (ln ? 64 : 0); }
+// [dW0's edge part H x H][hidden W, b pairs][last W, b][gain, shift]
+constexpr int64_t deep_edge_slab(int H, int NH, int ln) { return H * H + (NH + 1) * (H * H + H) + (ln ? 2 * H : 0); }
 hipError_t launch_deep32_edge_fwd(const DeepEdgeArgs& a, hipStream_t s);
 hipError_t launch_deep32_node_fwd(const DeepRowArgs& a, hipStream_t s);
-hipError_t launch_deep32_edge_bwd(const Deep32EdgeBwdArgs& a, int grid, hipStream_t s);
-hipError_t launch_deep32_node_bwd(const Deep32NodeBwdArgs& a, int grid, hipStream_t s);
+hipError_t launch_deep32_edge_bwd(const DeepSplitEdgeArgs& a, int grid, hipStream_t s);
+hipError_t launch_deep32_node_bwd(const DeepSplitNodeArgs& a, int grid, hipStream_t s);
+struct Deep8GqArgs {
+  DevGraph g;
+  const float* theta;
+  const float* x;
+  const float* g_h;  // [E][8]
+  float* g_x;        // [N][8], added to
+  float* part;       // [dW0a 8 x 8][dW0b 8 x 8][db0] per workgroup
+  int64_t slab;
+};
+hipError_t launch_deep8_proj(int64_t n, const float* x, const float* theta, float* P, float* Q, hipStream_t s);
+hipError_t launch_deep8_edge_bwd(const DeepSplitEdgeArgs& a, int grid, hipStream_t s);
+hipError_t launch_deep8_node_bwd(const DeepSplitNodeArgs& a, int grid, hipStream_t s);
+hipError_t launch_deep8_gq(const Deep8GqArgs& a, int grid, hipStream_t s);
 
 // Per-row records of rs columns are stored in blocks of kRecRows rows,
 // column by column inside a block: column c of row r is at
