@@ -1061,7 +1061,7 @@ int64_t deep32_fwd_tiles(const mp_dev_graph* g) {
   return std::max<int64_t>(1, std::min(n_tiles_for(g->n_edges, 0, 32, false, false), fit));
 }
 
-// Width 8 has its own adjoint kernels (mp_deep8.hip).
+// Width 8 has its own edge and adjoint kernels (mp_deep8.hip).
 bool deep8(const mp_deep_layer_cfg* c) { return c->H == 8 && c->n_hidden <= kDeep8MaxHidden; }
 
 struct DeepSplitWs {
@@ -1078,10 +1078,10 @@ struct DeepSplitWs {
     auto grid = [](int64_t most, int64_t n, int64_t per) {
       return (int)std::min<int64_t>(most, std::max<int64_t>(1, (n + per - 1) / per));
     };
-    if (H == 8) {  // four waves of 128 (edge) or 64 rows per workgroup
+    if (H == 8) {  // four waves of 128 (edge), 64 (node) or 32 rows (sender side) per workgroup
       gn = grid(512, N, 256);
       ge = grid(512, E, 512);
-      gq = grid(1024, N, 256);
+      gq = grid(1024, N, 128);
     } else {
       n_tiles = n_tiles_for(E, 0, 64, false, true);  // one wave per SIMD, as the FP32 adjoint at H = 64
       gr = row_grid(N);
@@ -1215,7 +1215,9 @@ extern "C" int mp_deep_layer_forward(const mp_deep_layer_cfg* cfg, const float* 
     ea.g.tile_e = t + 8 + ea.g.n_tiles + 1;
     if ((rc = run("tiles", s, [&] { return launch_tiles(tile_job(ea.g), s); }))) return rc;
     if ((rc = run("deep_edge_fwd", s, [&] { return launch_deep32_edge_fwd(ea, s); }))) return rc;
-  } else if ((rc = run("deep_edge_fwd", s, [&] { return launch_deep_edge(ea, H, false, s); }))) {
+  } else if ((rc = run("deep_edge_fwd", s, [&] {
+                return deep8(cfg) ? launch_deep8_edge_fwd(ea, s) : launch_deep_edge(ea, H, false, s);
+              }))) {
     return rc;
   }
   if (cfg->halo && (rc = run("halo", s, [&] { return launch_halo(H, d, a_star_out, s); }))) return rc;

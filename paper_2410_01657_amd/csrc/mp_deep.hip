@@ -1,8 +1,8 @@
 // Narrow deep MLPs: the paper's own models (Table I: hidden width 8 or 32,
 // two or five extra H -> H layers in every MLP), for the consistent layer
-// (Eq. 4a-e), the encoders and the decoder.  Layers of width 32 with up to five
-// extra layers (mp_deep32.hip) and the adjoint of those of width 8
-// (mp_deep8.hip) have kernels of their own.
+// (Eq. 4a-e), the encoders and the decoder.  Layers with up to five extra layers
+// have kernels of their own at width 32 (mp_deep32.hip) and, but for the node
+// update, at width 8 (mp_deep8.hip).
 //
 // At these widths a 16 x 16 matrix-core tile is mostly padding (H = 8) and
 // the products are small, so one thread owns one row (a node, or a

@@ -1,5 +1,6 @@
-// Adjoint of the deep layers of hidden width 8 (Table I's small model: two
-// extra H -> H layers in every MLP), for up to kDeep8MaxHidden extra layers.
+// Deep layers of hidden width 8 (Table I's small model: two extra H -> H layers
+// in every MLP): the edge update and the adjoint, for up to kDeep8MaxHidden extra
+// layers.
 //
 // At this width a matrix-unit tile is mostly padding for the MLP itself, so a
 // thread runs whole rows with FP32 FMAs on weights broadcast from LDS, two rows
@@ -96,15 +97,16 @@ __device__ __forceinline__ void put_cols(float* __restrict__ st, int b, const fl
 #pragma unroll
   for (int c = 0; c < kH; ++c) st[(8 * b + c) * kCS + lane] = v[c];
 }
-// acc += (blocks 0, 1)^T (blocks 2, 3) over the 64 staged rows: rows 0..7 x
+// acc += (blocks 0, 1)^T (blocks 2, 3) over the ROWS staged rows: rows 0..7 x
 // columns 0..7 hold block 0 against block 2, rows 8..15 x columns 8..15 block 1
 // against block 3 (the rest is not used).  bs, if given, gains the sums of
 // column lane % 16 of blocks 0, 1 over this lane's rows.
+template <int ROWS = 64>
 __device__ __forceinline__ void outer_tile(const float* __restrict__ st, v4f& acc, float* bs, int lane) {
   const float* g = st + (lane & 15) * kCS + 4 * (lane >> 4);
   const float* a = g + 16 * kCS;
 #pragma unroll
-  for (int r = 0; r < 64; r += 16) {
+  for (int r = 0; r < ROWS; r += 16) {
     const float4 gv = *reinterpret_cast<const float4*>(g + r), av = *reinterpret_cast<const float4*>(a + r);
     acc = __builtin_amdgcn_mfma_f32_16x16x4f32(gv.x, av.x, acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_16x16x4f32(gv.y, av.y, acc, 0, 0, 0);
@@ -327,6 +329,113 @@ struct Bwd8 {
   }
 };
 
+// Two MLP forwards at once, up to the last Linear's output, in z.
+template <int NH>
+__device__ __forceinline__ void fwd8_tail(const float* __restrict__ L, float (&z)[2][kH]) {
+#pragma unroll
+  for (int l = 0; l <= NH; ++l) {
+    const float* Wl = L + l * (int)kHid;
+    float h[2][kH];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+#pragma unroll
+      for (int c = 0; c < kH; ++c) h[q][c] = elu(z[q][c]);
+      load_vec8<kH>(Wl + kH * kH, z[q]);
+    }
+    lin2<kH, kH, 2>(Wl, h, z);
+  }
+}
+// LayerNorm of one row, in place.
+__device__ __forceinline__ void ln8(const float* __restrict__ gain, float eps, float (&z)[kH]) {
+  float s = 0.f, v = 0.f, ga[kH], be[kH];
+  load_vec8<kH>(gain, ga);
+  load_vec8<kH>(gain + kH, be);
+#pragma unroll
+  for (int c = 0; c < kH; ++c) s += z[c];
+  const float mean = s * (1.f / kH);
+#pragma unroll
+  for (int c = 0; c < kH; ++c) v += (z[c] - mean) * (z[c] - mean);
+  const float rstd = 1.f / sqrtf(v * (1.f / kH) + eps);
+#pragma unroll
+  for (int c = 0; c < kH; ++c) z[c] = (z[c] - mean) * rstd * ga[c] + be[c];
+}
+
+// Edge update and aggregation: a thread walks one receiver's incoming edges
+// two at a time, so that a broadcast weight feeds both.  W0 is split as in the
+// adjoint: W0a x_i + b0 once per receiver, [W0b | W0c] [x_j, e] per edge.  The
+// next pair's rows load while this one is computed.  6.3M edges: 0.26 ms with one
+// edge per thread, 0.20 ms here; three waves per SIMD spill and take 0.28.
+template <int NH>
+__global__ __launch_bounds__(256, 2) void k_deep8_edge_fwd(DeepEdgeArgs a) {
+  constexpr int W1 = kH * 16, GAIN = W1 + (NH + 1) * (int)kHid, W0A = GAIN + 2 * kH, B0 = W0A + kH * kH;
+  __shared__ float4 par[(B0 + kH) / 4];
+  float* L = reinterpret_cast<float*>(par);
+  for (int t = threadIdx.x; t < kH * 16; t += blockDim.x) L[t] = a.theta[t / 16 * 24 + kH + t % 16];
+  for (int t = threadIdx.x; t < kH * kH; t += blockDim.x) L[W0A + t] = a.theta[t / kH * 24 + t % kH];
+  for (int t = threadIdx.x; t < kH; t += blockDim.x) L[B0 + t] = a.theta[off_b0(24) + t];
+  for (int t = threadIdx.x; t < (NH + 1) * kHid; t += blockDim.x) L[W1 + t] = a.theta[off_hid(24, 0) + t];
+  if (a.ln)
+    for (int t = threadIdx.x; t < 2 * kH; t += blockDim.x) L[GAIN + t] = a.theta[off_hid(24, NH + 1) + t];
+  __syncthreads();
+  // XCD-aware numbering: each XCD's L2 sees a compact window of receivers
+  const int64_t i = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+  if (i >= a.g.n_rows) return;
+  const int k0 = a.g.rowptr[i], k1 = a.g.rowptr[i + 1];
+  float p[1][kH], acc[kH], nx[2][kH], ne[2][kH];
+  int nd[2];
+  auto load = [&](int k) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int kk = std::min(k + q, k1 - 1);
+      const int j = a.g.col[kk];
+      nd[q] = a.g.mult[kk];
+      load_vec8<kH>(a.e_in + (int64_t)kk * kH, ne[q]);
+      load_vec8<kH>(a.x + (int64_t)j * kH, nx[q]);
+    }
+  };
+  if (k0 < k1) load(k0);
+  {
+    float x[1][kH];
+    load_vec8<kH>(a.x + i * kH, x[0]);
+    load_vec8<kH>(L + B0, p[0]);
+    lin2<kH, kH, 1>(L + W0A, x, p);
+#pragma unroll
+    for (int c = 0; c < kH; ++c) acc[c] = 0.f;
+  }
+  for (int k = k0; k < k1; k += 2) {
+    float in[2][16], z[2][kH];
+    int d[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      d[q] = nd[q];
+#pragma unroll
+      for (int c = 0; c < kH; ++c) {
+        in[q][c] = nx[q][c];
+        in[q][kH + c] = ne[q][c];
+        z[q][c] = p[0][c];
+      }
+    }
+    if (k + 2 < k1) load(k + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    lin2<16, 16, 2>(L, in, z);
+    fwd8_tail<NH>(L + W1, z);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (k + q >= k1) continue;
+      if (a.ln) ln8(L + GAIN, a.eps, z[q]);
+      const float inv_d = 1.f / (float)d[q];
+#pragma unroll
+      for (int c = 0; c < kH; ++c) {
+        const float msg = z[q][c];
+        z[q][c] += in[q][kH + c];                     // residual edge update (Eq. 4a)
+        acc[c] += (a.am ? msg : z[q][c]) * inv_d;     // Eq. 4b (or the message variant)
+      }
+      store_vec8<kH>(a.e_out + (int64_t)(k + q) * kH, z[q]);
+    }
+  }
+  store_vec8<kH>(a.a_out + i * kH, acc);
+}
+
 // P = W0a x + b0, Q = W0b x: one node per thread.
 __global__ __launch_bounds__(256) void k_deep8_proj(int64_t n, const float* __restrict__ x,
                                                     const float* __restrict__ theta, float* __restrict__ P,
@@ -482,69 +591,85 @@ __global__ __launch_bounds__(64 * kWav, 2) void k_deep8_node_bwd(DeepSplitNodeAr
 // Per node: g_P = sum of g_h over its incoming edges, g_Q over the reverses of
 // them (its outgoing edges), in CSR order; g_x += W0a^T g_P + W0b^T g_Q;
 // dW0a = sum g_P x^T, dW0b = sum g_Q x^T, db0 = sum g_P.  Bound by the two
-// passes over g_h.  Slab: [dW0a][dW0b][db0].
-__global__ __launch_bounds__(64 * kWav, 3) void k_deep8_gq(Deep8GqArgs a) {
+// passes over g_h; two lanes share a node, half a row each, so that neighbouring
+// lanes read one 32-byte row and six edges' rows fit in flight (6.3M edges: 163 us
+// with one lane per node, 114 so).  Slab: [dW0a][dW0b][db0].
+__global__ __launch_bounds__(64 * kWav, 4) void k_deep8_gq(Deep8GqArgs a) {
   __shared__ float4 par[32];
   __shared__ float4 stage[kWav * kStage / 4];
   float* L = reinterpret_cast<float*>(par);
   for (int t = threadIdx.x; t < 128; t += blockDim.x) L[t] = a.theta[(t % 64 / 8) * 24 + (t / 64) * 8 + t % 8];
   __syncthreads();
-  const int lane = lane_id(), wave = threadIdx.x / 64;
+  const int lane = lane_id(), wave = threadIdx.x / 64, hf = lane & 1;
   float* st = reinterpret_cast<float*>(stage) + wave * kStage;
+  float* mine = st + 4 * hf * kCS + lane / 2;
   const DevGraph& gr = a.g;
   const int64_t n = gr.n_rows;
+  constexpr int CH = 6;
   v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
   float b0 = 0.f;
-  const Chunks ch(n, 64, wave);
+  const Chunks ch(n, 32, wave);
   for (int64_t c = ch.c0; c < ch.c1; c += ch.step) {
-    const int64_t r = c * 64 + lane, rr = std::min(r, n - 1);
+    const int64_t r = c * 32 + lane / 2, rr = std::min(r, n - 1);
     const bool valid = r < n;
-    float gp[kH], gq[kH], x[kH], gx[kH];
     const int k0 = gr.rowptr[rr], k1 = valid ? gr.rowptr[rr + 1] : k0;
-    load_vec8<kH>(a.x + rr * kH, x);
-    load_vec8<kH>(a.g_x + rr * kH, gx);
+    const float* gh = a.g_h + 4 * hf;
+    float v[3][4], gx[4];  // g_P, g_Q, x
+    load_vec8<4>(a.x + rr * kH + 4 * hf, v[2]);
+    load_vec8<4>(a.g_x + rr * kH + 4 * hf, gx);
 #pragma unroll
-    for (int i = 0; i < kH; ++i) gp[i] = gq[i] = 0.f;
-    // three edges at a time: their reverse indices first, then all their rows
-    for (int kb = k0; kb < k1; kb += 3) {
-      int rv[3];
+    for (int i = 0; i < 4; ++i) v[0][i] = v[1][i] = 0.f;
+    // six edges at a time: their reverse indices first, then all their rows
+    for (int kb = k0; kb < k1; kb += CH) {
+      int rv[CH];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) rv[q] = kb + q < k1 ? gr.rev[kb + q] : 0;
-      float ti[3][kH], tj[3][kH];
+      for (int q = 0; q < CH; ++q) rv[q] = gr.rev[std::min(kb + q, k1 - 1)];
+      float ti[CH][4], tj[CH][4];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        if (kb + q < k1) {
-          load_vec8<kH>(a.g_h + (int64_t)(kb + q) * kH, ti[q]);
-          load_vec8<kH>(a.g_h + (int64_t)rv[q] * kH, tj[q]);
-        }
+      for (int q = 0; q < CH; ++q) {
+        load_vec8<4>(gh + (int64_t)std::min(kb + q, k1 - 1) * kH, ti[q]);
+        load_vec8<4>(gh + (int64_t)rv[q] * kH, tj[q]);
       }
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
+      for (int q = 0; q < CH; ++q) {
         if (kb + q < k1) {
 #pragma unroll
-          for (int i = 0; i < kH; ++i) {
-            gp[i] += ti[q][i];
-            gq[i] += tj[q][i];
+          for (int i = 0; i < 4; ++i) {
+            v[0][i] += ti[q][i];
+            v[1][i] += tj[q][i];
           }
         }
       }
     }
     wave_lds_fence();
-    put_cols(st, 0, gp, lane);
-    put_cols(st, 1, gq, lane);
-    put_cols(st, 2, x, lane);
-    put_cols(st, 3, x, lane);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mine[(8 * b + i) * kCS] = v[b < 2 ? b : 2][i];
+    }
     wave_lds_fence();
-    outer_tile(st, acc, &b0, lane);
+    outer_tile<32>(st, acc, &b0, lane);
 #pragma unroll
-    for (int o = 0; o < kH; ++o) {
+    for (int b = 0; b < 2; ++b) {
+      // the whole row: lane l and its neighbour's half (quad_perm 1, 0, 3, 2)
+      float g[kH];
 #pragma unroll
-      for (int i = 0; i < kH; ++i) {
-        gx[i] = fmaf(L[o * 8 + i], gp[o], gx[i]);
-        gx[i] = fmaf(L[64 + o * 8 + i], gq[o], gx[i]);
+      for (int i = 0; i < 4; ++i) {
+        const float o = __builtin_bit_cast(
+            float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v[b][i]), 0xB1, 0xF, 0xF, true));
+        g[i] = hf ? o : v[b][i];
+        g[4 + i] = hf ? v[b][i] : o;
+      }
+      const float* W = L + 64 * b + 4 * hf;
+#pragma unroll
+      for (int o = 0; o < kH; ++o) {
+        float w[4];
+        load_vec8<4>(W + o * kH, w);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) gx[i] = fmaf(w[i], g[o], gx[i]);
       }
     }
-    if (valid) store_vec8<kH>(a.g_x + r * kH, gx);
+    if (valid) store_vec8<4>(a.g_x + r * kH + 4 * hf, gx);
   }
   float* slab = a.part + blockIdx.x * a.slab;
   float* scratch = reinterpret_cast<float*>(stage);
@@ -558,6 +683,17 @@ __global__ __launch_bounds__(64 * kWav, 3) void k_deep8_gq(Deep8GqArgs a) {
 hipError_t launch_deep8_proj(int64_t n, const float* x, const float* theta, float* P, float* Q, hipStream_t s) {
   hipLaunchKernelGGL(k_deep8_proj, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, x, theta, P, Q);
   return hipGetLastError();
+}
+hipError_t launch_deep8_edge_fwd(const DeepEdgeArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)((a.g.n_rows + 255) / 256));
+#define MP_CASE(NN)                                                          \
+  if (a.NH == NN) {                                                          \
+    hipLaunchKernelGGL(k_deep8_edge_fwd<NN>, grid, dim3(256), 0, s, a);      \
+    return hipGetLastError();                                                \
+  }
+  MP_CASE(0) MP_CASE(1) MP_CASE(2) MP_CASE(3) MP_CASE(4) MP_CASE(5)
+#undef MP_CASE
+  return hipErrorInvalidValue;
 }
 hipError_t launch_deep8_edge_bwd(const DeepSplitEdgeArgs& a, int grid, hipStream_t s) {
 #define MP_CASE(NN)                                                                       \

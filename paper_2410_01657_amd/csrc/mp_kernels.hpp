@@ -302,8 +302,8 @@ hipError_t launch_deep_edge(const DeepEdgeArgs& a, int H, bool bwd, hipStream_t 
 hipError_t launch_deep_gather(int H, const DevGraph& g, const float* gxn, const float* gxi, const float* gxj,
                               float* gx, hipStream_t s);
 
-// Width 32 with up to kDeep32MaxHidden extra layers on the matrix unit, and the
-// adjoint of width 8 with up to kDeep8MaxHidden.  The width-32 forward takes
+// Width 32 with up to kDeep32MaxHidden extra layers on the matrix unit, and width
+// 8 with up to kDeep8MaxHidden (edge update and adjoint).  The width-32 forward takes
 // DeepEdgeArgs / DeepRowArgs (with the graph's tile bounds); the adjoints split
 // W0's node parts off (P = W0a x + b0, Q = W0b x given, their adjoint left to
 // launch_gq and launch_deep8_gq).
@@ -355,6 +355,7 @@ struct Deep8GqArgs {
   int64_t slab;
 };
 hipError_t launch_deep8_proj(int64_t n, const float* x, const float* theta, float* P, float* Q, hipStream_t s);
+hipError_t launch_deep8_edge_fwd(const DeepEdgeArgs& a, hipStream_t s);
 hipError_t launch_deep8_edge_bwd(const DeepSplitEdgeArgs& a, int grid, hipStream_t s);
 hipError_t launch_deep8_node_bwd(const DeepSplitNodeArgs& a, int grid, hipStream_t s);
 hipError_t launch_deep8_gq(const Deep8GqArgs& a, int grid, hipStream_t s);
