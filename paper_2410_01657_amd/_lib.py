@@ -151,4 +151,5 @@ def check(fn, rc):
 
 
 def call(fn, *args):
-    return check(fn, getattr(lib(), fn)(*args))
+    rc = getattr(_lib or lib(), fn)(*args)
+    return rc if rc == MP_OK else check(fn, rc)
