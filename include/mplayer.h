@@ -211,8 +211,9 @@ typedef struct {
    * choice are bitwise reproducible, and equal up to the grouping of the
    * weight-gradient sums): waves per workgroup of the edge adjoint (4, or
    * 8 for BF16 GEMMs at H <= 64, which stage 16 x waves edges per
-   * weight-gradient round, and at H > 64, whose split adjoint then runs
-   * two waves per SIMD instead of one; FP32 at H <= 64 has one form), and
+   * weight-gradient round, and for FP32 at H > 64, whose split adjoint then
+   * runs two waves per SIMD instead of one; FP32 at H <= 64 and BF16 at
+   * H > 64 have one form), and
    * the tile order of the edge forward (0: a
    * fixed round robin over each XCD's range of tiles; 1: waves take the
    * next tile of their XCD's range from an atomic counter and move on to

@@ -5,8 +5,9 @@ schedule sets, in mp_layer_cfg: edges per tile (tile_edges), the workgroup
 counts of the forward and adjoint edge kernels (edge_grid, edge_bwd_grid),
 the waves per workgroup of the edge adjoint (edge_bwd_waves: 4, or 8 for
 BF16 GEMMs at H <= 64, i.e. 64 or 128 edges staged per weight-gradient
-round, and at H > 64, where 8 puts two waves of the split adjoint on each
-SIMD and 4 gives one wave all the registers it wants) and the tile order
+round, and for FP32 at H > 64, where 8 puts two waves of the split adjoint on
+each SIMD and 4 gives one wave all the registers it wants; BF16 at H > 64
+accepts both and has one form) and the tile order
 of the edge forward (edge_fwd_queue: fixed round robin, or per-XCD atomic
 tile counters).  The tuner times the library's own
 forward and backward on the actual graph and keeps the fastest, cached per
@@ -17,8 +18,7 @@ computes the same function; they differ only in the grouping of
 floating-point sums (and the forward's tile order not even in that).
 
 Not searched: 32 x 32 matrix-core tiles (every kernel's row-block layout is
-built on 16 x 16 products; the BF16 path is not bound by its products, and
-the FP32 products already issue back to back); the unsplit first edge
+built on 16 x 16 products, and no path is bound by its products alone); the unsplit first edge
 Linear (twice the flops for the same bytes, never faster).  BF16 storage of
 the edge states (estate="bf16") is not a schedule: it changes the stored
 precision, not just the grouping of sums, so tuned_schedule takes it from
@@ -42,7 +42,7 @@ SCHEDULE_FIELDS = ("tile_edges", "edge_grid", "edge_bwd_grid", "edge_bwd_waves",
 
 def edge_bwd_waves_options(H, gemm):
     """Waves per workgroup of the edge adjoint the library accepts (the
-    fused kernel: 8 only with BF16 GEMMs; the split one at H > 64: both)."""
+    fused kernel: 8 only with BF16 GEMMs; at H > 64 both)."""
     return (4, 8) if (gemm == "bf16" and H <= 64) or H > 64 else (4,)
 
 

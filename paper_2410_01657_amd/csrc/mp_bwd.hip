@@ -243,6 +243,32 @@ __device__ __forceinline__ void block_sum_scattered(float v, float* __restrict__
   __syncthreads();
 }
 
+// Two vectors reduced across each 16-lane group by sum16_scatter, added over the
+// waves in wave order: lane j of group g holds value indices q = j * NS + c of
+// the row-block layout, i.e. feature 16 (q / 4) + 4 g + q % 4.  Uses
+// NW * 64 * 2 * NS floats of LDS; contains barriers.
+template <int W, int NW>
+__device__ __forceinline__ void store_scattered2(const float (&v0)[W / 64], const float (&v1)[W / 64],
+                                                 float* __restrict__ red, float* __restrict__ dst0,
+                                                 float* __restrict__ dst1, int wave, int lane) {
+  constexpr int NS = W / 64;
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < NS; ++c) {
+    red[((wave * 64 + lane) * 2 + 0) * NS + c] = v0[c];
+    red[((wave * 64 + lane) * 2 + 1) * NS + c] = v1[c];
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < 2 * W; t += blockDim.x) {
+    const int v = t / W, f = t % W;
+    const int q = 4 * (f / 16) + f % 4, gg = (f % 16) / 4;
+    const int l = q / NS + 16 * gg, c = q % NS;
+    float sum = 0.f;
+    for (int w = 0; w < NW; ++w) sum += red[((w * 64 + l) * 2 + v) * NS + c];
+    (v == 0 ? dst0 : dst1)[f] = sum;
+  }
+}
+
 __device__ __forceinline__ void stage_frags(uint4* __restrict__ dst, const void* __restrict__ src, size_t bytes) {
   const uint4* s = reinterpret_cast<const uint4*>(src);
   for (size_t i = threadIdx.x; i < bytes / 16; i += blockDim.x) dst[i] = s[i];
@@ -722,43 +748,239 @@ static hipError_t launch_edge_bwd_h(const EdgeBwdArgs& a, int grid, hipStream_t 
   return hipGetLastError();
 }
 
+// ------------------------------------------------ edge adjoint, BF16, H = 128
+
+template <int H>
+struct EdgeBwdWideCfg {
+  static constexpr int NW = 4, ROWS = 16 * NW;
+  static constexpr size_t TB = tile_bytes<H, true, ROWS>();
+  static constexpr size_t STAGE = 4 * TB;
+  static constexpr size_t WB = wrow_bytes(H, H, true);
+  static constexpr size_t VECS = 2 * H * sizeof(float);    // b2 and the LayerNorm gain
+  static constexpr size_t CARRY = NW * H * sizeof(float);  // per-wave open-row sums between blocks
+  static constexpr int NS = H / 64;  // LayerNorm-parameter sums per lane after sum16_scatter
+  static constexpr size_t LDS = STAGE + 2 * WB + CARRY + VECS;
+  static_assert(LDS <= kLdsLimit, "weights and tiles in LDS");
+  static_assert(NW * 64 * 2 * NS * sizeof(float) <= STAGE, "sums of the waves in the tiles' place");
+};
+
+// k_edge_bwd at H = 128.  What made room for the weight gradients beside the
+// adjoint: one row-major copy of each weight serves both products (66 KB; four
+// fragment sets take 128), the LayerNorm-parameter sums stay in registers, and
+// four waves have 512 registers each (128 of them dW1c and dW2).  Bound by
+// memory: one pass over e, g_e', g_e and g_h (the kernel that left the weight
+// gradients to a later pass also wrote gm and u, 3.2 GB of 15.8 at 6.2M edges,
+// and that pass read 7.9).  A block's next e, P and Q rows load while the
+// weight gradients of this one are formed.  6.2M edges, adjoint and weight
+// gradients: 5.74 ms in the two kernels, 5.20 here (12.6 GB, 2.7 ms at the copy
+// rate: one wave per SIMD leaves its vector work and its waits in a row).  Eight
+// waves, four for the adjoint and four for the sums, spill and take 6.1.
+template <int H, bool AM, bool ES>
+__global__ __launch_bounds__(256, 1) void k_edge_bwd_wide(EdgeBwdArgs a) {
+  using C = EdgeBwdWideCfg<H>;
+  constexpr int NF = H / 4, NW = C::NW, ROWS = C::ROWS, NT = dw_tiles_per_wave<H, H, NW>(), NS = C::NS;
+  extern __shared__ uint4 smem[];
+  char* tG2 = reinterpret_cast<char*>(smem);
+  char* tA2 = tG2 + C::TB;
+  char* tG1 = tA2 + C::TB;
+  char* tA1 = tG1 + C::TB;
+  char* wl = tA1 + C::TB;
+  float* vecs = reinterpret_cast<float*>(wl + 2 * C::WB + C::CARRY);
+  float* carry = reinterpret_cast<float*>(wl + 2 * C::WB) + (threadIdx.x / 64) * H + (threadIdx.x / 16 % 4) * (H / 4);
+  stage_wrow<true, H, H>(wl, a.w1c.w);
+  stage_wrow<true, H, H>(wl + C::WB, a.w2.w);
+  for (int t = threadIdx.x; t < 2 * H; t += blockDim.x) vecs[t] = t < H ? a.b2[t] : (a.ln ? a.lng[t - H] : 0.f);
+  __syncthreads();
+
+  const DevGraph& gr = a.g;
+  const int lane = lane_id(), j = lane & 15, g0 = lane >> 4, wave = threadIdx.x / 64;
+  const int srow = wave * 16 + j;
+  const TileSched ts = tile_sched(gr.n_tiles);
+  v4f acc2[NT], acc1[NT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n) acc2[n] = acc1[n] = v4f{0.f, 0.f, 0.f, 0.f};
+  ColSum<H, NW> cs_b2;
+  cs_b2.zero();
+  float sbe[NS], sga[NS];  // this lane's share of dbeta, dgamma
+#pragma unroll
+  for (int c = 0; c < NS; ++c) sbe[c] = sga[c] = 0.f;
+
+  // groups of NW consecutive tiles, one per wave, processed in lock step
+  EdgeTile<NW> tl;
+  float ev[NF], u[NF], q[NF];
+  for (int64_t tg = ts.t0 + ts.rank * NW; tg < ts.t1; tg += ts.nr * NW) {
+    tl.open(gr, ts, tg, wave, lane);
+    int carry_key = 0;  // no open row at the start of a tile
+    auto load = [&](int64_t k, int g) {
+      load_row_t<H, ES>(a.e_in, k < tl.e1 ? k : tl.e_last, g, ev);
+      load_row<H>(a.P + (int64_t)tl.ix.ri * H, g, u);
+      load_row<H>(a.Q + (int64_t)tl.ix.sj * H, g, q);
+    };
+    load(tl.e0 + j, g0);
+    for (int64_t it = 0; it < tl.n_iter; ++it) {
+      // the weights are read again each block, and the lane's offsets formed
+      // anew: held over the loop they would cost every array's base
+      const int ln = lane + opaque_zero(), g = ln >> 4;
+      const char* w1c = wl + opaque_zero();
+      const char* w2 = w1c + C::WB;
+      const int64_t k = tl.e0 + it * 16 + j;
+      const bool valid = k < tl.e1;
+      const int64_t kk = valid ? k : tl.e_last;
+      const int ri = tl.ix.ri;
+      const float inv_d = 1.f / (float)tl.ix.md;
+      const bool last = valid && tl.ix.nx != ri;
+      const int key = valid ? ri + 1 : -1;
+      float gE[NF], go[NF], t[NF];
+      load_row<H>(a.g_a + (int64_t)ri * H, g, gE);
+      if (a.g_e_out) {
+        load_row_t<H, ES>(a.g_e_out, kk, g, go);
+      } else {
+#pragma unroll
+        for (int i = 0; i < NF; ++i) go[i] = 0.f;
+      }
+      tl.ix.fetch(gr, k + 16, tl.e1, tl.e_last);
+      __builtin_amdgcn_sched_barrier(0);
+
+      // recompute the forward
+#pragma unroll
+      for (int i = 0; i < NF; ++i) u[i] += q[i];
+      Op<true, H> o;
+      make_op(ev, o);
+      stage_row<H, true, ROWS>(tA1, srow, g, ev);
+      gemm_wn<true, H, H>(w1c, o, u, ln);
+#pragma unroll
+      for (int i = 0; i < NF; ++i) u[i] = elu(u[i]);
+      float mp[NF];
+      const float* vb = vecs + opaque_zero();
+      load_vec<H>(vb, g, mp);
+      make_op(u, o);
+      stage_row<H, true, ROWS>(tA2, srow, g, u);
+      gemm_wn<true, H, H>(w2, o, mp, ln);
+
+      // gradient reaching e', LayerNorm adjoint (mp becomes gm)
+#pragma unroll
+      for (int i = 0; i < NF; ++i) {
+        const float v = gE[i] * inv_d + go[i];
+        gE[i] = valid ? v : 0.f;
+      }
+      if (a.ln) {
+        float mean, rstd, gam[NF];
+        ln_stats<H>(mp, a.eps, mean, rstd);
+        load_vec<H>(vb + H, g, gam);
+        float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+        for (int i = 0; i < NF; ++i) {
+          const float xh = (mp[i] - mean) * rstd;
+          t[i] = gE[i] * xh;
+          const float gx = gE[i] * gam[i];
+          s1 += gx;
+          s2 += gx * xh;
+          mp[i] = xh;
+        }
+        {
+          float rs[NS];  // gE and t are zero on absent rows
+          sum16_scatter<NF>(gE, rs, j);
+#pragma unroll
+          for (int c = 0; c < NS; ++c) sbe[c] += rs[c];
+          sum16_scatter<NF>(t, rs, j);
+#pragma unroll
+          for (int c = 0; c < NS; ++c) sga[c] += rs[c];
+        }
+        s1 = row_sum(s1) * (1.f / H);
+        s2 = row_sum(s2) * (1.f / H);
+        // rstd (gE gam - s1 - x^ s2) as two multiply-adds per feature
+        const float c1 = -rstd * s1, c2 = -rstd * s2;
+#pragma unroll
+        for (int i = 0; i < NF; ++i) mp[i] = fmaf(mp[i], c2, fmaf(gE[i] * gam[i], rstd, c1));
+      } else {
+#pragma unroll
+        for (int i = 0; i < NF; ++i) mp[i] = gE[i];
+      }
+      // gh = (W2^T gm) * ELU'(h)
+      make_op(mp, o);
+      stage_row<H, true, ROWS>(tG2, srow, g, mp);
+#pragma unroll
+      for (int i = 0; i < NF; ++i) t[i] = 0.f;
+      gemm_wt<true, H, H>(w2, o, t, ln);
+#pragma unroll
+      for (int i = 0; i < NF; ++i) t[i] *= elu_deriv_from_value(u[i]);
+      load(k + 16, g);  // the next block's rows, ahead of this one's stores
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (AM) {  // residual path: the next layer's gradient only
+#pragma unroll
+        for (int i = 0; i < NF; ++i) gE[i] = go[i];
+      }
+      // g_e = gE + W1c^T gh
+      make_op(t, o);
+      stage_row<H, true, ROWS>(tG1, srow, g, t);
+      gemm_wt<true, H, H>(w1c, o, gE, ln);
+      if (valid) {
+        store_row_t<H, ES>(a.g_e_in, k, g, gE);
+        store_row_bf16<H>(reinterpret_cast<__bf16*>(a.g_h) + k * H, g, t);
+      }
+      edge_gp<H>(t, carry, carry_key, key, last, a.g_P + (int64_t)ri * H, j, g);
+
+      __syncthreads();
+      dw_tiles<H, H, true, NW>(tG2, tA2, acc2, wave, lane);
+      dw_tiles<H, H, true, NW>(tG1, tA1, acc1, wave, lane);
+      cs_b2.add(tG2, wave, lane);
+      __syncthreads();
+    }
+    zero_empty_rows<H>(gr, tl.r0, tl.r1, a.g_P, lane);
+  }
+  float* slab = a.part + blockIdx.x * a.slab;
+  dw_store<H, H, NW>(acc1, slab, H, wave, lane);
+  dw_store<H, H, NW>(acc2, slab + H * H, H, wave, lane);
+  float* red = reinterpret_cast<float*>(smem);
+  cs_b2.store(red, slab + 2 * H * H, wave, lane);
+  store_scattered2<H, NW>(sbe, sga, red, slab + 2 * H * H + 2 * H, slab + 2 * H * H + H, wave, lane);
+}
+
+template <int H, bool AM>
+static hipError_t launch_edge_bwd_wide_t(const EdgeBwdArgs& a, int grid, hipStream_t s) {
+  using C = EdgeBwdWideCfg<H>;
+  auto kern = a.es ? k_edge_bwd_wide<H, AM, true> : k_edge_bwd_wide<H, AM, false>;
+  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * C::NW), C::LDS, s, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_edge_bwd(const EdgeBwdArgs& a, int grid, hipStream_t s) {
   if (a.es && !a.bf) return hipErrorInvalidValue;
   if (a.H == 32) return launch_edge_bwd_h<32>(a, grid, s);
   if (a.H == 64) return launch_edge_bwd_h<64>(a, grid, s);
-  return hipErrorInvalidValue;  // wider layers: launch_edge_bwd_split
+  if (a.H == 128 && a.bf) return a.am ? launch_edge_bwd_wide_t<128, true>(a, grid, s) : launch_edge_bwd_wide_t<128, false>(a, grid, s);
+  return hipErrorInvalidValue;  // wide FP32 layers: launch_edge_bwd_split
 }
 
-// ------------------------------------------- split edge adjoint (wide H)
+// ------------------------------------- split edge adjoint (FP32, wide H)
 
 
-template <int H, bool BF, int NWQ>
+template <int H, int NWQ>
 struct EdgeBwdSplitCfg {
   // NWQ independent waves sharing the LDS weight fragments: 8 (two per
   // SIMD, 256 registers each), or 4 (one per SIMD with up to 512: the
   // per-edge adjoint at H = 128 wants about 320, and at 256 the compiler
-  // spills).  Measured on C3 (one launch, same box): BF16 7.30 ms at 8
-  // waves, 7.04 at 4; FP32, whose products keep the matrix unit busy, 14.3
-  // at 8 and 15.6 at 4.
+  // spills).  Measured on C3 (one launch, same box): 14.3 ms at 8 waves,
+  // whose products keep the matrix unit busy, 15.6 at 4.
   static_assert(NWQ == 4 || NWQ == 8, "4 or 8 waves per workgroup");
   static constexpr int NW = NWQ;
-  static constexpr size_t FB = frag_bytes(H, H, BF);
-  // BF16 keeps W1c, W2, W2^T, W1c^T; FP32 only W1c and W2 (the transposed
-  // products read them at transposed addresses, gemm_f32_tr)
-  static constexpr int NFR = BF ? 4 : 2;
+  static constexpr size_t FB = frag_bytes(H, H, false);
+  // W1c and W2 (the transposed products read them at transposed addresses,
+  // gemm_f32_tr)
+  static constexpr int NFR = 2;
   static constexpr size_t VECS = 2 * H * sizeof(float);
   static constexpr size_t CARRY = NW * H * sizeof(float);
   // per-lane LayerNorm-parameter sums of every wave, added up at the end
   static constexpr int NS = H / 64;  // values per lane after the 16-lane reduce-scatter
   static constexpr size_t RED = NW * 64 * 2 * NS * sizeof(float);
-  static constexpr bool LDS_FRAG = NFR * FB + VECS + CARRY + RED <= kLdsLimit;
-  static constexpr size_t RED_OFF = LDS_FRAG ? NFR * FB : 0;
+  static constexpr size_t RED_OFF = NFR * FB;
   static constexpr size_t LDS = RED_OFF + RED + CARRY + VECS;
+  static_assert(LDS <= kLdsLimit, "weights in LDS");
 };
 
-// The edge adjoint without its matrix weight gradients, for widths where
-// the fused kernel's staging tiles and accumulators do not fit next to the
-// weights.  Per edge it computes what k_edge_bwd computes (g_e, g_h, the
+// The FP32 edge adjoint without its matrix weight gradients, for widths where
+// staging tiles and accumulators do not fit next to the weights.  Per edge it computes what k_edge_bwd computes (g_e, g_h, the
 // segmented g_P) and writes the factors of the weight gradients instead of
 // accumulating them: gm and u (dW2 = sum gm u^T, db2 = sum gm); dW1c =
 // sum g_h e^T is formed from g_h and e.  The LayerNorm-parameter gradients
@@ -767,27 +989,14 @@ struct EdgeBwdSplitCfg {
 // H/64 features), accumulated per lane, and the waves' sums are added in
 // wave order into the workgroup's slab at the end.  Waves walk their tiles
 // independently (no barriers in the loop).
-template <int H, bool BF, bool AM, bool ES, int NWQ>
-__global__ __launch_bounds__((64 * EdgeBwdSplitCfg<H, BF, NWQ>::NW)) void k_edge_bwd_split(EdgeBwdArgs a) {
-  using C = EdgeBwdSplitCfg<H, BF, NWQ>;
+template <int H, bool AM, int NWQ>
+__global__ __launch_bounds__((64 * EdgeBwdSplitCfg<H, NWQ>::NW)) void k_edge_bwd_split(EdgeBwdArgs a) {
+  using C = EdgeBwdSplitCfg<H, NWQ>;
   constexpr int NF = H / 4, MB = H / 16, NW = C::NW;
-  // FP32: the transposed products read W1c / W2 in the rotated layout
-  constexpr bool ROT = !BF && C::LDS_FRAG;
   extern __shared__ uint4 smem[];
-  const char* fr;
-  if constexpr (C::LDS_FRAG) {
-    if constexpr (ROT) {
-      stage_frags_rot(smem, a.w1c.frag, C::NFR * C::FB);
-    } else {
-      stage_wfrag<BF, H, H>(smem, a.w1c.w);
-      stage_wfrag<BF, H, H>(smem + C::FB / 16, a.w2.w);
-      stage_wfrag<BF, H, H>(smem + 2 * C::FB / 16, WView{a.w2.w.p, a.w2.w.ld, 1});
-      stage_wfrag<BF, H, H>(smem + 3 * C::FB / 16, WView{a.w1c.w.p, a.w1c.w.ld, 1});
-    }
-    fr = reinterpret_cast<const char*>(smem);
-  } else {
-    fr = reinterpret_cast<const char*>(a.w1c.frag);
-  }
+  // the transposed products read W1c / W2 in the rotated layout
+  stage_frags_rot(smem, a.w1c.frag, C::NFR * C::FB);
+  const char* fr = reinterpret_cast<const char*>(smem);
   float* vecs = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + C::LDS - C::VECS);
   float* carry = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + C::LDS - C::VECS - C::CARRY) +
                  (threadIdx.x / 64) * H + (threadIdx.x / 16 % 4) * (H / 4);
@@ -819,8 +1028,6 @@ __global__ __launch_bounds__((64 * EdgeBwdSplitCfg<H, BF, NWQ>::NW)) void k_edge
       const char* frb = fr + opaque_zero();
       const char* fW1c = frb;
       const char* fW2 = frb + C::FB;
-      const char* fW2t = frb + 2 * C::FB;
-      const char* fW1ct = frb + 3 * C::FB;
       const int64_t k = base + j;
       const bool valid = k < e1;
       const int64_t kk = valid ? k : e_last;
@@ -842,7 +1049,7 @@ __global__ __launch_bounds__((64 * EdgeBwdSplitCfg<H, BF, NWQ>::NW)) void k_edge
         nx_n = (k2 + 1 < e1) ? gr.recv[k2 + 1] : -1;
       }
       float ev[NF], u[NF], t[NF], gE[NF];
-      load_row_t<H, ES>(a.e_in, kk, g, ev);
+      load_row_t<H, false>(a.e_in, kk, g, ev);
       load_row<H>(a.P + (int64_t)ri * H, g, u);
       load_row<H>(a.Q + (int64_t)sj * H, g, t);
       load_row<H>(a.g_a + (int64_t)ri * H, g, gE);
@@ -850,17 +1057,17 @@ __global__ __launch_bounds__((64 * EdgeBwdSplitCfg<H, BF, NWQ>::NW)) void k_edge
       // recompute the forward
 #pragma unroll
       for (int i = 0; i < NF; ++i) u[i] += t[i];
-      gemm<BF, MB, MB, ROT>(fW1c, ev, u, lane);
+      gemm<false, MB, MB, true>(fW1c, ev, u, lane);
 #pragma unroll
       for (int i = 0; i < NF; ++i) u[i] = elu(u[i]);
-      if (valid) store_row_t<H, BF>(a.u, k, g, u);
+      if (valid) store_row_t<H, false>(a.u, k, g, u);
       float mp[NF];
       const float* vb = vecs + opaque_zero();
       load_vec<H>(vb, g, mp);
-      gemm<BF, MB, MB, ROT>(fW2, u, mp, lane);
+      gemm<false, MB, MB, true>(fW2, u, mp, lane);
       // gradient reaching e'
       if (a.g_e_out) {
-        load_row_t<H, ES>(a.g_e_out, kk, g, t);
+        load_row_t<H, false>(a.g_e_out, kk, g, t);
 #pragma unroll
         for (int i = 0; i < NF; ++i) gE[i] = gE[i] * inv_d + t[i];
       } else {
@@ -902,32 +1109,26 @@ __global__ __launch_bounds__((64 * EdgeBwdSplitCfg<H, BF, NWQ>::NW)) void k_edge
 #pragma unroll
         for (int i = 0; i < NF; ++i) mp[i] = gE[i];
       }
-      if (valid) store_row_t<H, BF>(a.gm, k, g, mp);
+      if (valid) store_row_t<H, false>(a.gm, k, g, mp);
       // gh = (W2^T gm) * ELU'(h); ELU'(h) = 1 for h > 0 else exp(h) = u + 1
 #pragma unroll
       for (int i = 0; i < NF; ++i) t[i] = 0.f;
-      if constexpr (!BF && C::LDS_FRAG)
-        gemm_f32_tr<H, ROT>(reinterpret_cast<const float*>(fW2), mp, t, lane);
-      else
-        gemm<BF, MB, MB>(fW2t, mp, t, lane);
+      gemm_f32_tr<H, true>(reinterpret_cast<const float*>(fW2), mp, t, lane);
 #pragma unroll
       for (int i = 0; i < NF; ++i) t[i] *= elu_deriv_from_value(u[i]);
       if constexpr (AM) {  // residual path: the next layer's gradient only
         if (a.g_e_out) {
-          load_row_t<H, ES>(a.g_e_out, kk, g, gE);
+          load_row_t<H, false>(a.g_e_out, kk, g, gE);
         } else {
 #pragma unroll
           for (int i = 0; i < NF; ++i) gE[i] = 0.f;
         }
       }
       // g_e = gE + W1c^T gh
-      if constexpr (!BF && C::LDS_FRAG)
-        gemm_f32_tr<H, ROT>(reinterpret_cast<const float*>(fW1c), t, gE, lane);
-      else
-        gemm<BF, MB, MB>(fW1ct, t, gE, lane);
+      gemm_f32_tr<H, true>(reinterpret_cast<const float*>(fW1c), t, gE, lane);
       if (valid) {
-        store_row_t<H, ES>(a.g_e_in, k, g, gE);
-        store_row_t<H, BF>(a.g_h, k, g, t);
+        store_row_t<H, false>(a.g_e_in, k, g, gE);
+        store_row_t<H, false>(a.g_h, k, g, t);
       }
       // g_P: segmented sum of gh per receiver (carry through LDS); lanes
       // past the tile's last edge hold gh = 0 (gE zeroed) and a key of their own
@@ -957,57 +1158,25 @@ __global__ __launch_bounds__((64 * EdgeBwdSplitCfg<H, BF, NWQ>::NW)) void k_edge
     }
   }
   if (a.ln) {
-    // lane j of group g holds value indices q = j*NS + c of the row-block
-    // layout, i.e. feature 16 (q / 4) + 4 g + q % 4; add the waves in order
-    float* red = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + C::RED_OFF);
-#pragma unroll
-    for (int c = 0; c < NS; ++c) {
-      red[((wave * 64 + lane) * 2 + 0) * NS + c] = sbe[c];
-      red[((wave * 64 + lane) * 2 + 1) * NS + c] = sga[c];
-    }
-    __syncthreads();
     float* slab = a.part + blockIdx.x * a.slab;
-    for (int t = threadIdx.x; t < 2 * H; t += blockDim.x) {
-      const int v = t / H, f = t % H;
-      const int q = 4 * (f / 16) + f % 4, gg = (f % 16) / 4;
-      const int l = q / NS + 16 * gg, c = q % NS;
-      float sum = 0.f;
-      for (int w = 0; w < NW; ++w) sum += red[((w * 64 + l) * 2 + v) * NS + c];
-      slab[(v == 0 ? 2 * (int64_t)H * H + 2 * H : 2 * (int64_t)H * H + H) + f] = sum;  // dbeta, dgamma
-    }
+    store_scattered2<H, NW>(sbe, sga, reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + C::RED_OFF),
+                            slab + 2 * (int64_t)H * H + 2 * H, slab + 2 * (int64_t)H * H + H, wave, lane);
   }
 }
 
-template <int H, bool BF, bool AM, bool ES, int NWQ>
-static hipError_t launch_edge_bwd_split_es(const EdgeBwdArgs& a, int grid, hipStream_t s) {
-  using C = EdgeBwdSplitCfg<H, BF, NWQ>;
-  (void)hipFuncSetAttribute((const void*)k_edge_bwd_split<H, BF, AM, ES, NWQ>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
-  hipLaunchKernelGGL((k_edge_bwd_split<H, BF, AM, ES, NWQ>), dim3(grid), dim3(64 * C::NW), C::LDS, s, a);
+template <int H, int NWQ>
+static hipError_t launch_edge_bwd_split_t(const EdgeBwdArgs& a, int grid, hipStream_t s) {
+  using C = EdgeBwdSplitCfg<H, NWQ>;
+  auto kern = a.am ? k_edge_bwd_split<H, true, NWQ> : k_edge_bwd_split<H, false, NWQ>;
+  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * C::NW), C::LDS, s, a);
   return hipGetLastError();
 }
-template <int H, bool BF, bool AM, int NWQ>
-static hipError_t launch_edge_bwd_split_am(const EdgeBwdArgs& a, int grid, hipStream_t s) {
-  if constexpr (BF) {
-    if (a.es) return launch_edge_bwd_split_es<H, BF, AM, true, NWQ>(a, grid, s);
-  }
-  return launch_edge_bwd_split_es<H, BF, AM, false, NWQ>(a, grid, s);
-}
 
-// Waves per workgroup: 4 or 8; the default is 4 with BF16 GEMMs and 8 in
-// FP32 (the C ABI validates the field).
-template <int H, bool BF>
-static hipError_t launch_edge_bwd_split_t(const EdgeBwdArgs& a, int grid, hipStream_t s) {
-  const int nw = a.waves ? a.waves : (BF ? 4 : 8);
-  if (nw == 4)
-    return a.am ? launch_edge_bwd_split_am<H, BF, true, 4>(a, grid, s) : launch_edge_bwd_split_am<H, BF, false, 4>(a, grid, s);
-  return a.am ? launch_edge_bwd_split_am<H, BF, true, 8>(a, grid, s) : launch_edge_bwd_split_am<H, BF, false, 8>(a, grid, s);
-}
-
+// Waves per workgroup: 4 or 8 (the default; the C ABI validates the field).
 hipError_t launch_edge_bwd_split(const EdgeBwdArgs& a, int grid, hipStream_t s) {
-  if (a.es && !a.bf) return hipErrorInvalidValue;
-  if (a.H == 128) return a.bf ? launch_edge_bwd_split_t<128, true>(a, grid, s) : launch_edge_bwd_split_t<128, false>(a, grid, s);
-  return hipErrorInvalidValue;
+  if (a.es || a.bf || a.H != 128) return hipErrorInvalidValue;
+  return a.waves == 4 ? launch_edge_bwd_split_t<128, 4>(a, grid, s) : launch_edge_bwd_split_t<128, 8>(a, grid, s);
 }
 
 // ---------------------------------------- weight gradients from row pairs

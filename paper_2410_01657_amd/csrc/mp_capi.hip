@@ -218,9 +218,10 @@ struct LayerWs {
     const size_t H = c->H, N = g->n_rows, E = g->n_edges;
     n_tiles = n_tiles_for(E, c->tile_edges, c->H, c->gemm_dtype == MP_BF16, bwd);
     ge = c->edge_grid > 0 ? c->edge_grid : edge_grid(n_tiles, c->gemm_dtype != MP_BF16 && H == 64);
-    gbe = c->edge_bwd_grid > 0                         ? c->edge_bwd_grid
-          : c->gemm_dtype != MP_BF16 && !edge_bwd_split(H) ? edge_bwd_f32_grid(n_tiles, H)
-                                                           : edge_bwd_grid(E);
+    gbe = c->edge_bwd_grid > 0                  ? c->edge_bwd_grid
+          : c->gemm_dtype != MP_BF16 && H <= 64 ? edge_bwd_f32_grid(n_tiles, H)
+          : c->gemm_dtype == MP_BF16 && H > 64  ? std::min(256, edge_bwd_grid(E))  // one workgroup per CU
+                                                : edge_bwd_grid(E);
     gn = row_grid(N);
     gbn = row_bwd_grid(N);
     size_t o = fr.total;
@@ -241,7 +242,7 @@ struct LayerWs {
         o = align_up(o + N * H * 4);
       }
       gh = o; o = align_up(o + eb);
-      if (edge_bwd_split(c->H)) {
+      if (edge_bwd_split(c->H, c->gemm_dtype == MP_BF16)) {
         sgm = o; o = align_up(o + eb);
         su = o; o = align_up(o + eb);
       }
@@ -726,7 +727,7 @@ extern "C" int mp_layer_backward(const mp_layer_cfg* cfg, const mp_layer_params*
   eb.g_P = gP;
   eb.part = wsf(ws, W.part_e);
   eb.slab = edge_slab(H);
-  if (edge_bwd_split(H)) {
+  if (edge_bwd_split(H, bf)) {
     // wide layers: the adjoint writes the per-edge factors, then the weight
     // gradients are summed from them (same slab layout as the fused kernel)
     eb.gm = ws_at(ws, W.sgm);

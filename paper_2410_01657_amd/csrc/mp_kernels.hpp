@@ -149,7 +149,7 @@ struct EdgeBwdArgs {
   DevGraph g;
   int H, ln, bf;
   int am;  // the forward aggregated the MLP output (message), not e'
-  int waves;  // waves per workgroup: 0 (default), 4 or 8 (fused BF16 kernel and split kernel; the fused FP32 kernel has 8)
+  int waves;  // waves per workgroup: 0 (default), 4 or 8 (BF16 at H <= 64 and the split kernel; the others have 4)
   int es;     // edge states and their gradients (e_in, g_e_out, g_e_in) stored as BF16 (with bf only)
 
   const float* P;
@@ -168,15 +168,15 @@ struct EdgeBwdArgs {
   float* part;           // partial weight gradients, slab per workgroup
   int64_t slab;
   // split form (edge_bwd_split): per-edge factors of the matrix weight
-  // gradients, [E][H] each, BF16 on the BF16 path: gm (pre-LayerNorm
-  // gradient) and u (ELU output)
+  // gradients, [E][H] FP32 each: gm (pre-LayerNorm gradient) and u (ELU
+  // output)
   void* gm;
   void* u;
 };
 hipError_t launch_edge_bwd(const EdgeBwdArgs& a, int grid, hipStream_t s);
-// Whether layers of width H use the split edge adjoint (the fused kernel's
-// weight-gradient tiles and all four weight matrices do not fit on chip).
-constexpr bool edge_bwd_split(int H) { return H > 64; }
+// Whether layers of width H use the split edge adjoint (in FP32 the fused kernel's
+// weight-gradient tiles and the weight matrices do not fit on chip at H > 64).
+constexpr bool edge_bwd_split(int H, bool bf) { return H > 64 && !bf; }
 hipError_t launch_edge_bwd_split(const EdgeBwdArgs& a, int grid, hipStream_t s);
 // dst slab block [GW][AW] += sum over rows r of G[r] (x) A[r]  (G: [R][GW],
 // A: [R][AW]; BF16 or FP32 as `g_bf` / `a_bf`), one slab per workgroup at
