@@ -71,3 +71,25 @@ def test_adjoint_against_fp64(mesh, ln, agg, estate, with_ge):
     again = layer_backward(cfg, p, dg, x, e, a, gx, ge if with_ge else None)
     assert torch.equal(again[0], g_x) and torch.equal(again[1], g_e)
     assert all(torch.equal(again[2][k], grads[k]) for k in names)
+
+
+@pytest.mark.parametrize("mesh,ln", [("tail", True), ("odd", False), ("many_tiles", True)])
+def test_fp32_weight_gradients_against_fp64(mesh, ln):
+    """The separate weight-gradient passes of the FP32 layer, over row counts
+    that end inside 16- and 32-row blocks.  A sum of n products rounds to some
+    sqrt(n) 2^-24 of a term's size: 1e-5 of the sum leaves a factor of ten."""
+    from paper_2410_01657_amd.ops import layer_backward, layer_cfg, layer_forward
+    dg = _graph(mesh)
+    _, o, names = layer_params(H, ln)
+    p = {k: torch.from_numpy(o[v].astype(np.float32)).to(DEV) for k, v in names.items()}
+    gen = torch.Generator().manual_seed(5)
+    r = lambda n: torch.randn(n, H, generator=gen).to(DEV)
+    x, e, gx, ge = r(dg.n_rows), r(dg.n_edges), r(dg.n_rows), r(dg.n_edges)
+    cfg = layer_cfg(H, ln)
+    _, _, a = layer_forward(cfg, p, dg, x, e)
+    _, _, grads = layer_backward(cfg, p, dg, x, e, a, gx, ge)
+    ref = {k: v.double().requires_grad_(True) for k, v in p.items()}
+    out = _layer(dg, ref, x.double(), e.double(), ln, "state")
+    want = torch.autograd.grad(list(out), [ref[k] for k in names], [gx.double(), ge.double()])
+    for k, w in zip(names, want):
+        assert ((grads[k].double() - w).norm() / w.norm()).item() < 1e-5, k
