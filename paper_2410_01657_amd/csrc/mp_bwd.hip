@@ -1345,17 +1345,13 @@ static hipError_t launch_row_dw_t(const RowDwArgs& a, int grid, hipStream_t s) {
 }
 
 hipError_t launch_row_dw(const RowDwArgs& a, int grid, hipStream_t s) {
-  // forms in use: 128 x 128 (edge adjoint: G BF16/FP32, A BF16/FP32) and
-  // 128 x [128 | 128] (node update: A = [a*, x], FP32)
+  // forms in use: 128 x 128, both factors in the product type (node update; in
+  // FP32 the edge adjoint and the sender side too), and 128 x [128 | 128] (node
+  // update: A = [a*, x], FP32)
   if (a.GW != 128) return hipErrorInvalidValue;
   if (a.AW == 128 && !a.A2) {
-    // BF16 products take BF16 or FP32 operands; FP32 products FP32 operands
-    if (a.bf) {
-      if (a.g_bf && a.a_bf) return launch_row_dw_t<128, 128, true, true, true, false>(a, grid, s);
-      if (a.g_bf && !a.a_bf) return launch_row_dw_t<128, 128, true, true, false, false>(a, grid, s);
-      return hipErrorInvalidValue;
-    }
-    if (!a.g_bf && !a.a_bf) return launch_row_dw_t<128, 128, false, false, false, false>(a, grid, s);
+    if (a.bf && a.g_bf && a.a_bf) return launch_row_dw_t<128, 128, true, true, true, false>(a, grid, s);
+    if (!a.bf && !a.g_bf && !a.a_bf) return launch_row_dw_t<128, 128, false, false, false, false>(a, grid, s);
     return hipErrorInvalidValue;
   }
   if (a.AW == 256 && a.A2 && !a.a_bf) {

@@ -31,8 +31,10 @@ class Work:
 
 
 def edge_bwd_split(H):
-    """The library's edge adjoint runs in two passes (per-edge factors, then
-    the weight-gradient sums) at widths above 64."""
+    """Whether the edge adjoint is counted in two passes (per-edge factors, then
+    the weight-gradient sums): at widths above 64, where the FP32 kernels run
+    so.  The BF16 kernel forms both in one launch (edge_bwd); its count keeps
+    the two passes' roofs."""
     return H > 64
 
 
