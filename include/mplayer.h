@@ -375,7 +375,8 @@ int mp_deep_layer_workspace_size(const mp_deep_layer_cfg* cfg, const mp_dev_grap
  * (input [a*_i, x_i], 2H -> H); both updates residual.  x_in[N][H],
  * e_in[E][H] -> x_out[N][H], e_out[E][H]; a_star_out[N][H] (required)
  * receives the synchronised aggregate for the backward.  Outputs must not
- * alias inputs.  Errors: MP_EINVAL for a bad configuration (H not 8, 16 or
+ * alias inputs (x_out also serves as scratch until its rows are written).
+ * Errors: MP_EINVAL for a bad configuration (H not 8, 16 or
  * 32, n_hidden outside [0, 8], a non-positive ln_eps with LayerNorm, an
  * unknown aggregate), NULL, unaligned or aliasing buffers; MP_EPLAN for a
  * graph descriptor that is unsealed, changed after sealing, or pairs a
@@ -388,7 +389,7 @@ int mp_deep_layer_forward(const mp_deep_layer_cfg* cfg, const float* theta_edge,
 /* Adjoint (Eq. 3) of mp_deep_layer_forward for the same inputs and a*:
  * gradients of x_in, e_in and both parameter arrays.  MLP activations are
  * recomputed; the workspace (mp_deep_layer_workspace_size) holds per-row
- * records of them.  g_e_out may be NULL (zero).  The graph needs its
+ * records of them (H = 16, or n_hidden > 5), or one gradient row per edge.  g_e_out may be NULL (zero).  The graph needs its
  * reverse-edge array.  Errors: as mp_deep_layer_forward, plus MP_EINVAL
  * for a missing reverse-edge array or gradient outputs aliasing inputs and
  * MP_ENOMEM for ws_bytes below mp_deep_layer_workspace_size. */
