@@ -375,7 +375,8 @@ int mp_deep_layer_workspace_size(const mp_deep_layer_cfg* cfg, const mp_dev_grap
  * (input [a*_i, x_i], 2H -> H); both updates residual.  x_in[N][H],
  * e_in[E][H] -> x_out[N][H], e_out[E][H]; a_star_out[N][H] (required)
  * receives the synchronised aggregate for the backward.  Outputs must not
- * alias inputs (x_out also serves as scratch until its rows are written).
+ * alias inputs (x_out, where it overlaps no other buffer, also serves as
+ * scratch until its rows are written).
  * Errors: MP_EINVAL for a bad configuration (H not 8, 16 or
  * 32, n_hidden outside [0, 8], a non-positive ln_eps with LayerNorm, an
  * unknown aggregate), NULL, unaligned or aliasing buffers; MP_EPLAN for a

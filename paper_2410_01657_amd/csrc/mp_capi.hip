@@ -1055,6 +1055,12 @@ int deep_grad_sums(const char* name, const float* rec, int64_t n_rows, int rs, i
 // Width 32 with few enough extra layers runs on the matrix unit.
 bool deep32(const mp_deep_layer_cfg* c) { return c->H == 32 && c->n_hidden <= kDeep32MaxHidden; }
 
+// Whether [a, a + na) and [b, b + nb) share no byte.
+bool apart(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+  return p + na <= q || q + nb <= p;
+}
+
 // Tiles of the deep forward, whose bounds sit in the caller's x_out until the
 // node update writes it (the forward has no workspace): as many as fit there.
 int64_t deep32_fwd_tiles(const mp_dev_graph* g) {
@@ -1207,7 +1213,14 @@ extern "C" int mp_deep_layer_forward(const mp_deep_layer_cfg* cfg, const float* 
   ea.e_in = e_in;
   ea.e_out = e_out;
   ea.a_out = a_star_out;
-  const bool d32 = deep32(cfg);
+  // x_out holds the tile bounds only where the edge update neither reads nor
+  // writes it (a caller may give it the place of e_in or e_out, dead once the
+  // node update runs); the row-per-thread kernels need no bounds.
+  const size_t nx = (size_t)g->n_rows * H * 4, ne = (size_t)g->n_edges * H * 4;
+  const size_t nt = (size_t)deep_theta_floats(3 * H, H, cfg->n_hidden, H, ea.ln) * 4;
+  const bool d32 = deep32(cfg) && apart(x_out, nx, x_in, nx) && apart(x_out, nx, e_in, ne) &&
+                   apart(x_out, nx, e_out, ne) && apart(x_out, nx, a_star_out, nx) &&
+                   apart(x_out, nx, theta_edge, nt);
   if (d32) {
     int32_t* t = reinterpret_cast<int32_t*>(x_out);
     ea.g.n_tiles = deep32_fwd_tiles(g);
