@@ -1499,7 +1499,7 @@ __device__ __forceinline__ void stage_abt(void* __restrict__ dst, const WView& w
 
 // Per node j: g_Q[j] = sum of g_h over j's outgoing edges, read as the
 // reverse edges of j's incoming edges (in ascending order), then
-//   g_x[j] += W1a^T g_P[j] + W1b^T g_Q[j]
+//   g_x[j] = g_add[j] + W1a^T g_P[j] + W1b^T g_Q[j]
 //   dW1a += g_P x^T, dW1b += g_Q x^T, db1 += g_P.
 template <int H, bool BF>
 __global__ __launch_bounds__((64 * GqCfg<H, BF>::NW), (GqCfg<H, BF>::MINB)) void k_gq(GqArgs a) {
@@ -1574,7 +1574,7 @@ __global__ __launch_bounds__((64 * GqCfg<H, BF>::NW), (GqCfg<H, BF>::MINB)) void
       GqRaw<H, BF> t[GQ_CH];
 #pragma unroll
       for (int q = 0; q < GQ_CH; ++q) t[q].load(a.g_h, rv[q], g);
-      if (c == 0) load_row<H>(a.g_x + rr * H, g, gx);  // in flight with the gathers
+      if (c == 0) load_row<H>(a.g_add + rr * H, g, gx);  // in flight with the gathers
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int q = 0; q < GQ_CH; ++q)

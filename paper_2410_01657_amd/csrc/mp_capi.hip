@@ -763,6 +763,7 @@ extern "C" int mp_layer_backward(const mp_layer_cfg* cfg, const mp_layer_params*
   q.g_P = gP;
   q.g_h = gh;
   q.w = LW.w1a.w;
+  q.g_add = g_x_in;
   q.g_x = g_x_in;
   q.part = wsf(ws, W.part_q);
   q.slab = gq_slab(H);
@@ -1072,7 +1073,7 @@ int64_t deep32_fwd_tiles(const mp_dev_graph* g) {
 bool deep8(const mp_deep_layer_cfg* c) { return c->H == 8 && c->n_hidden <= kDeep8MaxHidden; }
 
 struct DeepSplitWs {
-  size_t tile_r = 0, tile_e = 0, queue = 0, P = 0, Q = 0, ga = 0, gP = 0, gh = 0, partN = 0, partE = 0, partQ = 0,
+  size_t tile_r = 0, tile_e = 0, queue = 0, P = 0, Q = 0, ga = 0, gxn = 0, gP = 0, gh = 0, partN = 0, partE = 0, partQ = 0,
          total = 0;
   int64_t n_tiles = 0, slabN = 0, slabE = 0, slabQ = 0;
   int gr = 0, gn, ge, gq, passes = 1;
@@ -1112,6 +1113,7 @@ struct DeepSplitWs {
     take(P, N * H * 4);
     take(Q, N * H * 4);
     take(ga, N * H * 4);
+    take(gxn, N * H * 4);
     take(gh, E * H * 4);
     take(partN, (size_t)gn * slabN * 4);
     take(partE, (size_t)ge * passes * slabE * 4);
@@ -1264,6 +1266,8 @@ int deep_split_backward(const mp_deep_layer_cfg* cfg, const float* theta_edge, c
   const bool d8 = H == 8;
   DevGraph d = dev_graph(g);
   float *P = wsf(ws, W.P), *Q = wsf(ws, W.Q), *ga = wsf(ws, W.ga), *gh = wsf(ws, W.gh);
+  // g_x_in is written last: a caller may give it the place of an edge array
+  float* gxn = wsf(ws, W.gxn);
   // the first edge Linear's node parts: W0 = [W0a | W0b | W0c], [H][3 H]
   const WSrc wa{WView{theta_edge, 3 * H, 0}, nullptr}, wb{WView{theta_edge + H, 3 * H, 0}, nullptr};
   if (!d8) {
@@ -1287,7 +1291,7 @@ int deep_split_backward(const mp_deep_layer_cfg* cfg, const float* theta_edge, c
   na.x = x_in;
   na.g_out = g_x_out;
   na.g_a = ga;
-  na.g_x = g_x_in;
+  na.g_x = gxn;
   na.part = wsf(ws, W.partN);
   na.slab = W.slabN;
   if ((rc = run("deep_node_bwd", s, [&] {
@@ -1319,7 +1323,7 @@ int deep_split_backward(const mp_deep_layer_cfg* cfg, const float* theta_edge, c
     return rc;
   float* partQ = wsf(ws, W.partQ);
   if (d8) {
-    const Deep8GqArgs q{d, theta_edge, x_in, gh, g_x_in, partQ, W.slabQ};
+    const Deep8GqArgs q{d, theta_edge, x_in, gh, gxn, g_x_in, partQ, W.slabQ};
     rc = run("gq", s, [&] { return launch_deep8_gq(q, W.gq, s); });
   } else {
     GqArgs q{};
@@ -1329,6 +1333,7 @@ int deep_split_backward(const mp_deep_layer_cfg* cfg, const float* theta_edge, c
     q.g_P = ea.g_P;
     q.g_h = gh;
     q.w = wa.w;
+    q.g_add = gxn;
     q.g_x = g_x_in;
     q.part = partQ;
     q.slab = W.slabQ;

@@ -589,7 +589,7 @@ __global__ __launch_bounds__(64 * kWav, 2) void k_deep8_node_bwd(DeepSplitNodeAr
 }
 
 // Per node: g_P = sum of g_h over its incoming edges, g_Q over the reverses of
-// them (its outgoing edges), in CSR order; g_x += W0a^T g_P + W0b^T g_Q;
+// them (its outgoing edges), in CSR order; g_x = g_add + W0a^T g_P + W0b^T g_Q;
 // dW0a = sum g_P x^T, dW0b = sum g_Q x^T, db0 = sum g_P.  Bound by the two
 // passes over g_h; two lanes share a node, half a row each, so that neighbouring
 // lanes read one 32-byte row and six edges' rows fit in flight (6.3M edges: 163 us
@@ -616,7 +616,7 @@ __global__ __launch_bounds__(64 * kWav, 4) void k_deep8_gq(Deep8GqArgs a) {
     const float* gh = a.g_h + 4 * hf;
     float v[3][4], gx[4];  // g_P, g_Q, x
     load_vec8<4>(a.x + rr * kH + 4 * hf, v[2]);
-    load_vec8<4>(a.g_x + rr * kH + 4 * hf, gx);
+    load_vec8<4>(a.g_add + rr * kH + 4 * hf, gx);
 #pragma unroll
     for (int i = 0; i < 4; ++i) v[0][i] = v[1][i] = 0.f;
     // six edges at a time: their reverse indices first, then all their rows

@@ -237,7 +237,8 @@ struct GqArgs {
   const float* g_P;
   const void* g_h;       // [E][H], FP32 or (BF16 path) BF16
   WView w;               // [W1a | W1b | ...], H rows: the first Linear's matrix
-  float* g_x;            // accumulated: g_x += W1a^T g_P + W1b^T g_Q
+  const float* g_add;    // the node update's part of g_x (may be g_x itself)
+  float* g_x;            // g_add + W1a^T g_P + W1b^T g_Q
   float* part;
   int64_t slab;
   float* gq_out;         // split form only: g_Q [N][H] (FP32)
@@ -350,7 +351,8 @@ struct Deep8GqArgs {
   const float* theta;
   const float* x;
   const float* g_h;  // [E][8]
-  float* g_x;        // [N][8], added to
+  const float* g_add;  // [N][8], the node update's part of g_x
+  float* g_x;
   float* part;       // [dW0a 8 x 8][dW0b 8 x 8][db0] per workgroup
   int64_t slab;
 };
