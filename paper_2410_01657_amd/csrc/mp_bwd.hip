@@ -585,7 +585,6 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
 
   const DevGraph& gr = a.g;
   const TileSched ts = tile_sched(gr.n_tiles);
-  const float sgn = dw_sign();  // all gradients in the loop carry this sign
   Dw d2, d1;
   d2.zero();
   d1.zero();
@@ -618,7 +617,7 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       const bool valid = k < e1;
       const int64_t kk = valid ? k : e_last;
       const int ri = ic.ri;
-      const float inv_d = sgn / (float)ic.md;
+      const float inv_d = 1.f / (float)ic.md;
       const bool last = valid && ic.nx != ri;
       const int key = valid ? ri + 1 : -1;
       EdgeBwdHead<H> cur = nx;
@@ -656,10 +655,12 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       // gradient reaching e', LayerNorm adjoint (mp becomes gm)
 #pragma unroll
       for (int i = 0; i < NF; ++i) {
-        go[i] *= sgn;
         const float v = gE[i] * inv_d + go[i];
         gE[i] = valid ? v : 0.f;
       }
+      // gm and gh below carry the row's sign
+      const float sg = row_sign(gE[0]);
+      const uint32_t flip = dw_flip(wave, sg);
       if (a.ln) {
         float mean, rstd, gam[NF];
         ln_stats<H>(mp, a.eps, mean, rstd);
@@ -677,19 +678,19 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
         }
         s1 = row_sum(s1) * (1.f / H);
         s2 = row_sum(s2) * (1.f / H);
-        const float c1 = -rstd * s1, c2 = -rstd * s2;
+        const float rs = rstd * sg, c1 = -rs * s1, c2 = -rs * s2;
 #pragma unroll
-        for (int i = 0; i < NF; ++i) mp[i] = fmaf(mp[i], c2, fmaf(gE[i] * gam[i], rstd, c1));
+        for (int i = 0; i < NF; ++i) mp[i] = fmaf(mp[i], c2, fmaf(gE[i] * gam[i], rs, c1));
       } else {
 #pragma unroll
-        for (int i = 0; i < NF; ++i) mp[i] = gE[i];
+        for (int i = 0; i < NF; ++i) mp[i] = gE[i] * sg;
       }
 #pragma unroll
-      for (int i = 0; i < NF; ++i) db2[i] += mp[i];
+      for (int i = 0; i < NF; ++i) db2[i] = fmaf(mp[i], sg, db2[i]);
       // gh = (W2^T gm) * ELU'(h); dW2 += gm u^T
       make_op(mp, o);
       gemm_wt<false, H, H, ACC_SET>(w2, o, t, ln);
-      stage_op<H>(tG2, Dw::GP, ln & 15, ln >> 4, o);
+      stage_op<H>(tG2, Dw::GP, ln & 15, ln >> 4, o, flip);
       wave_lds_fence();
       d2.add(tG2, tA2, ln);
 #pragma unroll
@@ -700,12 +701,12 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       }
       // g_e = gE + W1c^T gh; dW1c += gh e^T
       make_op(t, o);
-      gemm_wt<false, H, H, ACC_ADD>(w1c, o, gE, ln);
-      stage_op<H>(tG1, Dw::GP, ln & 15, ln >> 4, o);
+      gemm_wt<false, H, H, ACC_ADD>(w1c, o, gE, ln, sg);
+      stage_op<H>(tG1, Dw::GP, ln & 15, ln >> 4, o, flip);
       wave_lds_fence();
       d1.add(tG1, tA1, ln);
 #pragma unroll
-      for (int i = 0; i < NF; ++i) gE[i] *= sgn, t[i] *= sgn;
+      for (int i = 0; i < NF; ++i) t[i] *= sg;
       nx.settle();
       in.settle();
       if (valid) {
@@ -718,10 +719,8 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
   }
   float* slab = a.part + blockIdx.x * a.slab;
   float* scratch = reinterpret_cast<float*>(smem);
-  d1.template store<NW>(scratch, slab, nullptr, sgn, wave, lane);
-  d2.template store<NW>(scratch, slab + H * H, nullptr, sgn, wave, lane);
-#pragma unroll
-  for (int i = 0; i < NF; ++i) db2[i] *= sgn, dga[i] *= sgn, dbe[i] *= sgn;
+  d1.template store<NW>(scratch, slab, nullptr, wave, lane);
+  d2.template store<NW>(scratch, slab + H * H, nullptr, wave, lane);
   block_sum_vec<H, NW>(db2, scratch, slab + 2 * H * H, wave, lane);
   block_sum_vec<H, NW>(dga, scratch, slab + 2 * H * H + H, wave, lane);
   block_sum_vec<H, NW>(dbe, scratch, slab + 2 * H * H + 2 * H, wave, lane);
@@ -1258,7 +1257,6 @@ __global__ __launch_bounds__((64 * RowDwCfg<GW, AW, BF>::NW)) void k_row_dw(RowD
   for (int t = 0; t < NT; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
   ColSum<GW, 8> cs;  // BF16 tiles
   cs.zero();
-  const float sgn = BF ? 1.f : dw_sign();
   float csf[GW / 4];  // FP32 tiles: per-lane sums
 #pragma unroll
   for (int i = 0; i < GW / 4; ++i) csf[i] = 0.f;
@@ -1282,7 +1280,16 @@ __global__ __launch_bounds__((64 * RowDwCfg<GW, AW, BF>::NW)) void k_row_dw(RowD
 #pragma unroll
     for (int i = 0; i < AW / 4; ++i) asm volatile("" : "+v"(an[i]));
   }
+  // FP32: every other workgroup, and in each the middle half of its rows, sums
+  // negated (dw_flip does it by wave, but here each wave sums the rows of all; the
+  // partial sums, and the bias with them, grow from the first row to the last)
+  float sgn = blockIdx.x & 1 ? -1.f : 1.f;
   for (int64_t it = 0; it < n_iter; ++it) {
+    if (!BF && (it == n_iter / 4 || it == n_iter - n_iter / 4) && it > 0) {
+      sgn = -sgn;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[t] = -acc[t];
+    }
     const int64_t bk = b0 + it * NW + wave;
     const int64_t row = bk * 16 + j;
     const bool valid = bk < b1 && row < n;

@@ -226,13 +226,13 @@ struct Bwd32 {
 
   // Forward and adjoint of one block.  z: what the first matrix's product is
   // added to (bias, or P + Q); gE(y): the gradient arriving at the output, zero
-  // on absent rows and times dw_sign(), asked for once the forward is done;
-  // done(d, o): called with the first pre-activation's gradient d (times
-  // dw_sign()) and its operand.
+  // on absent rows, asked for once the forward is done; done(d, o, sg): called
+  // with the first pre-activation's gradient d and its operand, both times the
+  // row's sign sg.
   template <class GE, class DONE>
   __device__ __forceinline__ void run(const char* __restrict__ w, const float* __restrict__ v, char* __restrict__ tile,
                                       const Op<false, K>& in, float (&z)[kNF], int ln, float eps, int lane,
-                                      GE&& gE, DONE&& done) {
+                                      int wave, GE&& gE, DONE&& done) {
     const int j = lane & 15, g = lane >> 4;
     float u[NH + 1][kNF], y[kNF];
     char* tG = tile + T0 + (NH + 1) * T1;
@@ -261,6 +261,8 @@ struct Bwd32 {
     wf.template load_t<kH, kH>(w + W0 + NH * W1, lane);
     __builtin_amdgcn_sched_barrier(0);
     gE(y);
+    const float sg = row_sign(y[0]);  // gm carries it from here on
+    const uint32_t flip = dw_flip(wave, sg);
     float gm[kNF];
     if (ln) {
       float mean, rstd, gam[kNF];
@@ -279,12 +281,12 @@ struct Bwd32 {
       }
       s1 = row_sum(s1) * (1.f / kH);
       s2 = row_sum(s2) * (1.f / kH);
-      const float c1 = -rstd * s1, c2 = -rstd * s2;
+      const float rs = rstd * sg, c1 = -rs * s1, c2 = -rs * s2;
 #pragma unroll
-      for (int i = 0; i < kNF; ++i) gm[i] = fmaf(z[i], c2, fmaf(y[i] * gam[i], rstd, c1));
+      for (int i = 0; i < kNF; ++i) gm[i] = fmaf(z[i], c2, fmaf(y[i] * gam[i], rs, c1));
     } else {
 #pragma unroll
-      for (int i = 0; i < kNF; ++i) gm[i] = y[i];
+      for (int i = 0; i < kNF; ++i) gm[i] = y[i] * sg;
     }
     // back through the Linears: gm becomes the gradient at pre-activation l
     typename Dw1::Frags df;
@@ -303,7 +305,7 @@ struct Bwd32 {
       }
       wf.template gemm<ACC_SET>(o, gm);
       wave_lds_fence();
-      stage_op<kH>(tG, Dw1::GP, j, g, o);
+      stage_op<kH>(tG, Dw1::GP, j, g, o, flip);
       wave_lds_fence();
       Dw1::load(df, tG, tile + T0 + l * T1, lane);
       if (l > 0) wf.template load_t<kH, kH>(w + W0 + (l > 0 ? l - 1 : 0) * W1, lane);
@@ -315,29 +317,26 @@ struct Bwd32 {
     make_op(gm, o);
     d1[0].mma(df);
     wave_lds_fence();
-    stage_op<kH>(tG, Dw1::GP, j, g, o);
+    stage_op<kH>(tG, Dw1::GP, j, g, o, flip);
     wave_lds_fence();
     typename Dw0::Frags d0f;
     Dw0::load(d0f, tG, tile, lane);
-    done(gm, o);
+    done(gm, o, sg);
     d0.mma(d0f);
   }
 
   // Slab: [dW0 kH * K][db0 (node form only)][hidden W, b pairs][last W, b][dgain, dshift]
   __device__ __forceinline__ void store(float* __restrict__ scratch, float* __restrict__ slab, int ln, int wave,
                                         int lane) {
-    const float sgn = dw_sign();
     float* p = slab + kH * K;
-    d0.template store<NW>(scratch, slab, p, sgn, wave, lane);
+    d0.template store<NW>(scratch, slab, p, wave, lane);
     if constexpr (NODE) p += kH;
 #pragma unroll
     for (int l = 0; l <= NH; ++l) {
-      d1[l].template store<NW>(scratch, p, p + kH * kH, sgn, wave, lane);
+      d1[l].template store<NW>(scratch, p, p + kH * kH, wave, lane);
       p += kHid;
     }
     if (ln) {
-#pragma unroll
-      for (int i = 0; i < kNF; ++i) dga[i] *= sgn, dbe[i] *= sgn;
       block_sum_vec<kH, NW>(dga, scratch, p, wave, lane);
       block_sum_vec<kH, NW>(dbe, scratch, p + kH, wave, lane);
     }
@@ -365,9 +364,6 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) voi
   __syncthreads();
   const DevGraph& gr = a.g;
   const TileSched ts = tile_sched(gr.n_tiles);
-  // the whole adjoint of every other workgroup runs on negated gradients (see
-  // dw_sign): its weight-gradient sums come out negated
-  const float sgn = dw_sign();
   B acc;
   const int passes = NH ? a.passes : 1;
   for (int p = 0; p < passes; ++p) {
@@ -401,7 +397,7 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) voi
         const bool valid = k < e1;
         const int64_t kk = valid ? k : e_last;
         const int ri = ic.ri;
-        const float inv_d = sgn / (float)ic.md;
+        const float inv_d = 1.f / (float)ic.md;
         const bool last = valid && ic.nx != ri;
         const int key = valid ? ri + 1 : -1;
         float z[kNF], ga[kNF], go[kNF], ge[kNF];
@@ -421,31 +417,27 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) voi
         in.fetch(gr, k + 32, e1, e_last);
         __builtin_amdgcn_sched_barrier(0);
         acc.run(
-            wl + oz, vecs + oz, tile, oe, z, a.ln, a.eps, ln,
+            wl + oz, vecs + oz, tile, oe, z, a.ln, a.eps, ln, wave,
             [&](float (&y)[kNF]) {
 #pragma unroll
               for (int i = 0; i < kNF; ++i) {
-                const float s = ga[i] * inv_d + go[i] * sgn;
+                const float s = ga[i] * inv_d + go[i];
                 y[i] = valid ? s : 0.f;
                 // the residual path; message aggregation leaves Eq. 4b's part out
-                ge[i] = a.am ? go[i] * sgn : y[i];
+                ge[i] = a.am ? go[i] : y[i];
               }
             },
-            [&](float (&d)[kNF], const Op<false, kH>& o) {
-              gemm_wt<false, kH, kH, ACC_ADD>(wl + oz, o, ge, ln);
+            [&](float (&d)[kNF], const Op<false, kH>& o, float sg) {
+              gemm_wt<false, kH, kH, ACC_ADD>(wl + oz, o, ge, ln, sg);
               settle();
               in.settle();
-              float dd[kNF];
 #pragma unroll
-              for (int i = 0; i < kNF; ++i) {
-                ge[i] *= sgn;
-                dd[i] = d[i] * sgn;
-              }
+              for (int i = 0; i < kNF; ++i) d[i] *= sg;
               if (valid) {
                 store_row<kH>(a.g_e_in + k * kH, g, ge);
-                store_row<kH>(a.g_h + k * kH, g, dd);
+                store_row<kH>(a.g_h + k * kH, g, d);
               }
-              edge_gp<kH>(dd, carry, carry_key, key, last, a.g_P + (int64_t)ri * kH, j, g);
+              edge_gp<kH>(d, carry, carry_key, key, last, a.g_P + (int64_t)ri * kH, j, g);
             });
       }
       zero_empty_rows<kH>(gr, r0, r1, a.g_P, lane);
@@ -466,9 +458,6 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 64>::NW), (Bwd32<NH, 64>::OCC)) voi
   float* vecs = reinterpret_cast<float*>(wl + B::WB);
   B::stage(wl, vecs, a.theta, a.theta, 64, a.ln);
   __syncthreads();
-  // the whole adjoint of every other workgroup runs on negated gradients (see
-  // dw_sign): its weight-gradient sums come out negated
-  const float sgn = dw_sign();
   B acc;
   acc.zero();
   const int64_t n = a.n_rows, nblk = (n + 15) / 16;
@@ -486,20 +475,18 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 64>::NW), (Bwd32<NH, 64>::OCC)) voi
     put_piece(o, 1, x);
     load_vec<kH>(vecs + oz, g, z);
     acc.run(
-        wl + oz, vecs + oz, tile, o, z, a.ln, a.eps, ln,
+        wl + oz, vecs + oz, tile, o, z, a.ln, a.eps, ln, wave,
         [&](float (&y)[kNF]) {
 #pragma unroll
-          for (int i = 0; i < kNF; ++i) y[i] = valid ? go[i] * sgn : 0.f;
+          for (int i = 0; i < kNF; ++i) y[i] = valid ? go[i] : 0.f;
         },
-        [&](float (&d)[kNF], const Op<false, kH>& od) {
+        [&](float (&d)[kNF], const Op<false, kH>& od, float sg) {
 #pragma unroll
           for (int i = 0; i < kNF; ++i) {
             gi[i] = 0.f;
-            gi[kNF + i] = go[i] * sgn;
+            gi[kNF + i] = go[i];
           }
-          gemm_wt<false, kH, 64, ACC_ADD>(wl + oz, od, gi, ln);
-#pragma unroll
-          for (int i = 0; i < 2 * kNF; ++i) gi[i] *= sgn;
+          gemm_wt<false, kH, 64, ACC_ADD>(wl + oz, od, gi, ln, sg);
           if (valid) {
             store_row<kH>(a.g_a + row * kH, g, *reinterpret_cast<float(*)[kNF]>(gi));
             store_row<kH>(a.g_x + row * kH, g, *reinterpret_cast<float(*)[kNF]>(gi + kNF));

@@ -314,11 +314,12 @@ __device__ __forceinline__ void make_op(const float (&x)[W / 4], Op<false, W>& o
 // wf(t, mb, part) with part 0, 1, 2 = h, m, l (BF16: part 0 only).
 // How a product meets its accumulator: it starts from it (the large part
 // products are summed onto it), starts from zero and replaces it, or starts
-// from zero and is added at the end (one rounding; eight more registers).
+// from zero and is added at the end times `sc` (one rounding; eight more
+// registers).
 enum Acc { ACC_START, ACC_SET, ACC_ADD };
 
 template <int MB, int T, Acc MODE, class F>
-__device__ __forceinline__ void gemm_op(F&& wf, const Op<true, 32 * T>& in, float (&acc)[4 * MB]) {
+__device__ __forceinline__ void gemm_op(F&& wf, const Op<true, 32 * T>& in, float (&acc)[4 * MB], float = 1.f) {
   v4f c[MB];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb)
@@ -336,11 +337,15 @@ __device__ __forceinline__ void gemm_op(F&& wf, const Op<true, 32 * T>& in, floa
   }
 }
 template <int MB, int T, Acc MODE, class F>
-__device__ __forceinline__ void gemm_op(F&& wf, const Op<false, 32 * T>& in, float (&acc)[4 * MB]) {
+__device__ __forceinline__ void gemm_op(F&& wf, const Op<false, 32 * T>& in, float (&acc)[4 * MB], float sc = 1.f) {
   // two output blocks at a time: each weight part is read once, and no two
   // consecutive matrix instructions add to the same registers.  With one chunk
   // the large product comes last on the small ones' sum (one rounding at full
-  // size, no second accumulator).
+  // size, no second accumulator).  The instruction then cuts the small sum's low
+  // bits downwards, a mean error of 2^-27 of a term where two sums leave 2^-33;
+  // an adjoint, whose errors add up over millions of rows in the bias gradients,
+  // takes its rows by random sign (row_sign), so this one cancels as well (in two
+  // sums the width-32 deep layers take 3% longer and are no nearer to FP64).
   constexpr int G = MB % 2 == 0 ? 2 : 1;
   constexpr bool ONE = T == 1;
 #pragma unroll
@@ -386,10 +391,8 @@ __device__ __forceinline__ void gemm_op(F&& wf, const Op<false, 32 * T>& in, flo
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float& o = acc[4 * (m0 + i) + r];
-        if constexpr (ONE)
-          o = MODE == ACC_SET ? cs[i][r] : o + cs[i][r];
-        else
-          o = MODE == ACC_ADD ? o + (ch[i][r] + cs[i][r]) : ch[i][r] + cs[i][r];
+        const float v = ONE ? cs[i][r] : ch[i][r] + cs[i][r];
+        o = MODE == ACC_ADD ? fmaf(sc, v, o) : ONE && MODE == ACC_START ? o + v : v;
       }
     }
   }
@@ -531,23 +534,25 @@ __device__ __forceinline__ v8bf tr_read8(const char* base, int r0) {
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// Row `row` of an operand into a tile (FP32: three tiles, part_bytes apart).
+// Row `row` of an operand into a tile (FP32: three tiles, part_bytes apart), its
+// sign bits flipped by `flip`.
 template <int W>
-__device__ __forceinline__ void put_row(char* __restrict__ t, int g, int sz, const v8bf (&v)[W / 32]) {
+__device__ __forceinline__ void put_row(char* __restrict__ t, int g, int sz, const v8bf (&v)[W / 32], uint32_t flip) {
 #pragma unroll
   for (int b = 0; b < W / 16; ++b) {
     const v4u q = __builtin_bit_cast(v4u, v[b / 2]);
-    *reinterpret_cast<u32x2*>(t + ((4 * b + g) ^ sz) * 8) = b % 2 ? u32x2{q[2], q[3]} : u32x2{q[0], q[1]};
+    const u32x2 c = b % 2 ? u32x2{q[2], q[3]} : u32x2{q[0], q[1]};
+    *reinterpret_cast<u32x2*>(t + ((4 * b + g) ^ sz) * 8) = u32x2{c[0] ^ flip, c[1] ^ flip};
   }
 }
 template <int W>
 __device__ __forceinline__ void stage_op(void* __restrict__ tile, int part_bytes, int row, int g,
-                                         const Op<false, W>& o) {
+                                         const Op<false, W>& o, uint32_t flip = 0) {
   const int sz = stg_swz<W>(row);
   char* t = reinterpret_cast<char*>(tile) + row * (W * 2);
-  put_row<W>(t, g, sz, o.h);
-  put_row<W>(t + part_bytes, g, sz, o.m);
-  put_row<W>(t + 2 * part_bytes, g, sz, o.l);
+  put_row<W>(t, g, sz, o.h, flip);
+  put_row<W>(t + part_bytes, g, sz, o.m, flip);
+  put_row<W>(t + 2 * part_bytes, g, sz, o.l, flip);
 }
 
 // Weights row major in LDS for both products: gemm_wn reads W's operand,
@@ -612,9 +617,9 @@ __device__ __forceinline__ void gemm_wn(const char* __restrict__ w, const Op<BF,
 // acc += W^T in (ACC_SET: acc = W^T in)
 template <bool BF, int M, int K, Acc MODE = ACC_START>
 __device__ __forceinline__ void gemm_wt(const char* __restrict__ w, const Op<BF, M>& in, float (&acc)[K / 4],
-                                        int lane) {
+                                        int lane, float sc = 1.f) {
   gemm_op<K / 16, M / 32, MODE>([&](int t, int mb, int part) { return wt_frag<M, K>(w, t, mb, part, lane); }, in,
-                                acc);
+                                acc, sc);
 }
 
 // All fragments of a small FP32 matrix, read ahead of the product.
