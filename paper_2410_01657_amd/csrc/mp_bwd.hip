@@ -543,7 +543,8 @@ struct EdgeBwdF32Cfg {
   static constexpr size_t WTILE = 2 * (Dw::TILE_G + Dw::TILE_A);  // (gm, u) and (gh, e) of one wave
   static constexpr size_t VECS = 2 * H * sizeof(float);
   static constexpr size_t CARRY = NW * H * sizeof(float);
-  static constexpr size_t LDS = NW * WTILE + 2 * WB + CARRY + VECS;
+  static constexpr size_t ODD = 16;  // infinite weights met, per wave
+  static constexpr size_t LDS = NW * WTILE + 2 * WB + CARRY + VECS + ODD;
   static_assert(LDS <= kLdsLimit && NW * WTILE >= NW * H * H * sizeof(float), "weights, tiles, final sums in LDS");
 };
 
@@ -575,13 +576,14 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
   char* tG1 = tA2 + Dw::TILE_A;
   char* tA1 = tG1 + Dw::TILE_G;
   char* wl = reinterpret_cast<char*>(smem) + NW * C::WTILE;
-  stage_wrow<false, H, H>(wl, a.w1c.w);
-  stage_wrow<false, H, H>(wl + C::WB, a.w2.w);
-  float* vecs = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + C::LDS - C::VECS);
-  float* carry = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + C::LDS - C::VECS - C::CARRY) + wave * H +
-                 g * (H / 4);
+  float* carry = reinterpret_cast<float*>(wl + 2 * C::WB) + wave * H + g * (H / 4);
+  float* vecs = reinterpret_cast<float*>(wl + 2 * C::WB + C::CARRY);
+  int* odd = reinterpret_cast<int*>(wl + 2 * C::WB + C::CARRY + C::VECS);
+  const bool o1 = stage_wrow<false, H, H>(wl, a.w1c.w), o2 = stage_wrow<false, H, H>(wl + C::WB, a.w2.w);
+  note_odd(odd, o1 || o2);
   for (int t = threadIdx.x; t < 2 * H; t += blockDim.x) vecs[t] = t < H ? a.b2[t] : (a.ln ? a.lng[t - H] : 0.f);
   __syncthreads();
+  const bool wodd = read_odd(odd);
 
   const DevGraph& gr = a.g;
   const TileSched ts = tile_sched(gr.n_tiles);
@@ -616,7 +618,7 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       const int64_t k = base + j;
       const bool valid = k < e1;
       const int64_t kk = valid ? k : e_last;
-      const int ri = ic.ri;
+      const int ri = ic.ri, sj = ic.sj;
       const float inv_d = 1.f / (float)ic.md;
       const bool last = valid && ic.nx != ri;
       const int key = valid ? ri + 1 : -1;
@@ -651,6 +653,7 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       make_op(u, o);
       stage_op<H>(tA2, Dw::AP, ln & 15, ln >> 4, o);
       gemm_wn<false, H, H>(w2, o, mp, ln);
+      const bool m_nan = mp[0] != mp[0];
 
       // gradient reaching e', LayerNorm adjoint (mp becomes gm)
 #pragma unroll
@@ -707,6 +710,34 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       d1.add(tG1, tA1, ln);
 #pragma unroll
       for (int i = 0; i < NF; ++i) t[i] *= sg;
+      if (wodd || __ballot(m_nan || gE[0] != gE[0])) {
+        // an infinite operand: this block's g_e and g_h with FP32 instructions
+        float z[NF], u1[1][NF], w[NF];
+        auto w2m = [&](int) { return a.w2.w; };
+        load_row<H>(reinterpret_cast<const float*>(a.e_in) + kk * H, g, w);
+        load_row<H>(a.P + (int64_t)ri * H, g, z);
+        load_row<H>(a.Q + (int64_t)sj * H, g, t);
+#pragma unroll
+        for (int i = 0; i < NF; ++i) z[i] += t[i];
+        gemm_exact<H, H>(a.w1c.w, w, z, lane);
+        exact_forward<H, 1>(w2m, [&](int) { return vecs; }, z, u1, lane);
+        load_row<H>(a.g_a + (int64_t)ri * H, g, t);
+        if (a.g_e_out) {
+          load_row<H>(reinterpret_cast<const float*>(a.g_e_out) + kk * H, g, w);
+        } else {
+#pragma unroll
+          for (int i = 0; i < NF; ++i) w[i] = 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < NF; ++i) {
+          const float v = t[i] * inv_d + w[i];
+          t[i] = valid ? v : 0.f;
+          gE[i] = AM ? (valid ? w[i] : 0.f) : t[i];
+        }
+        if (a.ln) ln_adjoint<H>(z, t, vecs + H, a.eps, lane);
+        exact_adjoint<H, 1>(w2m, u1, t, lane);
+        gemm_exact_t<H, H>(a.w1c.w, t, gE, lane);
+      }
       nx.settle();
       in.settle();
       if (valid) {

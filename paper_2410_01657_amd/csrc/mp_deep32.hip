@@ -60,16 +60,22 @@ struct Fwd32 {
   static constexpr size_t VECS = n_vecs<NH>() * kH * sizeof(float);
   static constexpr int NW = WB > 50 * 1024 ? 8 : 4;  // two workgroups per CU, or four and more
 
-  static __device__ __forceinline__ void stage(char* __restrict__ w, float* __restrict__ v,
+  // odd: see note_odd
+  static __device__ __forceinline__ void stage(char* __restrict__ w, float* __restrict__ v, int* __restrict__ odd,
                                                const float* __restrict__ theta, int ln) {
-    stage_wfrag<false, kH, K>(w, WView{theta, K, 0});
+    bool o = stage_wfrag<false, kH, K>(w, WView{theta, K, 0});
 #pragma unroll
-    for (int l = 0; l <= NH; ++l) stage_wfrag<false, kH, kH>(w + W0 + l * W1, WView{theta + off_hid(K, l), kH, 0});
+    for (int l = 0; l <= NH; ++l)
+      o |= stage_wfrag<false, kH, kH>(w + W0 + l * W1, WView{theta + off_hid(K, l), kH, 0});
     stage_vecs<NH>(v, theta, K, ln);
+    note_odd(odd, o);
   }
-  // y = [LN] MLP(in)
+  // y = [LN] MLP(in); again(x): the input rows once more, for a block with an
+  // infinite operand (wodd: every block)
+  template <class F>
   static __device__ __forceinline__ void run(const char* __restrict__ w, const float* __restrict__ v,
-                                             const Op<false, K>& in, int ln, float eps, int lane, float (&y)[kNF]) {
+                                             const Op<false, K>& in, int ln, float eps, int lane, float (&y)[kNF],
+                                             bool wodd, const float* __restrict__ theta, F&& again) {
     const int g = lane >> 4;
     float u[kNF];
     load_vec<kH>(v, g, u);
@@ -82,6 +88,14 @@ struct Fwd32 {
       gemm_wf<false, kH, kH>(w + W0 + l * W1, u, y, lane);
 #pragma unroll
       for (int i = 0; i < kNF; ++i) u[i] = y[i];
+    }
+    if (wodd || any_nan(y[0])) {
+      float x[K / 4], ue[NH + 1][kNF];
+      again(x);
+      load_vec<kH>(v, g, y);
+      gemm_exact<kH, K>(WView{theta, K, 0}, x, y, lane);
+      exact_forward<kH, NH + 1>([&](int l) { return WView{theta + off_hid(K, l), kH, 0}; },
+                                [&](int l) { return v + (l + 1) * kH; }, y, ue, lane);
     }
     if (ln) {
       float mean, rstd, gam[kNF], bet[kNF];
@@ -99,6 +113,10 @@ template <int K>
 __device__ __forceinline__ void put_piece(Op<false, K>& o, int p, const float (&x)[kNF]) {
   split3_8(x, o.h[p], o.m[p], o.l[p]);
 }
+template <int K>
+__device__ __forceinline__ void load_piece(float (&x)[K], int p, const float* __restrict__ row, int g) {
+  load_row<kH>(row, g, *reinterpret_cast<float(*)[kNF]>(&x[p * kNF]));
+}
 
 // Eq. 4a-b, as k_edge_fwd: one row-aligned tile at a time per wave, the
 // aggregate by a segmented scan over the 16 edges of a block.
@@ -109,8 +127,10 @@ __global__ __launch_bounds__((64 * Fwd32<NH, 96>::NW), 4) void k_deep32_edge_fwd
   char* wl = reinterpret_cast<char*>(smem);
   float* vecs = reinterpret_cast<float*>(wl + F::WB);
   float* carry = vecs + n_vecs<NH>() * kH + (threadIdx.x / 64) * kH + (threadIdx.x / 16 % 4) * kNF;
-  F::stage(wl, vecs, a.theta, a.ln);
+  int* odd = reinterpret_cast<int*>(vecs + (n_vecs<NH>() + F::NW) * kH);
+  F::stage(wl, vecs, odd, a.theta, a.ln);
   __syncthreads();
+  const bool wodd = read_odd(odd);
   const DevGraph& gr = a.g;
   const int lane = lane_id(), j = lane & 15, g = lane >> 4;
   const TileSched ts = tile_sched(gr.n_tiles);
@@ -140,7 +160,11 @@ __global__ __launch_bounds__((64 * Fwd32<NH, 96>::NW), 4) void k_deep32_edge_fwd
       put_piece(in, 0, xi);
       put_piece(in, 1, xj);
       put_piece(in, 2, ev);
-      F::run(wl + oz, vecs + oz, in, a.ln, a.eps, lane, m);
+      F::run(wl + oz, vecs + oz, in, a.ln, a.eps, lane, m, wodd, a.theta, [&](float (&x)[3 * kNF]) {
+        load_piece(x, 0, a.x + (int64_t)ri * kH, g);
+        load_piece(x, 1, a.x + (int64_t)sj * kH, g);
+        load_piece(x, 2, a.e_in + (valid ? k : e_last) * kH, g);
+      });
 #pragma unroll
       for (int i = 0; i < kNF; ++i) ev[i] += m[i];
       if (valid) store_row<kH>(a.e_out + k * kH, g, ev);
@@ -159,8 +183,10 @@ __global__ __launch_bounds__((64 * Fwd32<NH, 64>::NW), 4) void k_deep32_node_fwd
   extern __shared__ uint4 smem[];
   char* wl = reinterpret_cast<char*>(smem);
   float* vecs = reinterpret_cast<float*>(wl + F::WB);
-  F::stage(wl, vecs, a.theta, a.ln);
+  int* odd = reinterpret_cast<int*>(vecs + n_vecs<NH>() * kH);
+  F::stage(wl, vecs, odd, a.theta, a.ln);
   __syncthreads();
+  const bool wodd = read_odd(odd);
   const int lane = lane_id(), j = lane & 15, g = lane >> 4;
   const int64_t n = a.n_rows, nblk = (n + 15) / 16;
   for (int64_t blk = (int64_t)blockIdx.x * F::NW + threadIdx.x / 64; blk < nblk; blk += (int64_t)gridDim.x * F::NW) {
@@ -173,7 +199,10 @@ __global__ __launch_bounds__((64 * Fwd32<NH, 64>::NW), 4) void k_deep32_node_fwd
     Op<false, 64> in;
     put_piece(in, 0, s);
     put_piece(in, 1, x);
-    F::run(wl + oz, vecs + oz, in, a.ln, a.eps, lane, y);
+    F::run(wl + oz, vecs + oz, in, a.ln, a.eps, lane, y, wodd, a.theta, [&](float (&again)[2 * kNF]) {
+      load_piece(again, 0, a.src_a + rr * kH, g);
+      load_piece(again, 1, a.src_b + rr * kH, g);
+    });
 #pragma unroll
     for (int i = 0; i < kNF; ++i) y[i] += x[i];
     if (row < n) store_row<kH>(a.out + row * kH, g, y);
@@ -199,7 +228,7 @@ struct Bwd32 {
   // the shallowest eight waves, two per SIMD; the others take the registers
   // (and more layers the LDS) of one: at two per SIMD they spill
   static constexpr int OCC = NH <= (K == kH ? 0 : 1) ? 2 : 1, NW = 4 * OCC;
-  static constexpr size_t LDS = NW * (WTILE + CARRY) + WB + VECS;
+  static constexpr size_t LDS = NW * (WTILE + CARRY) + WB + VECS + NW * sizeof(int);
   static_assert(LDS <= kLdsLimit && NW * WTILE >= NW * kH * K * sizeof(float), "weights, tiles, final sums in LDS");
   static_assert(NW * WTILE >= 16 * NW * kH * sizeof(float), "row sums in LDS");
 
@@ -215,20 +244,34 @@ struct Bwd32 {
     for (int i = 0; i < kNF; ++i) dga[i] = dbe[i] = 0.f;
   }
   // w0: the first matrix's columns used here (K of them, leading dimension ld)
-  static __device__ __forceinline__ void stage(char* __restrict__ w, float* __restrict__ v,
+  static __device__ __forceinline__ void stage(char* __restrict__ w, float* __restrict__ v, int* __restrict__ odd,
                                                const float* __restrict__ theta, const float* __restrict__ w0, int ld,
                                                int ln) {
-    stage_wrow<false, kH, K>(w, WView{w0, ld, 0});
+    bool o = stage_wrow<false, kH, K>(w, WView{w0, ld, 0});
 #pragma unroll
-    for (int l = 0; l <= NH; ++l) stage_wrow<false, kH, kH>(w + W0 + l * W1, WView{theta + off_hid(ld, l), kH, 0});
+    for (int l = 0; l <= NH; ++l)
+      o |= stage_wrow<false, kH, kH>(w + W0 + l * W1, WView{theta + off_hid(ld, l), kH, 0});
     stage_vecs<NH>(v, theta, ld, ln);
+    note_odd(odd, o);
+  }
+  // For a block with an infinite operand: from the input x, z less W0 x and the
+  // output's gradient t, the first pre-activation's gradient in t.
+  static __device__ __forceinline__ void exact(const float* __restrict__ theta, const float* __restrict__ w0, int ld,
+                                               const float* __restrict__ v, const float (&x)[K / 4], float (&z)[kNF],
+                                               float (&t)[kNF], int ln, float eps, int lane) {
+    float u[NH + 1][kNF];
+    auto W = [&](int l) { return WView{theta + off_hid(ld, l), kH, 0}; };
+    gemm_exact<kH, K>(WView{w0, ld, 0}, x, z, lane);
+    exact_forward<kH, NH + 1>(W, [&](int l) { return v + (l + 1) * kH; }, z, u, lane);
+    if (ln) ln_adjoint<kH>(z, t, v + (NH + 2) * kH, eps, lane);
+    exact_adjoint<kH, NH + 1>(W, u, t, lane);
   }
 
   // Forward and adjoint of one block.  z: what the first matrix's product is
   // added to (bias, or P + Q); gE(y): the gradient arriving at the output, zero
-  // on absent rows, asked for once the forward is done; done(d, o, sg): called
+  // on absent rows, asked for once the forward is done; done(d, o, sg, nan): called
   // with the first pre-activation's gradient d and its operand, both times the
-  // row's sign sg.
+  // row's sign sg; nan: the forward met an infinite operand (or a NaN).
   template <class GE, class DONE>
   __device__ __forceinline__ void run(const char* __restrict__ w, const float* __restrict__ v, char* __restrict__ tile,
                                       const Op<false, K>& in, float (&z)[kNF], int ln, float eps, int lane,
@@ -260,6 +303,7 @@ struct Bwd32 {
     }
     wf.template load_t<kH, kH>(w + W0 + NH * W1, lane);
     __builtin_amdgcn_sched_barrier(0);
+    const bool nan = z[0] != z[0];
     gE(y);
     const float sg = row_sign(y[0]);  // gm carries it from here on
     const uint32_t flip = dw_flip(wave, sg);
@@ -321,7 +365,7 @@ struct Bwd32 {
     wave_lds_fence();
     typename Dw0::Frags d0f;
     Dw0::load(d0f, tG, tile, lane);
-    done(gm, o, sg);
+    done(gm, o, sg, nan);
     d0.mma(d0f);
   }
 
@@ -360,8 +404,10 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) voi
   char* wl = reinterpret_cast<char*>(smem) + B::NW * B::WTILE;
   float* vecs = reinterpret_cast<float*>(wl + B::WB);
   float* carry = reinterpret_cast<float*>(wl + B::WB + B::VECS) + wave * kH + g * kNF;
-  B::stage(wl, vecs, a.theta, a.theta + 64, 96, a.ln);
+  int* odd = reinterpret_cast<int*>(wl + B::WB + B::VECS + B::NW * B::CARRY);
+  B::stage(wl, vecs, odd, a.theta, a.theta + 64, 96, a.ln);
   __syncthreads();
+  const bool wodd = read_odd(odd);
   const DevGraph& gr = a.g;
   const TileSched ts = tile_sched(gr.n_tiles);
   B acc;
@@ -396,7 +442,7 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) voi
         const int64_t k = base + j;
         const bool valid = k < e1;
         const int64_t kk = valid ? k : e_last;
-        const int ri = ic.ri;
+        const int ri = ic.ri, sj = ic.sj;
         const float inv_d = 1.f / (float)ic.md;
         const bool last = valid && ic.nx != ri;
         const int key = valid ? ri + 1 : -1;
@@ -427,12 +473,35 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) voi
                 ge[i] = a.am ? go[i] : y[i];
               }
             },
-            [&](float (&d)[kNF], const Op<false, kH>& o, float sg) {
+            [&](float (&d)[kNF], const Op<false, kH>& o, float sg, bool nan) {
               gemm_wt<false, kH, kH, ACC_ADD>(wl + oz, o, ge, ln, sg);
               settle();
               in.settle();
 #pragma unroll
               for (int i = 0; i < kNF; ++i) d[i] *= sg;
+              if (wodd || __ballot(nan || ge[0] != ge[0])) {
+                float x[kNF], zz[kNF], t[kNF];
+                load_row<kH>(a.e_in + kk * kH, g, x);
+                load_row<kH>(a.P + (int64_t)ri * kH, g, zz);
+                load_row<kH>(a.Q + (int64_t)sj * kH, g, t);
+#pragma unroll
+                for (int i = 0; i < kNF; ++i) zz[i] += t[i];
+                load_row<kH>(a.g_a + (int64_t)ri * kH, g, d);
+                if (a.g_e_out) {
+                  load_row<kH>(a.g_e_out + kk * kH, g, t);
+                } else {
+#pragma unroll
+                  for (int i = 0; i < kNF; ++i) t[i] = 0.f;
+                }
+#pragma unroll
+                for (int i = 0; i < kNF; ++i) {
+                  const float s = d[i] * inv_d + t[i];
+                  d[i] = valid ? s : 0.f;
+                  ge[i] = a.am ? t[i] : d[i];
+                }
+                B::exact(a.theta, a.theta + 64, 96, vecs, x, zz, d, a.ln, a.eps, lane);
+                gemm_exact_t<kH, kH>(WView{a.theta + 64, 96, 0}, d, ge, lane);
+              }
               if (valid) {
                 store_row<kH>(a.g_e_in + k * kH, g, ge);
                 store_row<kH>(a.g_h + k * kH, g, d);
@@ -456,8 +525,10 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 64>::NW), (Bwd32<NH, 64>::OCC)) voi
   char* tile = reinterpret_cast<char*>(smem) + wave * B::WTILE;
   char* wl = reinterpret_cast<char*>(smem) + B::NW * B::WTILE;
   float* vecs = reinterpret_cast<float*>(wl + B::WB);
-  B::stage(wl, vecs, a.theta, a.theta, 64, a.ln);
+  int* odd = reinterpret_cast<int*>(wl + B::WB + B::VECS + B::NW * B::CARRY);
+  B::stage(wl, vecs, odd, a.theta, a.theta, 64, a.ln);
   __syncthreads();
+  const bool wodd = read_odd(odd);
   B acc;
   acc.zero();
   const int64_t n = a.n_rows, nblk = (n + 15) / 16;
@@ -480,13 +551,28 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 64>::NW), (Bwd32<NH, 64>::OCC)) voi
 #pragma unroll
           for (int i = 0; i < kNF; ++i) y[i] = valid ? go[i] : 0.f;
         },
-        [&](float (&d)[kNF], const Op<false, kH>& od, float sg) {
+        [&](float (&d)[kNF], const Op<false, kH>& od, float sg, bool nan) {
 #pragma unroll
           for (int i = 0; i < kNF; ++i) {
             gi[i] = 0.f;
             gi[kNF + i] = go[i];
           }
           gemm_wt<false, kH, 64, ACC_ADD>(wl + oz, od, gi, ln, sg);
+          if (wodd || __ballot(nan || gi[0] != gi[0])) {
+            float again[2 * kNF], zz[kNF];
+            load_piece(again, 0, a.a_star + rr * kH, g);
+            load_piece(again, 1, a.x + rr * kH, g);
+            load_vec<kH>(vecs, g, zz);
+            load_row<kH>(a.g_out + rr * kH, g, d);
+#pragma unroll
+            for (int i = 0; i < kNF; ++i) {
+              gi[i] = 0.f;
+              gi[kNF + i] = d[i];
+              d[i] = valid ? d[i] : 0.f;
+            }
+            B::exact(a.theta, a.theta, 64, vecs, again, zz, d, a.ln, a.eps, lane);
+            gemm_exact_t<kH, 64>(WView{a.theta, 64, 0}, d, gi, lane);
+          }
           if (valid) {
             store_row<kH>(a.g_a + row * kH, g, *reinterpret_cast<float(*)[kNF]>(gi));
             store_row<kH>(a.g_x + row * kH, g, *reinterpret_cast<float(*)[kNF]>(gi + kNF));
@@ -501,7 +587,7 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 64>::NW), (Bwd32<NH, 64>::OCC)) voi
 template <int NH>
 hipError_t edge_fwd(const DeepEdgeArgs& a, int64_t waves, hipStream_t s) {
   using F = Fwd32<NH, 96>;
-  constexpr size_t lds = F::WB + F::VECS + F::NW * kH * sizeof(float);
+  constexpr size_t lds = F::WB + F::VECS + F::NW * (kH * sizeof(float) + sizeof(int));
   auto kern = k_deep32_edge_fwd<NH>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(kern, dim3((unsigned)((waves + F::NW - 1) / F::NW)), dim3(64 * F::NW), lds, s, a);
@@ -510,7 +596,7 @@ hipError_t edge_fwd(const DeepEdgeArgs& a, int64_t waves, hipStream_t s) {
 template <int NH>
 hipError_t node_fwd(const DeepRowArgs& a, int64_t waves, hipStream_t s) {
   using F = Fwd32<NH, 64>;
-  constexpr size_t lds = F::WB + F::VECS;
+  constexpr size_t lds = F::WB + F::VECS + F::NW * sizeof(int);
   auto kern = k_deep32_node_fwd<NH>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(kern, dim3((unsigned)((waves + F::NW - 1) / F::NW)), dim3(64 * F::NW), lds, s, a);

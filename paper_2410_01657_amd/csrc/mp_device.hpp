@@ -254,8 +254,16 @@ __device__ __forceinline__ void gemm_bf16(const uint4* __restrict__ frag, const 
 // sum takes K/32 roundings instead of the FP32 instruction's K/4: against FP64 (K = 64, normal values) the rms error is 4.6e-8 of the result,
 // 1.4e-7 with v_mfma_f32_16x16x4f32.  The rate: six v_mfma_f32_16x16x32_bf16
 // take 96 cycles for what eight 32-cycle FP32 instructions do, and unlike
-// those they issue beside vector instructions.  Infinite inputs give NaN
-// (their remainder is inf - inf), as a NaN input does.
+// those they issue beside vector instructions.
+//
+// An infinite operand has no parts: its remainder is inf - inf, so every output
+// it reaches is NaN.  The kernels look for one (a NaN among their results, or an
+// infinite weight met while staging, stage_wfrag) and then compute that block of
+// 16 rows again with FP32 instructions on the matrices in device memory
+// (gemm_exact), whose infinities are those of FP32 arithmetic.  That branch is
+// not taken for finite values and its test is one or two compares per block (1% of
+// the edge kernels' time).  Only sums over rows keep the parts' result: a weight
+// gradient with an infinite factor is not finite either way.
 //
 // Op<BF, W>: a W-wide row in the row-block layout as matrix operand; lane
 // value q of chunk t is in[8t + q].
@@ -439,11 +447,21 @@ __device__ __forceinline__ void split_w8(const float* x, v8bf& h, v8bf& m, v8bf&
   }
 }
 
+template <int N>
+__device__ __forceinline__ bool any_inf(const float (&x)[N]) {
+  bool r = false;
+#pragma unroll
+  for (int i = 0; i < N; ++i) r |= fabsf(x[i]) == __builtin_inff();
+  return r;
+}
+
 // Stage the M x K matrix w as fragments: 16-byte piece (mb*(K/32) + t)*64 +
 // lane holds A[16 mb + lane%16][32t + 16(q/4) + 4(lane/16) + q%4], q = 0..7;
 // the parts M*K*2 bytes apart.  All threads of the workgroup; no barrier.
+// Returns whether this thread met an infinite weight (FP32).
 template <bool BF, int M, int K>
-__device__ __forceinline__ void stage_wfrag(void* __restrict__ dst, const WView& w) {
+__device__ __forceinline__ bool stage_wfrag(void* __restrict__ dst, const WView& w) {
+  bool odd = false;
   constexpr int T = K / 32;
   uint4* d = reinterpret_cast<uint4*>(dst);
   const bool al = w_aligned(w);
@@ -464,10 +482,56 @@ __device__ __forceinline__ void stage_wfrag(void* __restrict__ dst, const WView&
     split_w8<BF>(x, h, m, l);
     d[e] = __builtin_bit_cast(uint4, h);
     if constexpr (!BF) {
+      odd |= any_inf(x);
       d[e + M * K / 8] = __builtin_bit_cast(uint4, m);
       d[e + 2 * (M * K / 8)] = __builtin_bit_cast(uint4, l);
     }
   }
+  return odd;
+}
+
+// Whether any thread of the workgroup staged an infinite weight: each wave leaves
+// its own answer in `slots` (one int per wave), and reads all after the barrier
+// that ends the staging.
+__device__ __forceinline__ void note_odd(int* __restrict__ slots, bool odd) {
+  const uint64_t any = __ballot(odd);
+  if ((threadIdx.x & 63) == 0) slots[threadIdx.x / 64] = any != 0;
+}
+__device__ __forceinline__ bool read_odd(const int* __restrict__ slots) {
+  int o = 0;
+  for (int w = 0; w < (int)blockDim.x / 64; ++w) o |= slots[w];
+  return __builtin_amdgcn_readfirstlane(o) != 0;
+}
+__device__ __forceinline__ bool any_nan(float x) { return __ballot(x != x) != 0; }
+
+// acc += A in with FP32 instructions, A(m, k) read from device memory, of any
+// alignment.  For the rare block with an infinite operand.
+template <int M, int K, class F>
+__device__ __forceinline__ void gemm_exact_of(F&& el, const float (&in)[K / 4], float (&acc)[M / 4], int lane) {
+  const int l = lane + opaque_zero(), i = l & 15, k = l >> 4;  // no address held outside the branch
+  v4f c[M / 16];
+#pragma unroll
+  for (int mb = 0; mb < M / 16; ++mb) c[mb] = v4f{acc[4 * mb], acc[4 * mb + 1], acc[4 * mb + 2], acc[4 * mb + 3]};
+#pragma unroll
+  for (int s = 0; s < K / 4; ++s) {
+    if (s % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // few weights in flight
+#pragma unroll
+    for (int mb = 0; mb < M / 16; ++mb)
+      c[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(el(16 * mb + i, 16 * (s / 4) + 4 * k + s % 4), in[s], c[mb], 0, 0, 0);
+  }
+#pragma unroll
+  for (int mb = 0; mb < M / 16; ++mb) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[4 * mb + r] = c[mb][r];
+  }
+}
+template <int M, int K>  // W M x K
+__device__ __forceinline__ void gemm_exact(const WView& w, const float (&in)[K / 4], float (&acc)[M / 4], int lane) {
+  gemm_exact_of<M, K>([&](int m, int k) { return w.p[(int64_t)m * w.ld + k]; }, in, acc, lane);
+}
+template <int M, int K>  // W^T in
+__device__ __forceinline__ void gemm_exact_t(const WView& w, const float (&in)[M / 4], float (&acc)[K / 4], int lane) {
+  gemm_exact_of<K, M>([&](int m, int k) { return w.p[(int64_t)k * w.ld + m]; }, in, acc, lane);
 }
 
 // acc += W in, W staged by stage_wfrag.
@@ -567,9 +631,10 @@ __host__ __device__ constexpr int wrow_part(int M, int K) { return wrow_at(M, K)
 __host__ __device__ constexpr size_t wrow_bytes(int M, int K, bool bf) { return size_t(wrow_part(M, K)) * (bf ? 1 : 3); }
 
 // Stage the M x K matrix w (not transposed).  All threads of the workgroup; no
-// barrier.
+// barrier.  Returns whether this thread met an infinite weight (FP32).
 template <bool BF, int M, int K>
-__device__ __forceinline__ void stage_wrow(void* __restrict__ dst, const WView& w) {
+__device__ __forceinline__ bool stage_wrow(void* __restrict__ dst, const WView& w) {
+  bool odd = false;
   const bool al = w_aligned(w);
   for (int e = threadIdx.x; e < M * K / 8; e += blockDim.x) {
     const int row = e / (K / 8), c = e % (K / 8) * 2;  // chunks c, c + 1
@@ -586,7 +651,9 @@ __device__ __forceinline__ void stage_wrow(void* __restrict__ dst, const WView& 
       *reinterpret_cast<u32x2*>(t + q * wrow_part(M, K) + (c ^ sz) * 8) = u32x2{v[0], v[1]};
       *reinterpret_cast<u32x2*>(t + q * wrow_part(M, K) + ((c + 1) ^ sz) * 8) = u32x2{v[2], v[3]};
     }
+    if constexpr (!BF) odd |= any_inf(x);
   }
+  return odd;
 }
 // One operand fragment of W (chunk t of K, output block mb of M) and of W^T
 // (chunk t of M, output block mb of K).
@@ -693,6 +760,50 @@ __device__ __forceinline__ void ln_stats(const float (&v)[W / 4], float eps, flo
   }
   const float var = row_sum(q) * (1.f / W);
   rstd = 1.f / sqrtf(var + eps);
+}
+
+// The Linears after an MLP's first, with gemm_exact: u[l] = ELU(z), z = bias(l) +
+// W(l) u[l] for l = 0 .. NL - 1, and back: g = (W(l)^T g) ELU'(u[l]).
+template <int H, int NL, class FW, class FB>
+__device__ __forceinline__ void exact_forward(FW&& W, FB&& bias, float (&z)[H / 4], float (&u)[NL][H / 4], int lane) {
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+#pragma unroll
+    for (int i = 0; i < H / 4; ++i) u[l][i] = elu(z[i]);
+    load_vec<H>(bias(l), lane >> 4, z);
+    gemm_exact<H, H>(W(l), u[l], z, lane);
+  }
+}
+template <int H, int NL, class FW>
+__device__ __forceinline__ void exact_adjoint(FW&& W, const float (&u)[NL][H / 4], float (&g)[H / 4], int lane) {
+#pragma unroll
+  for (int l = NL - 1; l >= 0; --l) {
+    float t[H / 4];
+#pragma unroll
+    for (int i = 0; i < H / 4; ++i) t[i] = 0.f;
+    gemm_exact_t<H, H>(W(l), g, t, lane);
+#pragma unroll
+    for (int i = 0; i < H / 4; ++i) g[i] = t[i] * elu_deriv_from_value(u[l][i]);
+  }
+}
+// Adjoint of y = LN(z) for the gradient g at y, in place.
+template <int W>
+__device__ __forceinline__ void ln_adjoint(float (&z)[W / 4], float (&g)[W / 4], const float* __restrict__ gain,
+                                           float eps, int lane) {
+  float mean, rstd, gam[W / 4], s1 = 0.f, s2 = 0.f;
+  ln_stats<W>(z, eps, mean, rstd);
+  load_vec<W>(gain, lane >> 4, gam);
+#pragma unroll
+  for (int i = 0; i < W / 4; ++i) {
+    z[i] = (z[i] - mean) * rstd;
+    g[i] *= gam[i];
+    s1 += g[i];
+    s2 += g[i] * z[i];
+  }
+  s1 = row_sum(s1) * (1.f / W);
+  s2 = row_sum(s2) * (1.f / W);
+#pragma unroll
+  for (int i = 0; i < W / 4; ++i) g[i] = rstd * (g[i] - s1 - z[i] * s2);
 }
 
 // --------------------------------------------- small first/last Linears

@@ -122,7 +122,7 @@ __global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (fwd_o
     int64_t n_rows, const float* __restrict__ x, WSrc wa, WSrc wb, const float* __restrict__ b1,
     float* __restrict__ P, float* __restrict__ Q, int n_main, TileJob tj) {
   constexpr int NF = H / 4, MB = H / 16;
-  constexpr bool RAW = raw_weights(H, BF);
+  constexpr bool RAW = raw_weights(H, BF), SPLIT = RAW && !BF;
   constexpr size_t FB = RAW ? w_bytes(H, H, BF) : frag_bytes(H, H, BF);
   static_assert(2 * FB <= kProjLdsBudget, "both matrices in LDS");
   extern __shared__ uint4 smem[];
@@ -130,14 +130,16 @@ __global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (fwd_o
     tile_bounds(tj, (int64_t)((int)blockIdx.x - n_main) * blockDim.x + threadIdx.x);
     return;
   }
+  int* odd = reinterpret_cast<int*>(smem + 2 * FB / 16);  // SPLIT: per wave
   if constexpr (RAW) {
-    stage_wfrag<BF, H, H>(smem, wa.w);
-    stage_wfrag<BF, H, H>(smem + FB / 16, wb.w);
+    const bool oa = stage_wfrag<BF, H, H>(smem, wa.w), ob = stage_wfrag<BF, H, H>(smem + FB / 16, wb.w);
+    if constexpr (!BF) note_odd(odd, oa || ob);
   } else {
     stage_to_lds(smem, wa.frag, FB);
     stage_to_lds(smem + FB / 16, wb.frag, FB);
   }
   __syncthreads();
+  const bool wodd = SPLIT && read_odd(odd);
   const char* fr = reinterpret_cast<const char*>(smem);
   const int lane = lane_id(), j = lane & 15, g = lane >> 4;
   const int nw = blockDim.x / 64;
@@ -165,6 +167,14 @@ __global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (fwd_o
       make_op(xv, xo);
       gemm_wf<BF, H, H>(frb, xo, p, lane);
       gemm_wf<BF, H, H>(frb + FB, xo, q, lane);
+      if (SPLIT && (wodd || any_nan(p[0]))) {
+        load_row<H>(x + std::min<int64_t>(row, n_rows - 1) * H, g, xv);
+        load_vec<H>(b1, g, p);
+#pragma unroll
+        for (int i = 0; i < NF; ++i) q[i] = 0.f;
+        gemm_exact<H, H>(wa.w, xv, p, lane);
+        gemm_exact<H, H>(wb.w, xv, q, lane);
+      }
     } else {
       gemm<BF, MB, MB>(fr, xv, p, lane);
       gemm<BF, MB, MB>(fr + FB, xv, q, lane);
@@ -186,10 +196,11 @@ static hipError_t launch_proj_t(int64_t n_rows, const float* x, const WSrc& wa, 
   constexpr int NW = fwd_waves<BF>(2 * FB);
   const int n_main = fit_grid(grid, NW, H > 64 ? 2 : fwd_occ<H, BF>(2 * FB), 2 * FB);
   const int n_tile = (int)((tj.n_tiles + 1 + 64 * NW - 1) / (64 * NW));
-  if (2 * FB > 64 * 1024)
-    (void)hipFuncSetAttribute((const void*)k_proj<H, BF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2 * FB));
-  hipLaunchKernelGGL((k_proj<H, BF>), dim3(n_main + n_tile), dim3(64 * NW), 2 * FB, s, n_rows, x, wa, wb, b1, P, Q,
-                     n_main, tj);
+  constexpr size_t lds = 2 * FB + (raw_weights(H, BF) && !BF ? NW * sizeof(int) : 0);
+  if (lds > 64 * 1024)
+    (void)hipFuncSetAttribute((const void*)k_proj<H, BF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((k_proj<H, BF>), dim3(n_main + n_tile), dim3(64 * NW), lds, s, n_rows, x, wa, wb, b1, P, Q, n_main,
+                     tj);
   return hipGetLastError();
 }
 
@@ -226,7 +237,7 @@ __global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (H > 6
                                                   int ln, float eps, void* __restrict__ e_out,
                                                   float* __restrict__ a_out) {
   constexpr int NF = H / 4, MB = H / 16;
-  constexpr bool RAW = raw_weights(H, BF);
+  constexpr bool RAW = raw_weights(H, BF), SPLIT = RAW && !BF;
   constexpr size_t FB = RAW ? w_bytes(H, H, BF) : frag_bytes(H, H, BF);
   static_assert(2 * FB <= kEdgeLdsBudget, "both matrices in LDS");
   extern __shared__ uint4 smem[];
@@ -239,14 +250,16 @@ __global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (H > 6
   float* carry = vecs + 3 * H + (threadIdx.x / 64) * H + (threadIdx.x / 16 % 4) * (H / 4);
   for (int t = threadIdx.x; t < 3 * H; t += blockDim.x)
     vecs[t] = t < H ? b2[t] : (ln ? (t < 2 * H ? lng[t - H] : lnb[t - 2 * H]) : 0.f);
+  int* odd = reinterpret_cast<int*>(vecs + (3 + blockDim.x / 64) * H);  // SPLIT: per wave
   if constexpr (RAW) {
-    stage_wfrag<BF, H, H>(smem, w1c.w);
-    stage_wfrag<BF, H, H>(smem + FB / 16, w2.w);
+    const bool o1 = stage_wfrag<BF, H, H>(smem, w1c.w), o2 = stage_wfrag<BF, H, H>(smem + FB / 16, w2.w);
+    if constexpr (!BF) note_odd(odd, o1 || o2);
   } else {
     stage_to_lds(smem, w1c.frag, FB);
     stage_to_lds(smem + FB / 16, w2.frag, FB);
   }
   __syncthreads();
+  const bool wodd = SPLIT && read_odd(odd);
   const int lane = lane_id(), j = lane & 15, g = lane >> 4;
   const int nw = blockDim.x / 64;
   const TileSched ts = tile_sched(gr.n_tiles);
@@ -316,6 +329,15 @@ __global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (H > 6
         gemm_wf<BF, H, H>(frb + FB, h, m, lane);
       else
         gemm<BF, MB, MB>(frb + FB, h, m, lane);
+      if (SPLIT && (wodd || any_nan(m[0]))) {
+        float u1[1][NF];
+        load_row<H>(P + (int64_t)ri * H, g, m);
+        load_row<H>(Q + (int64_t)sj * H, g, q);
+#pragma unroll
+        for (int i = 0; i < NF; ++i) m[i] += q[i];
+        gemm_exact<H, H>(w1c.w, ev, m, lane);
+        exact_forward<H, 1>([&](int) { return w2.w; }, [&](int) { return vb; }, m, u1, lane);
+      }
       if (ln) {
         float mean, rstd, gam[NF], bet[NF];
         ln_stats<H>(m, eps, mean, rstd);
@@ -367,8 +389,8 @@ static hipError_t launch_edge_fwd_t(const DevGraph& g, const float* P, const flo
                                     float eps, void* e_out, float* a_out, int grid, hipStream_t s) {
   constexpr size_t FB = raw_weights(H, BF) ? w_bytes(H, H, BF) : frag_bytes(H, H, BF);
   constexpr int NW = fwd_waves<BF>(2 * FB);
-  // fragments, 3 per-feature vectors, per-wave carries
-  constexpr size_t lds = 2 * FB + (3 + NW) * H * sizeof(float);
+  // fragments, 3 per-feature vectors, per-wave carries, infinite weights met
+  constexpr size_t lds = 2 * FB + (3 + NW) * H * sizeof(float) + (raw_weights(H, BF) && !BF ? NW * sizeof(int) : 0);
   if (lds > 64 * 1024)
     (void)hipFuncSetAttribute((const void*)k_edge_fwd<H, BF, AM, DQ, ES>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
@@ -510,7 +532,8 @@ struct MlpFwdCfg {
   // matrix is then read from LDS and only W1 from L2
   static constexpr bool LDS_F0 = !LDS_FRAG && F0 > 0 && F0 + SMALL + VECS <= kRowMlpLdsMax;
   static constexpr size_t FRAG_LDS = LDS_FRAG ? F0 + F1 : (LDS_F0 ? F0 : 0);
-  static constexpr size_t LDS = FRAG_LDS + SMALL + VECS;
+  static constexpr bool SPLIT = RAW && !BF;
+  static constexpr size_t LDS = FRAG_LDS + SMALL + VECS + (SPLIT ? NW * sizeof(int) : 0);
 };
 
 // OB: the H-wide output is stored as BF16 (the edge encoder's output, an
@@ -531,9 +554,12 @@ __global__ __launch_bounds__((64 * MlpFwdCfg<H, KIN, TIN, TOUT, BF>::NW), (MlpFw
     const int q = t / H, f = t % H;
     vecs[t] = q == 0 ? a.b0[f] : q == 1 ? (TOUT ? 0.f : a.b1[f]) : q == 2 ? (a.ln ? a.lng[f] : 0.f) : (a.ln ? a.lnb[f] : 0.f);
   }
+  int* odd = reinterpret_cast<int*>(vecs + 4 * H);  // SPLIT: per wave
   if constexpr (C::RAW) {
-    if constexpr (!TIN) stage_wfrag<BF, H, KIN>(smem, WView{a.W0, KIN, 0});
-    if constexpr (!TOUT) stage_wfrag<BF, H, H>(smem + C::F0 / 16, WView{a.W1, H, 0});
+    bool o = false;
+    if constexpr (!TIN) o |= stage_wfrag<BF, H, KIN>(smem, WView{a.W0, KIN, 0});
+    if constexpr (!TOUT) o |= stage_wfrag<BF, H, H>(smem + C::F0 / 16, WView{a.W1, H, 0});
+    if constexpr (!BF) note_odd(odd, o);
     f0 = reinterpret_cast<const char*>(smem);
     f1 = f0 + C::F0;
   } else if constexpr (C::LDS_FRAG) {
@@ -550,6 +576,7 @@ __global__ __launch_bounds__((64 * MlpFwdCfg<H, KIN, TIN, TOUT, BF>::NW), (MlpFw
     f1 = reinterpret_cast<const char*>(a.frag1);
   }
   __syncthreads();
+  const bool wodd = C::SPLIT && read_odd(odd);
   const int lane = lane_id(), j = lane & 15, g = lane >> 4;
   const int nw = blockDim.x / 64;
   const int64_t n = a.n_rows, nblk = (n + 15) / 16, stride = (int64_t)gridDim.x * nw;
@@ -578,6 +605,19 @@ __global__ __launch_bounds__((64 * MlpFwdCfg<H, KIN, TIN, TOUT, BF>::NW), (MlpFw
     } else {
       gemm<BF, MB, KB>(f0 + opaque_zero(), cur.in, z, lane);
     }
+    // the first pre-activation with FP32 instructions, from the rows in memory
+    auto exact_z = [&](float (&zz)[NF]) {
+      MlpFwdIn<H, KIN, TIN, TOUT> again;
+      again.load(a, std::min<int64_t>(row, n - 1), g, false);
+      load_vec<H>(vecs, g, zz);
+      if constexpr (TIN)
+        small_in_linear<H>(small, again.in, g, zz);
+      else
+        gemm_exact<H, KIN>(WView{a.W0, KIN, 0}, again.in, zz, lane);
+    };
+    if constexpr (C::SPLIT && TOUT) {
+      if (wodd || any_nan(z[0])) exact_z(z);
+    }
 #pragma unroll
     for (int i = 0; i < NF; ++i) z[i] = elu(z[i]);
     if constexpr (TOUT) {
@@ -600,6 +640,13 @@ __global__ __launch_bounds__((64 * MlpFwdCfg<H, KIN, TIN, TOUT, BF>::NW), (MlpFw
         gemm_wf<BF, H, H>(f1 + opaque_zero(), z, y, lane);
       else
         gemm<BF, MB, MB>(f1 + opaque_zero(), z, y, lane);
+      if constexpr (C::SPLIT) {
+        if (wodd || any_nan(y[0])) {
+          float u1[1][NF];
+          exact_z(y);
+          exact_forward<H, 1>([&](int) { return WView{a.W1, H, 0}; }, [&](int) { return vecs + H; }, y, u1, lane);
+        }
+      }
       if (a.ln) {
         float mean, rstd, gm[NF], bt[NF];
         load_vec<H>(vb + 2 * H, g, gm);
