@@ -193,8 +193,20 @@ typedef struct {
   int32_t H;          /* hidden width: 32, 64 or 128 */
   int32_t layernorm;  /* 1: LayerNorm on the output of both MLPs */
   int32_t halo;       /* 1: consistent (Eq. 4c-d); 0: "None" mode, halo skipped */
-  int32_t gemm_dtype; /* MP_F32 or MP_BF16 (operands rounded to nearest even) */
+  int32_t gemm_dtype; /* MP_F32 (see below) or MP_BF16 (operands rounded to nearest even) */
   float ln_eps;
+  /* MP_F32, here and in the MLPs and deep layers below: FP32 operands and
+   * sums.  At H = 64 and below (not the deep widths 8 and 16), and in the
+   * weight gradients at H = 128, a product may run on the BF16 matrix unit,
+   * from three BF16 parts of each operand that hold all its 24 bits; the three
+   * smallest of the nine part products are left out.  One product alone is
+   * then within 2^-22 of its exact value (an FP32 rounding: 2^-24); sums of 32
+   * and more have fewer roundings and come out nearer to the exact value (rms
+   * 3.9e-8 of a sum of 32 terms, 1.0e-7 with FP32 instructions; 5.0e-8 and
+   * 1.4e-7 at 64).  Operands below 2^-109 lose what is below 2^-133, and a
+   * result within 1% of the largest FP32 value may overflow.  Infinities and
+   * NaN are those of FP32 arithmetic, but for a weight gradient that an
+   * infinite value reaches: it is not finite, infinite or NaN. */
   /* Schedule (0 = library default): edges per row-aligned tile of the edge
    * kernels (16..4096), and the persistent workgroup counts of the forward
    * and adjoint edge kernels (1..65536).  Results are bitwise reproducible
