@@ -9,10 +9,13 @@ round, and for FP32 at H > 64, where 8 puts two waves of the split adjoint on
 each SIMD and 4 gives one wave all the registers it wants; BF16 at H > 64
 accepts both and has one form) and the tile order
 of the edge forward (edge_fwd_queue: fixed round robin, or per-XCD atomic
-tile counters).  The tuner times the library's own
+tile counters).  The library's defaults (0, which for FP32 depend on the
+graph's size) are among the candidates, so a tuned layer is no slower than an
+untuned one.  The tuner times the library's own
 forward and backward on the actual graph and keeps the fastest, cached per
-(arch, H, GEMM type, edge-state type, LayerNorm, rows, edges, sub-graphs)
-in a JSON file
+(arch, H, GEMM type, edge-state type, LayerNorm, rows, edges, sub-graphs) and
+library build (a schedule is as good as the kernels it was timed on) in a JSON
+file
 ($MPLAYER_TUNE_CACHE, default ~/.cache/mplayer/tune.json).  Every schedule
 computes the same function; they differ only in the grouping of
 floating-point sums (and the forward's tile order not even in that).
@@ -26,24 +29,27 @@ the caller and keeps a separate entry for it; tuned_edge_state searches it
 too, for callers that accept BF16 edge states.
 """
 
+import functools
+import hashlib
 import json
 import os
 
 import torch
 
+from ._lib import LIB_PATH
 from .ops import layer_backward, layer_cfg, layer_forward
 
-TILE_EDGES = (64, 128, 256, 512)
-EDGE_GRIDS = (512, 1024, 2048)
-EDGE_BWD_GRIDS = (256, 512, 1024)
+TILE_EDGES = (0, 64, 128, 256, 512)
+EDGE_GRIDS = (0, 512, 1024, 2048)
+EDGE_BWD_GRIDS = (0, 256, 512, 1024)
 EDGE_FWD_QUEUES = (0, 1)
 SCHEDULE_FIELDS = ("tile_edges", "edge_grid", "edge_bwd_grid", "edge_bwd_waves", "edge_fwd_queue")
 
 
 def edge_bwd_waves_options(H, gemm):
-    """Waves per workgroup of the edge adjoint the library accepts (the
-    fused kernel: 8 only with BF16 GEMMs; at H > 64 both)."""
-    return (4, 8) if (gemm == "bf16" and H <= 64) or H > 64 else (4,)
+    """Waves per workgroup of the edge adjoint that are different kernels (8
+    with BF16 GEMMs at H <= 64 and with FP32 above; elsewhere one form)."""
+    return (4, 8) if (gemm == "bf16") == (H <= 64) else (4,)
 
 
 def candidates(H=64, gemm="bf16"):
@@ -67,10 +73,22 @@ def _cache_path():
                           os.path.join(os.path.expanduser("~"), ".cache", "mplayer", "tune.json"))
 
 
+@functools.lru_cache(maxsize=None)
+def _library_id(path, size, mtime_ns):
+    with open(path, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:16]
+
+
+def library_id():
+    """Identifies the built kernels: a hash of the library file."""
+    st = os.stat(LIB_PATH)
+    return _library_id(LIB_PATH, st.st_size, st.st_mtime_ns)
+
+
 def _key(dg, H, layernorm, gemm, estate="f32"):
     arch = torch.cuda.get_device_properties(dg.device).gcnArchName.split(":")[0]
     es = "" if estate == "f32" else f"|es{estate}"
-    return f"{arch}|H{H}|{gemm}{es}|ln{int(layernorm)}|N{dg.n_rows}|E{dg.n_edges}|R{dg.host.R}|v2"
+    return f"{arch}|H{H}|{gemm}{es}|ln{int(layernorm)}|N{dg.n_rows}|E{dg.n_edges}|R{dg.host.R}|{library_id()}"
 
 
 def _load():
