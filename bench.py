@@ -337,8 +337,8 @@ def main():
     from mpinputs import CONFIGS, ModelSpec, make_inputs
     from paper_2410_01657_amd.autotune import tuned_schedule
     from paper_2410_01657_amd.model import Problem
-    from paper_2410_01657_amd.roofline import (PEAK, PEAK_HBM, PEAK_VALU, bound_of, deep_kernels,
-                                               layer_kernels, layer_roof_seconds)
+    from paper_2410_01657_amd.roofline import (PEAK_HBM, bound_of, deep_kernels, deep_peak, launched_kernels,
+                                               layer_roof_seconds, matrix_peak)
 
     wl = dict(WORKLOADS[a.workload])
     cfg = CONFIGS[a.workload]
@@ -392,18 +392,16 @@ def main():
         of whichever roof bounds that kernel."""
         gemm, estate = PATHS[name]
         work = (deep_kernels(N, E, G, M, spec.H, spec.n_hidden, spec.n_layers) if deep
-                else layer_kernels(N, E, G, M, spec.H, gemm, spec.n_layers, estate))
+                else launched_kernels(N, E, G, M, spec.H, gemm, spec.n_layers, estate))
         kern = res[name]["kernels"]
         dom = max((k for k in kern if k in work), key=lambda k: kern[k]["ms_total"])
         w = work[dom]
         avg_s = kern[dom]["ms_avg"] * 1e-3
-        if deep and w.flops / PEAK_VALU > w.bytes / PEAK_HBM:
-            r = {"bound": "alu", "achieved": w.flops / avg_s / 1e12, "peak": PEAK_VALU / 1e12, "unit": "TFLOP/s"}
-        elif bound_of(w, gemm) == "hbm":
+        unit, peak = deep_peak(spec.H, spec.n_hidden) if deep else ("mfma", matrix_peak(dom, spec.H, gemm))
+        if bound_of(w, gemm, peak) == "hbm":
             r = {"bound": "hbm", "achieved": w.bytes / avg_s / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s"}
         else:
-            r = {"bound": "mfma", "achieved": w.flops / avg_s / 1e12, "peak": PEAK[gemm] / 1e12,
-                 "unit": "TFLOP/s"}
+            r = {"bound": unit, "achieved": w.flops / avg_s / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s"}
         r["frac"] = r["achieved"] / r["peak"]
         r.update({"kernel": dom, "ms_avg": kern[dom]["ms_avg"], "algorithmic_GB": w.bytes / 1e9,
                   "algorithmic_GFLOP": w.flops / 1e9})

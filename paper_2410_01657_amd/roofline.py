@@ -18,6 +18,8 @@ from dataclasses import dataclass
 # MI355X published peaks
 PEAK_HBM = 8.0e12          # bytes/s
 PEAK = {"f32": 157.3e12, "bf16": 2.5e15}   # dense MFMA flop/s by operand type
+# FP32 products formed from three BF16 parts per operand take six BF16 products
+PEAK_F32_PARTS = PEAK["bf16"] / 6
 # FP32 vector ALU: 256 CUs x 4 SIMDs x 16 lanes x 2 flops (FMA) x 2 (packed
 # FP32) x 2.4 GHz.  The library is built without packed FP32 operations, so
 # its own ceiling is half of this (78.6 TFLOP/s).
@@ -30,12 +32,10 @@ class Work:
     flops: float
 
 
-def edge_bwd_split(H):
-    """Whether the edge adjoint is counted in two passes (per-edge factors, then
-    the weight-gradient sums): at widths above 64, where the FP32 kernels run
-    so.  The BF16 kernel forms both in one launch (edge_bwd); its count keeps
-    the two passes' roofs."""
-    return H > 64
+def edge_bwd_split(H, gemm="f32"):
+    """Whether the edge adjoint runs in two passes (per-edge factors, then the
+    weight-gradient sums): FP32 at widths above 64."""
+    return H > 64 and gemm == "f32"
 
 
 def node_bwd_split(H):
@@ -44,6 +44,14 @@ def node_bwd_split(H):
 
 def gq_split(H, gemm):
     return H > 64 and gemm == "f32"
+
+
+def matrix_peak(kernel, H, gemm):
+    """Matrix flop/s that a layer kernel's products can reach: FP32 products
+    run from BF16 parts at H <= 64 (but for the node update's adjoint and the
+    sender-side pass) and in the weight-gradient passes above."""
+    parts = kernel.endswith("_dw") if H > 64 else kernel in ("proj", "edge_fwd", "node_fwd", "edge_bwd")
+    return PEAK_F32_PARTS if gemm == "f32" and parts else PEAK[gemm]
 
 
 def layer_kernels(N, E, G, M, H, gemm="bf16", n_layers=1, estate="f32"):
@@ -56,13 +64,14 @@ def layer_kernels(N, E, G, M, H, gemm="bf16", n_layers=1, estate="f32"):
     e, e' and their gradients ("bf16": 2 bytes per value).
 
     At H > 64 the edge and node adjoints (and, in FP32, the sender-side
-    pass) run split: the first pass recomputes the MLP and forms the input
+    pass) are counted split: the first pass recomputes the MLP and forms the input
     gradients, a second pass (edge_dw / node_dw / gq_dw) sums the weight
     gradients from per-row factors the first pass stored.  The products are
     then counted where they run; the stored factors are implementation
     traffic, and each second pass is charged only the bytes of the factors
     it must read (one launch of edge_dw / node_dw / gq_dw stands for all of
-    that pass's launches in a layer)."""
+    that pass's launches in a layer).  The BF16 edge adjoint forms its weight
+    gradients itself: launched_kernels has it as it runs."""
     f = 4.0                              # bytes per FP32 value
     fe = 2.0 if estate == "bf16" else 4.0  # bytes per edge-state value
     fh = 2.0 if gemm == "bf16" else 4.0  # bytes per g_h value (and per stored factor)
@@ -84,7 +93,7 @@ def layer_kernels(N, E, G, M, H, gemm="bf16", n_layers=1, estate="f32"):
         # g_P, g_h (through reverse edges), x, g_x -> g_x ; 2 (2H x H) products per node
         "gq": Work(E * (H * fh + 4) + N * (4 * H * f + 4), N * 2 * 4 * H * H),
     }
-    if edge_bwd_split(H):
+    if H > 64:
         # pass 1: recompute (W1c, W2) and the input-gradient products (W2^T, W1c^T)
         w["edge_bwd"] = Work(w["edge_bwd"].bytes, E * 2 * 4 * H * H)
         # pass 2: dW1c = sum g_h e^T, dW2 = sum gm u^T (+ LayerNorm sums)
@@ -100,6 +109,16 @@ def layer_kernels(N, E, G, M, H, gemm="bf16", n_layers=1, estate="f32"):
     return w
 
 
+def launched_kernels(N, E, G, M, H, gemm="bf16", n_layers=1, estate="f32"):
+    """layer_kernels by the launches that run: in BF16 at H > 64 one kernel
+    forms the edge adjoint and its weight gradients, so its products are
+    edge_bwd's and no factor is stored or read."""
+    w = layer_kernels(N, E, G, M, H, gemm, n_layers, estate)
+    if "edge_dw" in w and not edge_bwd_split(H, gemm):
+        w["edge_bwd"] = Work(w["edge_bwd"].bytes, w["edge_bwd"].flops + w.pop("edge_dw").flops)
+    return w
+
+
 # kernels that belong to the message-passing layers (the rest of a model
 # step: encoders, decoder, loss, edge inputs)
 LAYER_KERNEL_NAMES = ("pack", "tiles", "proj", "edge_fwd", "halo", "halo_adj", "node_fwd", "node_bwd",
@@ -110,17 +129,16 @@ def layer_roof_seconds(N, E, G, M, H, gemm, n_layers, hbm=None, peak=None, estat
     """Lower bound on the time of the message-passing layers' forward and
     adjoint: every kernel of every layer at the higher of its HBM floor
     (algorithmic bytes / bandwidth) and its product floor (flops / matrix
-    peak of the operand type).  hbm / peak default to the published MI355X
-    figures."""
+    peak of the operand type, FP32 from parts where the kernel runs so).
+    hbm / peak default to the published MI355X figures."""
     hbm = PEAK_HBM if hbm is None else hbm
-    peak = PEAK[gemm] if peak is None else peak
-    w = layer_kernels(N, E, G, M, H, gemm, n_layers, estate)
-    return n_layers * sum(max(k.bytes / hbm, k.flops / peak) for k in w.values())
+    w = launched_kernels(N, E, G, M, H, gemm, n_layers, estate)
+    return n_layers * sum(max(k.bytes / hbm, k.flops / (peak or matrix_peak(n, H, gemm))) for n, k in w.items())
 
 
-def bound_of(work, gemm):
+def bound_of(work, gemm, peak=None):
     """'hbm' or 'mfma': whichever roof takes longer for this work."""
-    return "hbm" if work.bytes / PEAK_HBM >= work.flops / PEAK[gemm] else "mfma"
+    return "hbm" if work.bytes / PEAK_HBM >= work.flops / (peak or PEAK[gemm]) else "mfma"
 
 
 def mlp_flops(K, H, NH, O):
@@ -128,23 +146,53 @@ def mlp_flops(K, H, NH, O):
     return 2.0 * (K * H + NH * H * H + O * H)
 
 
+def deep_split(H, NH):
+    """Whether a deep layer runs on the kernels of its own width (8: FP32 FMAs,
+    32: the matrix unit, from BF16 parts), whose adjoint has the first edge
+    Linear's node parts split off and forms its weight gradients itself."""
+    return H in (8, 32) and NH <= 5
+
+
+def deep_peak(H, NH):
+    """(bound, flop/s) of the deep kernels' products."""
+    return ("mfma", PEAK_F32_PARTS) if H == 32 and deep_split(H, NH) else ("alu", PEAK_VALU)
+
+
 def deep_kernels(N, E, G, M, H, NH, n_layers=1):
     """Per launch, one layer of the narrow deep-MLP kernels (keys match the
-    library's profile names).  Bytes: the layer's inputs and outputs only
-    (each row once); the per-row adjoint records the kernels keep in HBM are
-    an implementation choice and not counted.  Flops: the MLP products
-    (recomputed forward plus transposed products in the adjoint kernels; one
-    product per weight per row in the weight-gradient sums)."""
+    library's profile names).  Bytes: the layer's inputs and outputs and what
+    passes between its launches (each row once); the per-row adjoint records
+    of H = 16 and deeper MLPs are an implementation choice and not counted.
+    Flops: the MLP products (recomputed forward, transposed products, and one
+    product per weight per row for the weight gradients, where they run)."""
     f = 4.0
     ge = (n_layers - 1) / n_layers if n_layers > 1 else 1.0
     fe, fn = mlp_flops(3 * H, H, NH, H), mlp_flops(2 * H, H, NH, H)
-    return {
+    halo = Work(M * 2 * H * f + 4 * (M + G + 1), 0.0)
+    w = {
         "deep_edge_fwd": Work(E * (2 * H * f + 5) + N * (3 * H * f + 4), E * fe),
-        "halo": Work(M * 2 * H * f + 4 * (M + G + 1), 0.0),
+        "halo": halo,
+        "halo_adj": halo,
         "deep_node_fwd": Work(N * 3 * H * f, N * fn),
-        "deep_node_bwd": Work(N * 5 * H * f, N * 2 * fn),
-        "deep_edge_bwd": Work(E * ((2 + ge) * H * f + 5) + N * (3 * H * f + 4), E * 2 * fe),
-        "deep_gather": Work(E * (H * f + 4) + N * (3 * H * f + 4), 0.0),
-        "deep_edge_dw": Work(0.0, E * fe),
-        "deep_node_dw": Work(0.0, N * fn),
     }
+    if deep_split(H, NH):
+        w.update({
+            # x -> P = W0a x + b0, Q = W0b x
+            "proj": Work(N * 3 * H * f, N * 2 * 2 * H * H),
+            "deep_node_bwd": Work(N * 5 * H * f, N * 3 * fn),
+            # e, [g_e'], P_i, Q_j, g_a_i -> g_e, g_h (and at H = 32 g_P)
+            "deep_edge_bwd": Work(E * ((3 + ge) * H * f + 9) + N * (4 if H == 32 else 3) * H * f,
+                                  E * 3 * mlp_flops(H, H, NH, H)),
+            # g_h through the reverse edges (g_P given, or summed here as well), x, g_x -> g_x
+            "gq": Work(E * ((1 if H == 32 else 2) * H * f + 4) + N * ((4 if H == 32 else 3) * H * f + 4),
+                       N * 2 * 4 * H * H),
+        })
+    else:
+        w.update({
+            "deep_node_bwd": Work(N * 5 * H * f, N * 2 * fn),
+            "deep_edge_bwd": Work(E * ((2 + ge) * H * f + 5) + N * (3 * H * f + 4), E * 2 * fe),
+            "deep_gather": Work(E * (H * f + 4) + N * (3 * H * f + 4), 0.0),
+            "deep_edge_dw": Work(0.0, E * fe),
+            "deep_node_dw": Work(0.0, N * fn),
+        })
+    return w
