@@ -193,16 +193,17 @@ int row_grid(int64_t N) { return (int)std::max<int64_t>(1, std::min<int64_t>(102
 int row_bwd_grid(int64_t N) { return (int)std::max<int64_t>(1, std::min<int64_t>(512, (N + 255) / 256)); }
 
 // Packed fragments of one layer, in this order:
-// W1a W1b | W1c W2 W2^T W1c^T | Wn1 Wn2 Wn2^T Wn1^T
+// [W1a W1b | W1c W2 without raw_weights] | Wn1 Wn2 Wn2^T Wn1^T
 struct LayerFrags {
   size_t f1, f2;  // bytes of an H x H and an H x 2H matrix
   size_t proj, edge, node, total;
   LayerFrags(int H, bool bf) {
     f1 = frag_bytes(H, H, bf);
     f2 = frag_bytes(H, 2 * H, bf);
+    const size_t own = raw_weights(H, bf) ? 0 : 2 * f1;
     proj = 0;
-    edge = proj + 2 * f1;
-    node = edge + 4 * f1;
+    edge = proj + own;
+    node = edge + own;
     total = align_up(node + 2 * f2 + 2 * f1);
   }
 };
@@ -290,10 +291,6 @@ PackJobs layer_jobs(const mp_layer_cfg* c, const mp_layer_params* p, const Layer
   add_job(J, H, 2 * H, view(p->Wn1, 2 * H, 0, 0), F.node);                 // Wn1
   add_job(J, H, H, view(p->Wn2, H, 0, 0), F.node + F.f2);                  // Wn2
   if (bwd) {
-    if (!raw) {
-      add_job(J, H, H, view(p->We2, H, 0, 1), F.edge + 2 * F.f1);          // W2^T
-      add_job(J, H, H, view(p->We1, 3 * H, 2 * H, 1), F.edge + 3 * F.f1);  // W1c^T
-    }
     add_job(J, H, H, view(p->Wn2, H, 0, 1), F.node + F.f2 + F.f1);         // Wn2^T
     add_job(J, 2 * H, H, view(p->Wn1, 2 * H, 0, 1), F.node + F.f2 + 2 * F.f1);  // Wn1^T
   }
@@ -325,10 +322,12 @@ struct LayerWeights {
   WSrc w1a, w1b, w1c, w2;
   LayerWeights(const mp_layer_cfg* c, const mp_layer_params* p, void* ws, const LayerWs& W) {
     const int H = c->H;
-    w1a = WSrc{WView{p->We1, 3 * H, 0}, ws_at(ws, W.fr.proj)};
-    w1b = WSrc{WView{p->We1 + H, 3 * H, 0}, ws_at(ws, W.fr.proj + W.fr.f1)};
-    w1c = WSrc{WView{p->We1 + 2 * H, 3 * H, 0}, ws_at(ws, W.fr.edge)};
-    w2 = WSrc{WView{p->We2, H, 0}, ws_at(ws, W.fr.edge + W.fr.f1)};
+    const bool raw = raw_weights(H, c->gemm_dtype == MP_BF16);
+    auto frag = [&](size_t off) -> const void* { return raw ? nullptr : ws_at(ws, off); };
+    w1a = WSrc{WView{p->We1, 3 * H, 0}, frag(W.fr.proj)};
+    w1b = WSrc{WView{p->We1 + H, 3 * H, 0}, frag(W.fr.proj + W.fr.f1)};
+    w1c = WSrc{WView{p->We1 + 2 * H, 3 * H, 0}, frag(W.fr.edge)};
+    w2 = WSrc{WView{p->We2, H, 0}, frag(W.fr.edge + W.fr.f1)};
   }
 };
 

@@ -157,7 +157,7 @@ struct EdgeBwdArgs {
   const void* e_in;
   const void* g_e_out;   // may be null
   const float* g_a;      // gradient of a (after the adjoint halo sum)
-  WSrc w1c, w2;          // with packed fragments: W1c, W2, W2^T, W1c^T, consecutive from w1c.frag
+  WSrc w1c, w2;          // packed fragments (split form): W1c, W2, consecutive from w1c.frag
   const float* b2;
   const float* lng;
   const float* lnb;
