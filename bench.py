@@ -133,8 +133,9 @@ def copy_calibration():
 # SHA-256 of the kernel's source files and is used only while they are
 # unchanged (else traffic is null).
 TRAFFIC_GLOB = "profiles/*_hbm_traffic.md"
-KERNEL_SOURCES = {"edge_bwd": ("mp_bwd.hip", "mp_adjoint.hpp", "mp_device.hpp", "mp_kernels.hpp"),
-                  "edge_fwd": ("mp_fwd.hip", "mp_device.hpp", "mp_kernels.hpp")}
+_EDGE_SOURCES = ("mp_edge.hpp", "mp_exact.hpp", "mp_device.hpp", "mp_kernels.hpp")
+KERNEL_SOURCES = {"edge_bwd": ("mp_bwd.hip", "mp_adjoint.hpp") + _EDGE_SOURCES,
+                  "edge_fwd": ("mp_fwd.hip",) + _EDGE_SOURCES}
 
 
 def sources_sha256(kernel):

@@ -205,8 +205,9 @@ typedef struct {
    * 3.9e-8 of a sum of 32 terms, 1.0e-7 with FP32 instructions; 5.0e-8 and
    * 1.4e-7 at 64).  Operands below 2^-109 lose what is below 2^-133, and a
    * result within 1% of the largest FP32 value may overflow.  Infinities and
-   * NaN are those of FP32 arithmetic, but for a weight gradient that an
-   * infinite value reaches: it is not finite, infinite or NaN. */
+   * NaN come out of a product as FP32 arithmetic has them, but for a weight
+   * gradient that an infinite value reaches: it is not finite, infinite or
+   * NaN. */
   /* Schedule (0 = library default): edges per row-aligned tile of the edge
    * kernels (16..4096), and the persistent workgroup counts of the forward
    * and adjoint edge kernels (1..65536).  Results are bitwise reproducible

@@ -1,9 +1,10 @@
-// Pieces shared by the adjoint kernels: weight gradients of FP32 products, the
-// segmented receiver sum of an edge block, sums over a workgroup's rows.
+// Pieces shared by the adjoint kernels: weight gradients of FP32 products, sums
+// over a workgroup's rows.
 #pragma once
 #include <algorithm>
 
 #include "mp_device.hpp"
+#include "mp_exact.hpp"
 #include "mp_kernels.hpp"
 
 namespace mp {
@@ -11,11 +12,12 @@ namespace mp {
 constexpr size_t kLdsLimit = 160 * 1024 - 1024;
 constexpr int kWaves = 4;  // waves per workgroup in the row-MLP lock-step kernels
 
-// Sum a per-lane row-block vector over all 16*NW rows of the workgroup (16
-// lanes x NW waves) in a fixed order and write the W sums to dst, added in FP64
-// (once per kernel; in FP32 these 16*NW roundings were most of the error of a
-// bias gradient: 280k edges at H = 64, db1 1.2e-4 against 0.4e-4).  Uses
-// `scratch` (at least 16*NW*W floats of LDS); contains barriers.
+// Sum a per-lane row-block vector over all 16*NW rows of the workgroup of NW waves
+// (16 lanes each) in a fixed order and write the W sums to dst, added in FP64 (once
+// per kernel; in FP32 these 16*NW roundings were most of the error of a bias
+// gradient: 280k edges at H = 64, db1 1.2e-4 against 0.5e-4), each column by as many
+// threads as there are.  Uses `scratch` (at least 16*NW*W floats of LDS, aligned to
+// 8 bytes); contains barriers.
 template <int W, int NW = kWaves>
 __device__ __forceinline__ void block_sum_vec(const float (&v)[W / 4], float* __restrict__ scratch,
                                               float* __restrict__ dst, int wave, int lane) {
@@ -24,12 +26,23 @@ __device__ __forceinline__ void block_sum_vec(const float (&v)[W / 4], float* __
 #pragma unroll
   for (int i = 0; i < W / 4; ++i) scratch[(wave * 16 + j) * W + 16 * (i / 4) + 4 * g + (i % 4)] = v[i];
   __syncthreads();
-  for (int t = threadIdx.x; t < W; t += blockDim.x) {
-    double s = 0.;
+  constexpr int P = 64 * NW / W > 0 ? 64 * NW / W : 1, R = 16 * NW / P;  // threads per column, rows each
+  static_assert(64 * NW >= W && R * P == 16 * NW, "a thread per column and more");
+  const int c = threadIdx.x % W, q = threadIdx.x / W;
+  double s = 0.;
 #pragma unroll 8
-    for (int r = 0; r < 16 * NW; ++r) s += scratch[r * W + t];
-    dst[t] = (float)s;
+  for (int r = q * R; r < (q + 1) * R; ++r) s += scratch[r * W + c];
+  if constexpr (P > 1) {
+    double* part = reinterpret_cast<double*>(scratch);
+    __syncthreads();
+    part[q * W + c] = s;
+    __syncthreads();
+    if (q == 0) {
+#pragma unroll
+      for (int k = 1; k < P; ++k) s += part[k * W + c];
+    }
   }
+  if (q == 0) dst[c] = (float)s;
   __syncthreads();
 }
 
@@ -172,62 +185,6 @@ struct DwWave {
 // operations of one wave complete in order).
 __device__ __forceinline__ void wave_lds_fence() {
   asm volatile("" ::: "memory");
-}
-
-// Indices of one edge per lane: receiver, sender, multiplicity, and the next
-// edge's receiver (-1 past the tile); past the tile's end those of e_last.
-struct EdgeIdx {
-  int ri, sj, md, nx;
-  __device__ __forceinline__ void fetch(const DevGraph& gr, int64_t k, int64_t e1, int64_t e_last) {
-    const int64_t kk = k < e1 ? k : e_last;
-    ri = gr.recv[kk];
-    sj = gr.col[kk];
-    md = gr.mult[kk];
-    nx = (k + 1 < e1) ? gr.recv[k + 1] : -1;
-  }
-  // Complete the loads here: the loop's entry state (or the stores that
-  // follow) then has no pending loads, else the compiler's wait for them
-  // also drains the stores.
-  __device__ __forceinline__ void settle() { asm volatile("" : "+v"(ri), "+v"(sj), "+v"(md), "+v"(nx)); }
-};
-
-// rows without incoming edges have g_P = 0
-template <int H>
-__device__ __forceinline__ void zero_empty_rows(const DevGraph& gr, int64_t r0, int64_t r1, float* __restrict__ g_P,
-                                                int lane) {
-  for (int64_t r = r0 + (lane >> 2); r < r1; r += 16) {
-    if (gr.rowptr[r] == gr.rowptr[r + 1]) {
-      float* dst = g_P + r * H;
-      for (int c = (lane & 3) * 4; c < H; c += 16) *reinterpret_cast<float4*>(dst + c) = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  }
-}
-
-// g_P of one block: segmented sum of gh per receiver, the open row's partial
-// sum handed from lane 15 of one block to lane 0 of the next through LDS
-// (same wave, so no barrier is needed).  Lanes past the tile's last edge hold
-// gh = 0 and a key of their own, so they add nothing to any row's sum.
-template <int H>
-__device__ __forceinline__ void edge_gp(float (&t)[H / 4], float* __restrict__ carry, int& carry_key, int key,
-                                        bool last, float* __restrict__ dst, int j, int g) {
-  constexpr int NF = H / 4;
-  if (j == 0 && key == carry_key) {
-#pragma unroll
-    for (int i = 0; i < NF; i += 4) {
-      const float4 c = *reinterpret_cast<const float4*>(carry + i);
-      t[i] += c.x;
-      t[i + 1] += c.y;
-      t[i + 2] += c.z;
-      t[i + 3] += c.w;
-    }
-  }
-  seg_scan16<NF>(t, key);
-  if (last) store_row<H>(dst, g, t);
-  if (j == 15) {
-#pragma unroll
-    for (int i = 0; i < NF; i += 4) *reinterpret_cast<float4*>(carry + i) = make_float4(t[i], t[i + 1], t[i + 2], t[i + 3]);
-  }
-  carry_key = from_prev_lane_i(key);
 }
 
 }  // namespace mp

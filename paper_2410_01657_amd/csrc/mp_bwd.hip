@@ -594,6 +594,7 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
 #pragma unroll
   for (int i = 0; i < NF; ++i) db2[i] = dga[i] = dbe[i] = 0.f;
 
+  bool nan = false;  // an infinite operand met (or a NaN)
   for (int64_t tile = ts.t0 + ts.rank * NW + wave; tile < ts.t1; tile += ts.nr * NW) {
     const int64_t r0 = gr.tile_r[tile], r1 = gr.tile_r[tile + 1];
     const int64_t e0 = gr.tile_e[tile], e1 = gr.tile_e[tile + 1];
@@ -618,7 +619,7 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       const int64_t k = base + j;
       const bool valid = k < e1;
       const int64_t kk = valid ? k : e_last;
-      const int ri = ic.ri, sj = ic.sj;
+      const int ri = ic.ri;
       const float inv_d = 1.f / (float)ic.md;
       const bool last = valid && ic.nx != ri;
       const int key = valid ? ri + 1 : -1;
@@ -653,7 +654,7 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       make_op(u, o);
       stage_op<H>(tA2, Dw::AP, ln & 15, ln >> 4, o);
       gemm_wn<false, H, H>(w2, o, mp, ln);
-      const bool m_nan = mp[0] != mp[0];
+      nan |= mp[0] != mp[0];
 
       // gradient reaching e', LayerNorm adjoint (mp becomes gm)
 #pragma unroll
@@ -661,9 +662,10 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
         const float v = gE[i] * inv_d + go[i];
         gE[i] = valid ? v : 0.f;
       }
-      // gm and gh below carry the row's sign
+      // gm carries the row's sign, and at H = 32 gh: at 64 the bias of g_e (2^-33 of
+      // a term) is left, and ELU' takes the sign off at no cost
       const float sg = row_sign(gE[0]);
-      const uint32_t flip = dw_flip(wave, sg);
+      const uint32_t flip = dw_flip(wave, sg), flip1 = H == 32 ? flip : dw_flip(wave, 1.f);
       if (a.ln) {
         float mean, rstd, gam[NF];
         ln_stats<H>(mp, a.eps, mean, rstd);
@@ -697,47 +699,23 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
       wave_lds_fence();
       d2.add(tG2, tA2, ln);
 #pragma unroll
-      for (int i = 0; i < NF; ++i) t[i] *= elu_deriv_from_value(u[i]);
+      for (int i = 0; i < NF; ++i)
+        t[i] *= H == 32 ? elu_deriv_from_value(u[i]) : __builtin_amdgcn_fmed3f(fmaf(u[i], sg, sg), -1.f, 1.f);
       if constexpr (AM) {  // the residual carries the next layer's gradient only
 #pragma unroll
         for (int i = 0; i < NF; ++i) gE[i] = valid ? go[i] : 0.f;
       }
       // g_e = gE + W1c^T gh; dW1c += gh e^T
       make_op(t, o);
-      gemm_wt<false, H, H, ACC_ADD>(w1c, o, gE, ln, sg);
-      stage_op<H>(tG1, Dw::GP, ln & 15, ln >> 4, o, flip);
+      gemm_wt<false, H, H, ACC_ADD>(w1c, o, gE, ln, H == 32 ? sg : 1.f);
+      stage_op<H>(tG1, Dw::GP, ln & 15, ln >> 4, o, flip1);
       wave_lds_fence();
       d1.add(tG1, tA1, ln);
+      if constexpr (H == 32) {
 #pragma unroll
-      for (int i = 0; i < NF; ++i) t[i] *= sg;
-      if (wodd || __ballot(m_nan || gE[0] != gE[0])) {
-        // an infinite operand: this block's g_e and g_h with FP32 instructions
-        float z[NF], u1[1][NF], w[NF];
-        auto w2m = [&](int) { return a.w2.w; };
-        load_row<H>(reinterpret_cast<const float*>(a.e_in) + kk * H, g, w);
-        load_row<H>(a.P + (int64_t)ri * H, g, z);
-        load_row<H>(a.Q + (int64_t)sj * H, g, t);
-#pragma unroll
-        for (int i = 0; i < NF; ++i) z[i] += t[i];
-        gemm_exact<H, H>(a.w1c.w, w, z, lane);
-        exact_forward<H, 1>(w2m, [&](int) { return vecs; }, z, u1, lane);
-        load_row<H>(a.g_a + (int64_t)ri * H, g, t);
-        if (a.g_e_out) {
-          load_row<H>(reinterpret_cast<const float*>(a.g_e_out) + kk * H, g, w);
-        } else {
-#pragma unroll
-          for (int i = 0; i < NF; ++i) w[i] = 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < NF; ++i) {
-          const float v = t[i] * inv_d + w[i];
-          t[i] = valid ? v : 0.f;
-          gE[i] = AM ? (valid ? w[i] : 0.f) : t[i];
-        }
-        if (a.ln) ln_adjoint<H>(z, t, vecs + H, a.eps, lane);
-        exact_adjoint<H, 1>(w2m, u1, t, lane);
-        gemm_exact_t<H, H>(a.w1c.w, t, gE, lane);
+        for (int i = 0; i < NF; ++i) t[i] *= sg;
       }
+      nan |= gE[0] != gE[0];
       nx.settle();
       in.settle();
       if (valid) {
@@ -755,6 +733,21 @@ __global__ __launch_bounds__(256, (H == 64 ? 1 : 2)) void k_edge_bwd_f32(EdgeBwd
   block_sum_vec<H, NW>(db2, scratch, slab + 2 * H * H, wave, lane);
   block_sum_vec<H, NW>(dga, scratch, slab + 2 * H * H + H, wave, lane);
   block_sum_vec<H, NW>(dbe, scratch, slab + 2 * H * H + 2 * H, wave, lane);
+  if (wodd || __ballot(nan)) {
+    auto pre = [&](int ri, int sj, const float (&e)[NF], float (&z)[NF]) {
+      float q[NF];
+      load_row<H>(a.P + (int64_t)ri * H, g, z);
+      load_row<H>(a.Q + (int64_t)sj * H, g, q);
+#pragma unroll
+      for (int i = 0; i < NF; ++i) z[i] += q[i];
+      gemm_exact<H, H>(a.w1c.w, e, z, lane);
+    };
+    for (int64_t tile = ts.t0 + ts.rank * NW + wave; tile < ts.t1; tile += ts.nr * NW)
+      exact_edge_adjoint_tile<H, 1>(
+          gr, tile, reinterpret_cast<const float*>(a.e_in), reinterpret_cast<const float*>(a.g_e_out), a.g_a,
+          reinterpret_cast<float*>(a.g_e_in), reinterpret_cast<float*>(a.g_h), a.g_P, AM, carry, pre, a.w1c.w,
+          [&](int) { return a.w2.w; }, [&](int) { return vecs; }, a.ln ? vecs + H : nullptr, a.eps, lane);
+  }
 }
 
 template <int H, bool AM, int NWQ>

@@ -51,6 +51,18 @@ __device__ __forceinline__ void stage_vecs(float* __restrict__ v, const float* _
   }
 }
 
+// The Linears after the first of an MLP with K inputs: matrices in device memory,
+// biases in LDS (stage_vecs).
+struct Rest {
+  const float* theta;
+  int K;
+  __device__ __forceinline__ WView operator()(int l) const { return WView{theta + off_hid(K, l), kH, 0}; }
+  struct Bias {
+    const float* v;
+    __device__ __forceinline__ const float* operator()(int l) const { return v + (l + 1) * kH; }
+  };
+};
+
 // ------------------------------------------------------------------ forward
 
 template <int NH, int K>
@@ -70,12 +82,11 @@ struct Fwd32 {
     stage_vecs<NH>(v, theta, K, ln);
     note_odd(odd, o);
   }
-  // y = [LN] MLP(in); again(x): the input rows once more, for a block with an
-  // infinite operand (wodd: every block)
+  // y = [LN] MLP(in); odd(y): called with the last Linear's output
   template <class F>
   static __device__ __forceinline__ void run(const char* __restrict__ w, const float* __restrict__ v,
                                              const Op<false, K>& in, int ln, float eps, int lane, float (&y)[kNF],
-                                             bool wodd, const float* __restrict__ theta, F&& again) {
+                                             F&& odd) {
     const int g = lane >> 4;
     float u[kNF];
     load_vec<kH>(v, g, u);
@@ -89,14 +100,7 @@ struct Fwd32 {
 #pragma unroll
       for (int i = 0; i < kNF; ++i) u[i] = y[i];
     }
-    if (wodd || any_nan(y[0])) {
-      float x[K / 4], ue[NH + 1][kNF];
-      again(x);
-      load_vec<kH>(v, g, y);
-      gemm_exact<kH, K>(WView{theta, K, 0}, x, y, lane);
-      exact_forward<kH, NH + 1>([&](int l) { return WView{theta + off_hid(K, l), kH, 0}; },
-                                [&](int l) { return v + (l + 1) * kH; }, y, ue, lane);
-    }
+    odd(y);
     if (ln) {
       float mean, rstd, gam[kNF], bet[kNF];
       ln_stats<kH>(y, eps, mean, rstd);
@@ -113,11 +117,6 @@ template <int K>
 __device__ __forceinline__ void put_piece(Op<false, K>& o, int p, const float (&x)[kNF]) {
   split3_8(x, o.h[p], o.m[p], o.l[p]);
 }
-template <int K>
-__device__ __forceinline__ void load_piece(float (&x)[K], int p, const float* __restrict__ row, int g) {
-  load_row<kH>(row, g, *reinterpret_cast<float(*)[kNF]>(&x[p * kNF]));
-}
-
 // Eq. 4a-b, as k_edge_fwd: one row-aligned tile at a time per wave, the
 // aggregate by a segmented scan over the 16 edges of a block.
 template <int NH>
@@ -134,6 +133,7 @@ __global__ __launch_bounds__((64 * Fwd32<NH, 96>::NW), 4) void k_deep32_edge_fwd
   const DevGraph& gr = a.g;
   const int lane = lane_id(), j = lane & 15, g = lane >> 4;
   const TileSched ts = tile_sched(gr.n_tiles);
+  bool nan = false;  // an infinite operand met (or a NaN)
   for (int64_t tile = ts.t0 + ts.rank * F::NW + threadIdx.x / 64; tile < ts.t1; tile += ts.nr * F::NW) {
     const int64_t r0 = gr.tile_r[tile], r1 = gr.tile_r[tile + 1];
     const int64_t e0 = gr.tile_e[tile], e1 = gr.tile_e[tile + 1];
@@ -160,11 +160,7 @@ __global__ __launch_bounds__((64 * Fwd32<NH, 96>::NW), 4) void k_deep32_edge_fwd
       put_piece(in, 0, xi);
       put_piece(in, 1, xj);
       put_piece(in, 2, ev);
-      F::run(wl + oz, vecs + oz, in, a.ln, a.eps, lane, m, wodd, a.theta, [&](float (&x)[3 * kNF]) {
-        load_piece(x, 0, a.x + (int64_t)ri * kH, g);
-        load_piece(x, 1, a.x + (int64_t)sj * kH, g);
-        load_piece(x, 2, a.e_in + (valid ? k : e_last) * kH, g);
-      });
+      F::run(wl + oz, vecs + oz, in, a.ln, a.eps, lane, m, [&](float (&y)[kNF]) { nan |= y[0] != y[0]; });
 #pragma unroll
       for (int i = 0; i < kNF; ++i) ev[i] += m[i];
       if (valid) store_row<kH>(a.e_out + k * kH, g, ev);
@@ -174,6 +170,19 @@ __global__ __launch_bounds__((64 * Fwd32<NH, 96>::NW), 4) void k_deep32_edge_fwd
     }
     zero_empty_rows<kH>(gr, r0, r1, a.a_out, lane);
   }
+  if (!wodd && !__ballot(nan)) return;
+  auto pre = [&](int ri, int sj, const float (&e)[kNF], float (&z)[kNF]) {
+    float x[kNF];
+    load_vec<kH>(vecs, g, z);
+    load_row<kH>(a.x + (int64_t)ri * kH, g, x);
+    gemm_exact<kH, kH>(WView{a.theta, 96, 0}, x, z, lane);
+    load_row<kH>(a.x + (int64_t)sj * kH, g, x);
+    gemm_exact<kH, kH>(WView{a.theta + kH, 96, 0}, x, z, lane);
+    gemm_exact<kH, kH>(WView{a.theta + 2 * kH, 96, 0}, e, z, lane);
+  };
+  for (int64_t tile = ts.t0 + ts.rank * F::NW + threadIdx.x / 64; tile < ts.t1; tile += ts.nr * F::NW)
+    exact_edge_tile<kH, NH + 1>(gr, tile, a.e_in, a.e_out, a.a_out, a.am, carry, pre, Rest{a.theta, 96},
+                                Rest::Bias{vecs}, a.ln ? vecs + (NH + 2) * kH : nullptr, a.eps, lane);
 }
 
 // Eq. 4e: x' = x + MLP([a*, x]).
@@ -199,9 +208,17 @@ __global__ __launch_bounds__((64 * Fwd32<NH, 64>::NW), 4) void k_deep32_node_fwd
     Op<false, 64> in;
     put_piece(in, 0, s);
     put_piece(in, 1, x);
-    F::run(wl + oz, vecs + oz, in, a.ln, a.eps, lane, y, wodd, a.theta, [&](float (&again)[2 * kNF]) {
-      load_piece(again, 0, a.src_a + rr * kH, g);
-      load_piece(again, 1, a.src_b + rr * kH, g);
+    F::run(wl + oz, vecs + oz, in, a.ln, a.eps, lane, y, [&](float (&z)[kNF]) {
+      if (!wodd && !any_nan(z[0])) return;
+      float again[kNF], u[NH + 1][kNF];
+      const int l = lane + oz;
+      const float* v = vecs + oz;
+      load_vec<kH>(v, g, z);
+      load_row<kH>(a.src_a + rr * kH, g, again);
+      gemm_exact<kH, kH>(WView{a.theta, 64, 0}, again, z, l);
+      load_row<kH>(a.src_b + rr * kH, g, again);
+      gemm_exact<kH, kH>(WView{a.theta + kH, 64, 0}, again, z, l);
+      exact_forward<kH, NH + 1>(Rest{a.theta, 64}, Rest::Bias{v}, z, u, l);
     });
 #pragma unroll
     for (int i = 0; i < kNF; ++i) y[i] += x[i];
@@ -254,19 +271,6 @@ struct Bwd32 {
     stage_vecs<NH>(v, theta, ld, ln);
     note_odd(odd, o);
   }
-  // For a block with an infinite operand: from the input x, z less W0 x and the
-  // output's gradient t, the first pre-activation's gradient in t.
-  static __device__ __forceinline__ void exact(const float* __restrict__ theta, const float* __restrict__ w0, int ld,
-                                               const float* __restrict__ v, const float (&x)[K / 4], float (&z)[kNF],
-                                               float (&t)[kNF], int ln, float eps, int lane) {
-    float u[NH + 1][kNF];
-    auto W = [&](int l) { return WView{theta + off_hid(ld, l), kH, 0}; };
-    gemm_exact<kH, K>(WView{w0, ld, 0}, x, z, lane);
-    exact_forward<kH, NH + 1>(W, [&](int l) { return v + (l + 1) * kH; }, z, u, lane);
-    if (ln) ln_adjoint<kH>(z, t, v + (NH + 2) * kH, eps, lane);
-    exact_adjoint<kH, NH + 1>(W, u, t, lane);
-  }
-
   // Forward and adjoint of one block.  z: what the first matrix's product is
   // added to (bias, or P + Q); gE(y): the gradient arriving at the output, zero
   // on absent rows, asked for once the forward is done; done(d, o, sg, nan): called
@@ -404,14 +408,15 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) voi
   char* wl = reinterpret_cast<char*>(smem) + B::NW * B::WTILE;
   float* vecs = reinterpret_cast<float*>(wl + B::WB);
   float* carry = reinterpret_cast<float*>(wl + B::WB + B::VECS) + wave * kH + g * kNF;
-  int* odd = reinterpret_cast<int*>(wl + B::WB + B::VECS + B::NW * B::CARRY);
-  B::stage(wl, vecs, odd, a.theta, a.theta + 64, 96, a.ln);
+  int* slots = reinterpret_cast<int*>(wl + B::WB + B::VECS + B::NW * B::CARRY);
+  B::stage(wl, vecs, slots, a.theta, a.theta + 64, 96, a.ln);
   __syncthreads();
-  const bool wodd = read_odd(odd);
+  const bool wodd = read_odd(slots);
   const DevGraph& gr = a.g;
   const TileSched ts = tile_sched(gr.n_tiles);
   B acc;
   const int passes = NH ? a.passes : 1;
+  bool odd = false;  // an infinite operand met (or a NaN)
   for (int p = 0; p < passes; ++p) {
     acc.zero();
     const int64_t p0 = ts.t0 + (ts.t1 - ts.t0) * p / passes, p1 = ts.t0 + (ts.t1 - ts.t0) * (p + 1) / passes;
@@ -442,7 +447,7 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) voi
         const int64_t k = base + j;
         const bool valid = k < e1;
         const int64_t kk = valid ? k : e_last;
-        const int ri = ic.ri, sj = ic.sj;
+        const int ri = ic.ri;
         const float inv_d = 1.f / (float)ic.md;
         const bool last = valid && ic.nx != ri;
         const int key = valid ? ri + 1 : -1;
@@ -479,29 +484,7 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) voi
               in.settle();
 #pragma unroll
               for (int i = 0; i < kNF; ++i) d[i] *= sg;
-              if (wodd || __ballot(nan || ge[0] != ge[0])) {
-                float x[kNF], zz[kNF], t[kNF];
-                load_row<kH>(a.e_in + kk * kH, g, x);
-                load_row<kH>(a.P + (int64_t)ri * kH, g, zz);
-                load_row<kH>(a.Q + (int64_t)sj * kH, g, t);
-#pragma unroll
-                for (int i = 0; i < kNF; ++i) zz[i] += t[i];
-                load_row<kH>(a.g_a + (int64_t)ri * kH, g, d);
-                if (a.g_e_out) {
-                  load_row<kH>(a.g_e_out + kk * kH, g, t);
-                } else {
-#pragma unroll
-                  for (int i = 0; i < kNF; ++i) t[i] = 0.f;
-                }
-#pragma unroll
-                for (int i = 0; i < kNF; ++i) {
-                  const float s = d[i] * inv_d + t[i];
-                  d[i] = valid ? s : 0.f;
-                  ge[i] = a.am ? t[i] : d[i];
-                }
-                B::exact(a.theta, a.theta + 64, 96, vecs, x, zz, d, a.ln, a.eps, lane);
-                gemm_exact_t<kH, kH>(WView{a.theta + 64, 96, 0}, d, ge, lane);
-              }
+              odd |= nan || ge[0] != ge[0];
               if (valid) {
                 store_row<kH>(a.g_e_in + k * kH, g, ge);
                 store_row<kH>(a.g_h + k * kH, g, d);
@@ -512,6 +495,22 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) voi
       zero_empty_rows<kH>(gr, r0, r1, a.g_P, lane);
     }
     acc.store(reinterpret_cast<float*>(smem), a.part + ((int64_t)p * gridDim.x + blockIdx.x) * a.slab, a.ln, wave, lane);
+  }
+  if (!wodd && !__ballot(odd)) return;
+  auto pre = [&](int ri, int sj, const float (&e)[kNF], float (&z)[kNF]) {
+    float q[kNF];
+    load_row<kH>(a.P + (int64_t)ri * kH, g, z);
+    load_row<kH>(a.Q + (int64_t)sj * kH, g, q);
+#pragma unroll
+    for (int i = 0; i < kNF; ++i) z[i] += q[i];
+    gemm_exact<kH, kH>(WView{a.theta + 64, 96, 0}, e, z, lane);
+  };
+  for (int p = 0; p < passes; ++p) {  // the tiles this wave ran, in its passes
+    const int64_t p0 = ts.t0 + (ts.t1 - ts.t0) * p / passes, p1 = ts.t0 + (ts.t1 - ts.t0) * (p + 1) / passes;
+    for (int64_t tl = p0 + ts.rank * B::NW + wave; tl < p1; tl += ts.nr * B::NW)
+      exact_edge_adjoint_tile<kH, NH + 1>(gr, tl, a.e_in, a.g_e_out, a.g_a, a.g_e_in, a.g_h, a.g_P, a.am, carry, pre,
+                                          WView{a.theta + 64, 96, 0}, Rest{a.theta, 96}, Rest::Bias{vecs},
+                                          a.ln ? vecs + (NH + 2) * kH : nullptr, a.eps, lane);
   }
 }
 
@@ -559,10 +558,14 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 64>::NW), (Bwd32<NH, 64>::OCC)) voi
           }
           gemm_wt<false, kH, 64, ACC_ADD>(wl + oz, od, gi, ln, sg);
           if (wodd || __ballot(nan || gi[0] != gi[0])) {
-            float again[2 * kNF], zz[kNF];
-            load_piece(again, 0, a.a_star + rr * kH, g);
-            load_piece(again, 1, a.x + rr * kH, g);
-            load_vec<kH>(vecs, g, zz);
+            float again[kNF], zz[kNF], u[NH + 1][kNF];
+            const float* v = vecs + oz;
+            load_vec<kH>(v, g, zz);
+            load_row<kH>(a.a_star + rr * kH, g, again);
+            gemm_exact<kH, kH>(WView{a.theta, 64, 0}, again, zz, ln);
+            load_row<kH>(a.x + rr * kH, g, again);
+            gemm_exact<kH, kH>(WView{a.theta + kH, 64, 0}, again, zz, ln);
+            exact_forward<kH, NH + 1>(Rest{a.theta, 64}, Rest::Bias{v}, zz, u, ln);
             load_row<kH>(a.g_out + rr * kH, g, d);
 #pragma unroll
             for (int i = 0; i < kNF; ++i) {
@@ -570,8 +573,9 @@ __global__ __launch_bounds__((64 * Bwd32<NH, 64>::NW), (Bwd32<NH, 64>::OCC)) voi
               gi[kNF + i] = d[i];
               d[i] = valid ? d[i] : 0.f;
             }
-            B::exact(a.theta, a.theta, 64, vecs, again, zz, d, a.ln, a.eps, lane);
-            gemm_exact_t<kH, 64>(WView{a.theta, 64, 0}, d, gi, lane);
+            if (a.ln) ln_adjoint<kH>(zz, d, v + (NH + 2) * kH, a.eps, ln);
+            exact_adjoint<kH, NH + 1>(Rest{a.theta, 64}, u, d, ln);
+            gemm_exact_t<kH, 64>(WView{a.theta, 64, 0}, d, gi, ln);
           }
           if (valid) {
             store_row<kH>(a.g_a + row * kH, g, *reinterpret_cast<float(*)[kNF]>(gi));

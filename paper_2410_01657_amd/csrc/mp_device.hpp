@@ -258,12 +258,10 @@ __device__ __forceinline__ void gemm_bf16(const uint4* __restrict__ frag, const 
 //
 // An infinite operand has no parts: its remainder is inf - inf, so every output
 // it reaches is NaN.  The kernels look for one (a NaN among their results, or an
-// infinite weight met while staging, stage_wfrag) and then compute that block of
-// 16 rows again with FP32 instructions on the matrices in device memory
-// (gemm_exact), whose infinities are those of FP32 arithmetic.  That branch is
-// not taken for finite values and its test is one or two compares per block (1% of
-// the edge kernels' time).  Only sums over rows keep the parts' result: a weight
-// gradient with an infinite factor is not finite either way.
+// infinite weight met while staging, stage_wfrag) and then compute those rows
+// again with FP32 instructions (mp_exact.hpp), whose infinities are those of FP32
+// arithmetic.  Only sums over rows keep the parts' result: a weight gradient with
+// an infinite factor is not finite either way.
 //
 // Op<BF, W>: a W-wide row in the row-block layout as matrix operand; lane
 // value q of chunk t is in[8t + q].
@@ -504,36 +502,6 @@ __device__ __forceinline__ bool read_odd(const int* __restrict__ slots) {
 }
 __device__ __forceinline__ bool any_nan(float x) { return __ballot(x != x) != 0; }
 
-// acc += A in with FP32 instructions, A(m, k) read from device memory, of any
-// alignment.  For the rare block with an infinite operand.
-template <int M, int K, class F>
-__device__ __forceinline__ void gemm_exact_of(F&& el, const float (&in)[K / 4], float (&acc)[M / 4], int lane) {
-  const int l = lane + opaque_zero(), i = l & 15, k = l >> 4;  // no address held outside the branch
-  v4f c[M / 16];
-#pragma unroll
-  for (int mb = 0; mb < M / 16; ++mb) c[mb] = v4f{acc[4 * mb], acc[4 * mb + 1], acc[4 * mb + 2], acc[4 * mb + 3]};
-#pragma unroll
-  for (int s = 0; s < K / 4; ++s) {
-    if (s % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // few weights in flight
-#pragma unroll
-    for (int mb = 0; mb < M / 16; ++mb)
-      c[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(el(16 * mb + i, 16 * (s / 4) + 4 * k + s % 4), in[s], c[mb], 0, 0, 0);
-  }
-#pragma unroll
-  for (int mb = 0; mb < M / 16; ++mb) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) acc[4 * mb + r] = c[mb][r];
-  }
-}
-template <int M, int K>  // W M x K
-__device__ __forceinline__ void gemm_exact(const WView& w, const float (&in)[K / 4], float (&acc)[M / 4], int lane) {
-  gemm_exact_of<M, K>([&](int m, int k) { return w.p[(int64_t)m * w.ld + k]; }, in, acc, lane);
-}
-template <int M, int K>  // W^T in
-__device__ __forceinline__ void gemm_exact_t(const WView& w, const float (&in)[M / 4], float (&acc)[K / 4], int lane) {
-  gemm_exact_of<K, M>([&](int m, int k) { return w.p[(int64_t)k * w.ld + m]; }, in, acc, lane);
-}
-
 // acc += W in, W staged by stage_wfrag.
 template <bool BF, int M, int K>
 __device__ __forceinline__ void gemm_wf(const void* __restrict__ w, const Op<BF, K>& in, float (&acc)[M / 4],
@@ -760,50 +728,6 @@ __device__ __forceinline__ void ln_stats(const float (&v)[W / 4], float eps, flo
   }
   const float var = row_sum(q) * (1.f / W);
   rstd = 1.f / sqrtf(var + eps);
-}
-
-// The Linears after an MLP's first, with gemm_exact: u[l] = ELU(z), z = bias(l) +
-// W(l) u[l] for l = 0 .. NL - 1, and back: g = (W(l)^T g) ELU'(u[l]).
-template <int H, int NL, class FW, class FB>
-__device__ __forceinline__ void exact_forward(FW&& W, FB&& bias, float (&z)[H / 4], float (&u)[NL][H / 4], int lane) {
-#pragma unroll
-  for (int l = 0; l < NL; ++l) {
-#pragma unroll
-    for (int i = 0; i < H / 4; ++i) u[l][i] = elu(z[i]);
-    load_vec<H>(bias(l), lane >> 4, z);
-    gemm_exact<H, H>(W(l), u[l], z, lane);
-  }
-}
-template <int H, int NL, class FW>
-__device__ __forceinline__ void exact_adjoint(FW&& W, const float (&u)[NL][H / 4], float (&g)[H / 4], int lane) {
-#pragma unroll
-  for (int l = NL - 1; l >= 0; --l) {
-    float t[H / 4];
-#pragma unroll
-    for (int i = 0; i < H / 4; ++i) t[i] = 0.f;
-    gemm_exact_t<H, H>(W(l), g, t, lane);
-#pragma unroll
-    for (int i = 0; i < H / 4; ++i) g[i] = t[i] * elu_deriv_from_value(u[l][i]);
-  }
-}
-// Adjoint of y = LN(z) for the gradient g at y, in place.
-template <int W>
-__device__ __forceinline__ void ln_adjoint(float (&z)[W / 4], float (&g)[W / 4], const float* __restrict__ gain,
-                                           float eps, int lane) {
-  float mean, rstd, gam[W / 4], s1 = 0.f, s2 = 0.f;
-  ln_stats<W>(z, eps, mean, rstd);
-  load_vec<W>(gain, lane >> 4, gam);
-#pragma unroll
-  for (int i = 0; i < W / 4; ++i) {
-    z[i] = (z[i] - mean) * rstd;
-    g[i] *= gam[i];
-    s1 += g[i];
-    s2 += g[i] * z[i];
-  }
-  s1 = row_sum(s1) * (1.f / W);
-  s2 = row_sum(s2) * (1.f / W);
-#pragma unroll
-  for (int i = 0; i < W / 4; ++i) g[i] = rstd * (g[i] - s1 - z[i] * s2);
 }
 
 // --------------------------------------------- small first/last Linears

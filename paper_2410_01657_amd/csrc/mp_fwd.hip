@@ -6,6 +6,7 @@
 #include <algorithm>
 
 #include "mp_device.hpp"
+#include "mp_exact.hpp"
 #include "mp_kernels.hpp"
 
 namespace mp {
@@ -266,6 +267,22 @@ __global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (H > 6
   const int64_t V = gridDim.x < 8 ? gridDim.x : 8;
   const int x0 = (int)(blockIdx.x % V);
   int qi = 0;
+  bool m_nan = false;  // SPLIT: an infinite operand met (or a NaN)
+  auto again = [&](int64_t tile) {
+    if constexpr (SPLIT) {
+      auto pre = [&](int ri, int sj, const float (&e)[NF], float (&z)[NF]) {
+        float q[NF];
+        load_row<H>(P + (int64_t)ri * H, g, z);
+        load_row<H>(Q + (int64_t)sj * H, g, q);
+#pragma unroll
+        for (int i = 0; i < NF; ++i) z[i] += q[i];
+        gemm_exact<H, H>(w1c.w, e, z, lane);
+      };
+      exact_edge_tile<H, 1>(gr, tile, reinterpret_cast<const float*>(e_in), reinterpret_cast<float*>(e_out), a_out, AM,
+                            carry, pre, [&](int) { return w2.w; }, [&](int) { return vecs; }, ln ? vecs + H : nullptr,
+                            eps, lane);
+    }
+  };
 
   for (int64_t tile = DQ ? queue_next(gr.queue, gr.n_tiles, V, x0, qi) : ts.t0 + ts.rank * nw + threadIdx.x / 64;
        DQ ? tile >= 0 : tile < ts.t1;
@@ -273,6 +290,7 @@ __global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (H > 6
     const int64_t r0 = gr.tile_r[tile], r1 = gr.tile_r[tile + 1];
     const int64_t e0 = gr.tile_e[tile], e1 = gr.tile_e[tile + 1];
     int carry_key = 0;  // no open row at the start of a tile
+    if constexpr (DQ) m_nan = false;
 
     // Index loads run one block ahead (issued before the block's row
     // loads), so each block waits on one round trip to memory, for its rows.
@@ -329,15 +347,7 @@ __global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (H > 6
         gemm_wf<BF, H, H>(frb + FB, h, m, lane);
       else
         gemm<BF, MB, MB>(frb + FB, h, m, lane);
-      if (SPLIT && (wodd || any_nan(m[0]))) {
-        float u1[1][NF];
-        load_row<H>(P + (int64_t)ri * H, g, m);
-        load_row<H>(Q + (int64_t)sj * H, g, q);
-#pragma unroll
-        for (int i = 0; i < NF; ++i) m[i] += q[i];
-        gemm_exact<H, H>(w1c.w, ev, m, lane);
-        exact_forward<H, 1>([&](int) { return w2.w; }, [&](int) { return vb; }, m, u1, lane);
-      }
+      if constexpr (SPLIT) m_nan |= m[0] != m[0];
       if (ln) {
         float mean, rstd, gam[NF], bet[NF];
         ln_stats<H>(m, eps, mean, rstd);
@@ -373,13 +383,14 @@ __global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (H > 6
       }
       carry_key = from_prev_lane_i(key);
     }
-    // rows without incoming edges aggregate to zero
-    for (int64_t r = r0 + (lane >> 2); r < r1; r += 16) {
-      if (gr.rowptr[r] == gr.rowptr[r + 1]) {
-        float* dst = a_out + r * H;
-        for (int c = (lane & 3) * 4; c < H; c += 16) *reinterpret_cast<float4*>(dst + c) = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
+    if constexpr (SPLIT && DQ) {
+      if (wodd || __ballot(m_nan)) again(tile);
     }
+    zero_empty_rows<H>(gr, r0, r1, a_out, lane);  // they aggregate to zero
+  }
+  if constexpr (SPLIT && !DQ) {
+    if (wodd || __ballot(m_nan))
+      for (int64_t tile = ts.t0 + ts.rank * nw + threadIdx.x / 64; tile < ts.t1; tile += ts.nr * nw) again(tile);
   }
 }
 
@@ -584,7 +595,8 @@ __global__ __launch_bounds__((64 * MlpFwdCfg<H, KIN, TIN, TOUT, BF>::NW), (MlpFw
   const bool sep_resid = !TOUT && a.resid != nullptr && !(KIN == 2 * H && a.resid == a.src1);
   const bool has_resid = !TOUT && a.resid != nullptr;
 
-  int64_t blk = (int64_t)blockIdx.x * nw + threadIdx.x / 64;
+  // the wave's index as a scalar: its block number then takes no vector register
+  int64_t blk = (int64_t)blockIdx.x * nw + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   MlpFwdIn<H, KIN, TIN, TOUT> nx;
   nx.load(a, std::min<int64_t>(blk * 16 + j, n - 1), g, sep_resid);
   nx.settle();  // the loop's entry state holds no pending loads
@@ -606,17 +618,25 @@ __global__ __launch_bounds__((64 * MlpFwdCfg<H, KIN, TIN, TOUT, BF>::NW), (MlpFw
       gemm<BF, MB, KB>(f0 + opaque_zero(), cur.in, z, lane);
     }
     // the first pre-activation with FP32 instructions, from the rows in memory
-    auto exact_z = [&](float (&zz)[NF]) {
-      MlpFwdIn<H, KIN, TIN, TOUT> again;
-      again.load(a, std::min<int64_t>(row, n - 1), g, false);
-      load_vec<H>(vecs, g, zz);
-      if constexpr (TIN)
+    auto exact_z = [&](float (&zz)[NF], const float* v, int g) {
+      const int64_t rr = std::min<int64_t>(row, n - 1);
+      load_vec<H>(v, g, zz);
+      if constexpr (TIN) {
+        MlpFwdIn<H, KIN, TIN, TOUT> again;
+        again.load(a, rr, g, false);
         small_in_linear<H>(small, again.in, g, zz);
-      else
-        gemm_exact<H, KIN>(WView{a.W0, KIN, 0}, again.in, zz, lane);
+      } else {
+        float half[NF];
+        load_row<H>(a.src0 + rr * H, g, half);
+        gemm_exact<H, H>(WView{a.W0, KIN, 0}, half, zz, lane);
+        if constexpr (KIN == 2 * H) {
+          load_row<H>(a.src1 + rr * H, g, half);
+          gemm_exact<H, H>(WView{a.W0 + H, KIN, 0}, half, zz, lane);
+        }
+      }
     };
     if constexpr (C::SPLIT && TOUT) {
-      if (wodd || any_nan(z[0])) exact_z(z);
+      if (wodd || any_nan(z[0])) exact_z(z, vecs + opaque_zero(), g);
     }
 #pragma unroll
     for (int i = 0; i < NF; ++i) z[i] = elu(z[i]);
@@ -640,13 +660,7 @@ __global__ __launch_bounds__((64 * MlpFwdCfg<H, KIN, TIN, TOUT, BF>::NW), (MlpFw
         gemm_wf<BF, H, H>(f1 + opaque_zero(), z, y, lane);
       else
         gemm<BF, MB, MB>(f1 + opaque_zero(), z, y, lane);
-      if constexpr (C::SPLIT) {
-        if (wodd || any_nan(y[0])) {
-          float u1[1][NF];
-          exact_z(y);
-          exact_forward<H, 1>([&](int) { return WView{a.W1, H, 0}; }, [&](int) { return vecs + H; }, y, u1, lane);
-        }
-      }
+      const bool y_nan = C::SPLIT && y[0] != y[0];
       if (a.ln) {
         float mean, rstd, gm[NF], bt[NF];
         load_vec<H>(vb + 2 * H, g, gm);
@@ -667,6 +681,32 @@ __global__ __launch_bounds__((64 * MlpFwdCfg<H, KIN, TIN, TOUT, BF>::NW), (MlpFw
         }
       }
       nx.settle();  // next block's loads complete before this block's stores
+      if constexpr (C::SPLIT) {
+        if (wodd || __ballot(y_nan)) {  // all of it again, here where least is live
+          float t[NF], u1[1][NF];
+          const float* v = vecs + opaque_zero();
+          const int ln = lane + opaque_zero(), g = ln >> 4;
+          exact_z(y, v, g);
+          exact_forward<H, 1>([&](int) { return WView{a.W1, H, 0}; }, [&](int) { return v + H; }, y, u1, ln);
+          if (a.ln) {
+            float mean, rstd;
+            ln_stats<H>(y, a.eps, mean, rstd);
+#pragma unroll
+            for (int i = 0; i < NF; ++i) y[i] = (y[i] - mean) * rstd;
+            load_vec<H>(v + 2 * H, g, t);
+#pragma unroll
+            for (int i = 0; i < NF; ++i) y[i] *= t[i];
+            load_vec<H>(v + 3 * H, g, t);
+#pragma unroll
+            for (int i = 0; i < NF; ++i) y[i] += t[i];
+          }
+          if (has_resid) {
+            load_row<H>(a.resid + std::min<int64_t>(row, n - 1) * H, g, t);
+#pragma unroll
+            for (int i = 0; i < NF; ++i) y[i] += t[i];
+          }
+        }
+      }
       if (valid) store_row_t<H, OB>(a.out, row, g, y);
     }
   }
