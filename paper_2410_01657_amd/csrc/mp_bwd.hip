@@ -5,15 +5,17 @@
 // gathers of receiver/sender features become in-row sums (the sender part
 // through the reverse-edge index, so no atomics are needed).
 //
-// Weight gradients are sums over all rows of outer products.  The NW waves
-// of a workgroup (4 or 8) walk their rows in lock step: every wave stages
-// one 16-row block of the two factors in LDS, transposed, then each wave
-// accumulates its own subset of 16x16 gradient tiles over the 16*NW staged
-// rows with MFMA.  Each workgroup writes one slab of partial gradients;
-// launch_wreduce adds the slabs in workgroup order.  Where the fused form
-// does not fit on chip (H = 128), a streaming kernel writes the per-row
-// factors and k_row_dw forms the same sums from them.  Schedules are
-// static, so every result is bitwise reproducible.
+// Weight gradients are sums over all rows of outer products.  In BF16 the NW
+// waves of a workgroup (4 or 8) walk their rows in lock step: every wave stages
+// one 16-row block of the two factors in LDS, then each wave accumulates its own
+// subset of 16x16 gradient tiles over the 16*NW staged rows with MFMA, reading
+// them transposed; the FP32 row MLPs and sender side do the same from transposed
+// tiles.  In the FP32 edge adjoint (H <= 64) each wave sums its own rows (DwWave).
+// Each workgroup writes one slab of partial gradients; launch_wreduce adds the
+// slabs in workgroup order.  Where a fused form does not fit on chip (at H = 128
+// the node update, and in FP32 the edge adjoint and the sender side), a streaming
+// kernel writes the per-row factors and k_row_dw forms the same sums from them.
+// Schedules are static, so every result is bitwise reproducible.
 #include <algorithm>
 #include <type_traits>
 
@@ -39,10 +41,10 @@ namespace mp {
 // chunk c of row r sits at chunk c ^ stg_swz(r): with 32 chunks per LDS bank
 // cycle the 32 lanes of a half wave then hit all banks once, in the stores
 // (16 rows, two chunks each) and in the reads (8 rows, four chunks each),
-// with no padding.  Against the transposed tile: k_row_dw at H = 128 (bound by
-// its staging) 1.82 -> 1.55 ms per layer of 6.1M edges, the fused edge adjoint
-// (bound by its row traffic) 3.08 -> 3.00 ms at 11.1M edges, 1.88 -> 1.78 ms
-// with BF16 edge states at 6.6M, and 16 registers fewer.
+// with no padding.  Against the transposed tile: the fused edge adjoint (bound by
+// its row traffic) 3.08 -> 3.00 ms at 11.1M edges, 1.88 -> 1.78 ms with BF16 edge
+// states at 6.6M, and 16 registers fewer; a pass bound by its staging (6.1M rows,
+// 128 x 128) 1.82 -> 1.55 ms.
 template <bool BF, int ROWS>
 struct Stg {
   using T = typename std::conditional<BF, __bf16, float>::type;
@@ -972,7 +974,8 @@ hipError_t launch_edge_bwd(const EdgeBwdArgs& a, int grid, hipStream_t s) {
   if (a.es && !a.bf) return hipErrorInvalidValue;
   if (a.H == 32) return launch_edge_bwd_h<32>(a, grid, s);
   if (a.H == 64) return launch_edge_bwd_h<64>(a, grid, s);
-  if (a.H == 128 && a.bf) return a.am ? launch_edge_bwd_wide_t<128, true>(a, grid, s) : launch_edge_bwd_wide_t<128, false>(a, grid, s);
+  if (a.H == 128 && a.bf)
+    return a.am ? launch_edge_bwd_wide_t<128, true>(a, grid, s) : launch_edge_bwd_wide_t<128, false>(a, grid, s);
   return hipErrorInvalidValue;  // wide FP32 layers: launch_edge_bwd_split
 }
 
@@ -984,7 +987,7 @@ struct EdgeBwdSplitCfg {
   // NWQ independent waves sharing the LDS weight fragments: 8 (two per
   // SIMD, 256 registers each), or 4 (one per SIMD with up to 512: the
   // per-edge adjoint at H = 128 wants about 320, and at 256 the compiler
-  // spills).  Measured on C3 (one launch, same box): 14.3 ms at 8 waves,
+  // spills).  10.5M edges, one launch, same box: 14.3 ms at 8 waves,
   // whose products keep the matrix unit busy, 15.6 at 4.
   static_assert(NWQ == 4 || NWQ == 8, "4 or 8 waves per workgroup");
   static constexpr int NW = NWQ;
@@ -1003,9 +1006,9 @@ struct EdgeBwdSplitCfg {
 };
 
 // The FP32 edge adjoint without its matrix weight gradients, for widths where
-// staging tiles and accumulators do not fit next to the weights.  Per edge it computes what k_edge_bwd computes (g_e, g_h, the
-// segmented g_P) and writes the factors of the weight gradients instead of
-// accumulating them: gm and u (dW2 = sum gm u^T, db2 = sum gm); dW1c =
+// staging tiles and accumulators do not fit next to the weights.  Per edge it
+// computes what k_edge_bwd computes (g_e, g_h, the segmented g_P) and writes the
+// factors of the weight gradients instead of accumulating them: gm and u (dW2 = sum gm u^T, db2 = sum gm); dW1c =
 // sum g_h e^T is formed from g_h and e.  The LayerNorm-parameter gradients
 // (dbeta = sum gE, dgamma = sum gE * normalised m) are summed here: each
 // block's 16 rows are reduced across lanes (sum16_scatter, so a lane keeps
@@ -1058,8 +1061,7 @@ __global__ __launch_bounds__((64 * EdgeBwdSplitCfg<H, NWQ>::NW)) void k_edge_bwd
       // the lane's feature offset, recomputed per block: hoisted out of the
       // loop, every array's 64-bit base plus offset would be held in
       // registers (at eight waves they spilled, and their reloads
-      // serialised the block's row loads; C3: BF16 7.9 -> 7.3 ms, FP32
-      // 14.8 -> 14.3 ms per launch at eight waves)
+      // serialised the block's row loads: 10.5M edges 14.8 -> 14.3 ms)
       const int g = g0 + opaque_zero();
       const float inv_d = 1.f / (float)md_n;
       const bool last = valid && nx_n != ri;

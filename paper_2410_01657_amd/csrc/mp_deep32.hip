@@ -20,10 +20,11 @@
 // adjoint, the sums over receivers and senders, in k_gq.
 //
 // Five extra layers, 3.5M edges, 0.63M nodes, one layer forward and adjoint:
-// 9.44 -> 3.0 ms (edge adjoint with its weight gradients 6.2 -> 1.53 ms, edge
-// forward 1.65 -> 0.59, node adjoint 1.1 -> 0.32, sender sums 0.26 -> 0.18).
-// The edge adjoint issues 50% of its SIMD's vector slots and 27% of its matrix
-// cycles with one wave there: what does not overlap between the two adds up.
+// 9.41 -> 2.95 ms (edge adjoint with its weight gradients 5.2 -> 1.73 ms, edge
+// forward 1.63 -> 0.61, node adjoint 0.66 and its weight gradients -> 0.31, sender
+// sums 0.26 -> 0.18).  With its one wave per SIMD the edge adjoint has the matrix
+// unit busy in 27% of the cycles and issues vector instructions in 50%, a quarter of
+// the matrix cycles beside them: what does not overlap adds up.
 #include "mp_adjoint.hpp"
 
 namespace mp {
@@ -397,7 +398,7 @@ struct Bwd32 {
 // parts and b0, which k_gq forms from g_P and the senders' sums.  The
 // next block's first rows load while this one is computed.  A wave's weight
 // sums round in proportion to their own growing size, so a long run is summed
-// in a.passes parts, each its own slab (2M edges, NH = 5, gradient error
+// in a.passes parts, each its own slab (3.5M edges, NH = 5, gradient error
 // against FP64: 9.0e-7 in one part, 7.0e-7 in two; FP32 instructions 8.9e-7).
 template <int NH>
 __global__ __launch_bounds__((64 * Bwd32<NH, 32>::NW), (Bwd32<NH, 32>::OCC)) void k_deep32_edge_bwd(DeepSplitEdgeArgs a) {

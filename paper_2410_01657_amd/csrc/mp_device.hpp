@@ -249,12 +249,16 @@ __device__ __forceinline__ void gemm_bf16(const uint4* __restrict__ frag, const 
 // An FP32 value is the exact sum of three BF16 parts, x = h + m + l: h its
 // upper half, m the rounded remainder, l what then is left (8 + 8 + 8 bits).
 // Six of the nine part products give W x: the dropped m*l, l*m and l*l are
-// below 2^-22 of |w||x| and symmetric, and the products summed are exact in
+// below 2^-23 of |w||x| and symmetric, and the products summed are exact in
 // FP32.  The five small ones are summed apart and added once, so the large
-// sum takes K/32 roundings instead of the FP32 instruction's K/4: against FP64 (K = 64, normal values) the rms error is 4.6e-8 of the result,
-// 1.4e-7 with v_mfma_f32_16x16x4f32.  The rate: six v_mfma_f32_16x16x32_bf16
-// take 96 cycles for what eight 32-cycle FP32 instructions do, and unlike
-// those they issue beside vector instructions.
+// sum takes K/32 roundings instead of the FP32 instruction's K/4: against FP64
+// (normal values) the rms error is 5.0e-8 of the result at K = 64 and 3.9e-8 at
+// 32, with v_mfma_f32_16x16x4f32 1.44e-7 and 1.03e-7; one product alone is off by
+// up to 2.1e-7 (FP32: 6e-8).  With m*l and l*m that would be 6.0e-8, and 4.8e-8 over
+// 64 terms: no case measured came nearer to FP64 by them, and the FP32 forward took
+// 7%, the width-32 deep layers 13% longer.  The rate: six
+// v_mfma_f32_16x16x32_bf16 take 96 cycles for what eight 32-cycle FP32 instructions
+// do, and unlike those they issue beside vector instructions.
 //
 // An infinite operand has no parts: its remainder is inf - inf, so every output
 // it reaches is NaN.  The kernels look for one (a NaN among their results, or an
@@ -548,8 +552,9 @@ __device__ __forceinline__ int stg_swz(int row) {
   return ((k & (KR - 1)) << 2) | (((k / KR) & 1) << 1);
 }
 
-// MFMA operand of a tile, its rows along K: lane (i, kk) receives feature 16 fb + i of rows r0 + 4 kk + 0..3 and r0 + 16 + 4 kk + 0..3 (r0 a
-// multiple of 16; the same row order for both operands of a product).
+// MFMA operand of a tile, its rows along K: lane (i, kk) receives feature 16 fb + i
+// of rows r0 + 4 kk + 0..3 and r0 + 16 + 4 kk + 0..3 (r0 a multiple of 16; the same
+// row order for both operands of a product).
 // tr_base: the lane's address for feature block fb.
 typedef __attribute__((address_space(3))) v4bf lds_v4bf;
 template <int W>

@@ -119,7 +119,8 @@ static int fit_grid(int grid, int waves, int occ, size_t lds) {
 // `n_main` on compute the edge kernels' tile bounds, which the next launch
 // needs too (a launch of their own costs about 5 us of a small layer).
 template <int H, bool BF>
-__global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (fwd_occ<H, BF>(2 * w_bytes(H, H, BF)))) void k_proj(
+__global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))),
+                             (fwd_occ<H, BF>(2 * w_bytes(H, H, BF)))) void k_proj(
     int64_t n_rows, const float* __restrict__ x, WSrc wa, WSrc wb, const float* __restrict__ b1,
     float* __restrict__ P, float* __restrict__ Q, int n_main, TileJob tj) {
   constexpr int NF = H / 4, MB = H / 16;
@@ -231,12 +232,11 @@ hipError_t launch_proj(int H, bool bf, int64_t n_rows, const float* x, const WSr
 // the fixed round robin of tile_sched.  ES: e_in and e_out hold BF16 (the
 // update and the aggregation run in FP32; e' is rounded where it is stored).
 template <int H, bool BF, bool AM, bool DQ, bool ES>
-__global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (H > 64 ? 2 : fwd_occ<H, BF>(2 * w_bytes(H, H, BF)))) void k_edge_fwd(DevGraph gr, const float* __restrict__ P,
-                                                  const float* __restrict__ Q, const void* __restrict__ e_in,
-                                                  WSrc w1c, WSrc w2, const float* __restrict__ b2,
-                                                  const float* __restrict__ lng, const float* __restrict__ lnb,
-                                                  int ln, float eps, void* __restrict__ e_out,
-                                                  float* __restrict__ a_out) {
+__global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))),
+                             (H > 64 ? 2 : fwd_occ<H, BF>(2 * w_bytes(H, H, BF)))) void k_edge_fwd(
+    DevGraph gr, const float* __restrict__ P, const float* __restrict__ Q, const void* __restrict__ e_in, WSrc w1c,
+    WSrc w2, const float* __restrict__ b2, const float* __restrict__ lng, const float* __restrict__ lnb, int ln,
+    float eps, void* __restrict__ e_out, float* __restrict__ a_out) {
   constexpr int NF = H / 4, MB = H / 16;
   constexpr bool RAW = raw_weights(H, BF), SPLIT = RAW && !BF;
   constexpr size_t FB = RAW ? w_bytes(H, H, BF) : frag_bytes(H, H, BF);
@@ -396,8 +396,8 @@ __global__ __launch_bounds__((64 * fwd_waves<BF>(2 * w_bytes(H, H, BF))), (H > 6
 
 template <int H, bool BF, bool AM, bool DQ, bool ES>
 static hipError_t launch_edge_fwd_t(const DevGraph& g, const float* P, const float* Q, const void* e_in,
-                                    const WSrc& w1c, const WSrc& w2, const float* b2, const float* lng, const float* lnb, int ln,
-                                    float eps, void* e_out, float* a_out, int grid, hipStream_t s) {
+                                    const WSrc& w1c, const WSrc& w2, const float* b2, const float* lng,
+                                    const float* lnb, int ln, float eps, void* e_out, float* a_out, int grid, hipStream_t s) {
   constexpr size_t FB = raw_weights(H, BF) ? w_bytes(H, H, BF) : frag_bytes(H, H, BF);
   constexpr int NW = fwd_waves<BF>(2 * FB);
   // fragments, 3 per-feature vectors, per-wave carries, infinite weights met
@@ -405,8 +405,8 @@ static hipError_t launch_edge_fwd_t(const DevGraph& g, const float* P, const flo
   if (lds > 64 * 1024)
     (void)hipFuncSetAttribute((const void*)k_edge_fwd<H, BF, AM, DQ, ES>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
-  hipLaunchKernelGGL((k_edge_fwd<H, BF, AM, DQ, ES>), dim3(grid), dim3(64 * NW), lds, s, g, P, Q, e_in, w1c, w2, b2, lng, lnb,
-                     ln, eps, e_out, a_out);
+  hipLaunchKernelGGL((k_edge_fwd<H, BF, AM, DQ, ES>), dim3(grid), dim3(64 * NW), lds, s, g, P, Q, e_in, w1c, w2, b2,
+                     lng, lnb, ln, eps, e_out, a_out);
   return hipGetLastError();
 }
 
@@ -423,8 +423,8 @@ static hipError_t launch_edge_fwd_am(bool am, bool dq, const DevGraph& g, const 
 }
 
 hipError_t launch_edge_fwd(int H, bool ln, bool bf, bool am, bool dq, bool es, const DevGraph& g, const float* P,
-                           const float* Q, const void* e_in, const WSrc& w1c, const WSrc& w2, const float* b2, const float* lng,
-                           const float* lnb, float eps, void* e_out, float* a_out, int grid, hipStream_t s) {
+                           const float* Q, const void* e_in, const WSrc& w1c, const WSrc& w2, const float* b2,
+                           const float* lng, const float* lnb, float eps, void* e_out, float* a_out, int grid, hipStream_t s) {
   if (es && !bf) return hipErrorInvalidValue;  // BF16 edge states go with BF16 products
 #define MP_CASE(HH)                                                                                              \
   if (H == HH) {                                                                                                 \
@@ -550,7 +550,8 @@ struct MlpFwdCfg {
 // OB: the H-wide output is stored as BF16 (the edge encoder's output, an
 // edge state, when edge states are BF16).
 template <int H, int KIN, bool TIN, bool TOUT, bool BF, bool OB>
-__global__ __launch_bounds__((64 * MlpFwdCfg<H, KIN, TIN, TOUT, BF>::NW), (MlpFwdCfg<H, KIN, TIN, TOUT, BF>::OCC)) void k_mlp_fwd(MlpFwdArgs a) {
+__global__ __launch_bounds__((64 * MlpFwdCfg<H, KIN, TIN, TOUT, BF>::NW),
+                             (MlpFwdCfg<H, KIN, TIN, TOUT, BF>::OCC)) void k_mlp_fwd(MlpFwdArgs a) {
   using C = MlpFwdCfg<H, KIN, TIN, TOUT, BF>;
   constexpr int NF = H / 4, MB = H / 16, KB = TIN ? 1 : KIN / 16;
   extern __shared__ uint4 smem[];
@@ -563,7 +564,10 @@ __global__ __launch_bounds__((64 * MlpFwdCfg<H, KIN, TIN, TOUT, BF>::NW), (MlpFw
     for (int t = threadIdx.x; t < 4 * H; t += blockDim.x) small[t] = (t / H) < a.n_out ? a.W1[t] : 0.f;
   for (int t = threadIdx.x; t < 4 * H; t += blockDim.x) {
     const int q = t / H, f = t % H;
-    vecs[t] = q == 0 ? a.b0[f] : q == 1 ? (TOUT ? 0.f : a.b1[f]) : q == 2 ? (a.ln ? a.lng[f] : 0.f) : (a.ln ? a.lnb[f] : 0.f);
+    vecs[t] = q == 0   ? a.b0[f]
+              : q == 1 ? (TOUT ? 0.f : a.b1[f])
+              : !a.ln  ? 0.f
+                       : (q == 2 ? a.lng[f] : a.lnb[f]);
   }
   int* odd = reinterpret_cast<int*>(vecs + 4 * H);  // SPLIT: per wave
   if constexpr (C::RAW) {
@@ -720,7 +724,8 @@ static hipError_t launch_mlp_fwd_t(const MlpFwdArgs& a, int grid, hipStream_t s)
   if (C::LDS > 64 * 1024)
     (void)hipFuncSetAttribute((const void*)k_mlp_fwd<H, KIN, TIN, TOUT, BF, OB>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
-  hipLaunchKernelGGL((k_mlp_fwd<H, KIN, TIN, TOUT, BF, OB>), dim3(fit_grid(grid, C::NW, H > 64 ? 2 : C::OCC, C::LDS)), dim3(64 * C::NW), C::LDS, s, a);
+  const int wgs = fit_grid(grid, C::NW, H > 64 ? 2 : C::OCC, C::LDS);
+  hipLaunchKernelGGL((k_mlp_fwd<H, KIN, TIN, TOUT, BF, OB>), dim3(wgs), dim3(64 * C::NW), C::LDS, s, a);
   return hipGetLastError();
 }
 

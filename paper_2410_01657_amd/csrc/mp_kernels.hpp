@@ -308,6 +308,12 @@ hipError_t launch_deep_gather(int H, const DevGraph& g, const float* gxn, const 
 // DeepEdgeArgs / DeepRowArgs (with the graph's tile bounds); the adjoints split
 // W0's node parts off (P = W0a x + b0, Q = W0b x given, their adjoint left to
 // launch_gq and launch_deep8_gq).
+// One layer forward and adjoint by the number of extra layers, 0 to 5, against the
+// row-per-thread kernels, in us: width 8, 3.2M edges 350 390 420 500 530 710 for 850
+// 1000 1100 1220 1300 1500, 95k edges 90 to 110 for 94 to 140; width 32, 3.2M edges
+// 1260 1690 1970 2250 2470 2780 for 4320 to 8620, 600 edges 90 to 100 for 280 to
+// 610.  Beyond five the width-32 adjoint's weights and tiles do not fit in LDS, and
+// the activations of width 8 not in registers.
 constexpr int kDeep32MaxHidden = 5;
 constexpr int kDeep8MaxHidden = 5;
 struct DeepSplitEdgeArgs {
